@@ -27,7 +27,8 @@ COPY_BYTES = 1 << 31  # device-to-device copy: achievable bandwidth, and the cou
 # Measured HBM traffic of the kernels (rocprofv3 read requests by size and
 # WRITE_SIZE), valid while the kernel sources hash as recorded there.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_16tenant-50kop-128dev.md")
-KERNEL_SOURCES = ("paper_2608_15762_amd/csrc/sim_fast.hip", "paper_2608_15762_amd/csrc/gmg_load.cpp")
+KERNEL_SOURCES = ("paper_2608_15762_amd/csrc/sim_fast.hip", "paper_2608_15762_amd/csrc/peaks.hip",
+                  "paper_2608_15762_amd/csrc/gmg_load.cpp")
 
 
 def parse():

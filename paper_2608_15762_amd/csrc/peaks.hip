@@ -1,0 +1,678 @@
+// Memory pass of the 32-bit path for graphs whose gap table fits one CU's LDS
+// (gfx950): per-device peaks of the residency intervals (Sec. 3.3.2) and the
+// violation verdict, one workgroup per candidate, with no interval record in
+// global memory.
+//
+// A device's ops run one at a time in dispatch order, so their starts
+// S[0..m) are sorted and cut the device's time into gaps 0..m.  Every event
+// falls into one gap:
+//   own output of rank k    allocated at S[k], counted as opening gap k + 1
+//   copy allocated at t     gap #{k : S[k] < t}
+//   free at t               gap #{k : S[k] < t}
+// (frees precede allocations at equal times: intervals are half-open).  A free
+// at the finish of a local op of rank k has gap k + 1; a copy is allocated at
+// or before the start of its first consumer, of rank k, so its gap is searched
+// downwards from k; a transfer-bound free of an op of rank k upwards from
+// k + 1.  With A[g] the bytes allocated and F[g] the bytes freed in gap g,
+//   L[g] = sum_{g' <= g} A[g'] - F[g']
+// is the live bytes before own g, so L[k] + own_k is exact at every own start,
+// and U[g] = L[g] + F[g] bounds the live bytes inside gap g.  Only a "hard"
+// gap, whose U exceeds the best exact value of its device, has its events
+// collected and swept in time order (0 to 4 events per gap and about three
+// such gaps per device with every op placed at random; one or two gaps per
+// candidate when a candidate moves a few ops of a partition).
+//
+// All devices of a candidate share one flat index space of N + D entries
+// (device d from gb[d], m + 1 entries), 12 bytes an entry with 32-bit byte
+// sums, so a workgroup walks the ops in index order with full lanes whatever
+// the devices' loads, the prefix sum is one block scan, and the only traffic
+// beyond the placement and finish rows is a two-byte rank and a two-byte gap
+// per op, which stay in the CU's caches.
+//
+// Bound: instruction issue and LDS access (no phase waits for memory beyond the
+// L2).  It takes the place of interval records in global memory, bucketed per
+// device and evaluated one device at a time in a wave of its own, whose fixed
+// cost per device was most of the pass on small graphs; before and after, for
+// the whole call: 256 candidates of 32 ops 111 and 52 us, 65,536 of 322 ops
+// 3.07 and 1.26 ms, 100,003 of 2,052 ops 13.97 and 7.20 ms, 131,072 of 10,000
+// ops 48.7 and 28.9 ms, 32,771 of a 2,001-op graph with 34 consumers of some
+// outputs 19.0 and 6.69 ms.  Graphs that do not fit keep the records.
+#include <algorithm>
+#include <climits>
+#include <type_traits>
+
+#include "peaks.h"
+
+namespace {
+
+constexpr int kWave = 64;
+constexpr uint32_t kInf32 = 0xFFFFFFFFu;
+constexpr uint32_t kNoEvent = 0xFFFFu;  // gap table: the own output is never freed
+// gap table entries hold the flat gap of the own free in the low bits and
+// this flag for an op with a copy on some device
+constexpr uint32_t kHasCopy = 0x8000u;
+constexpr int kMaxFlat = 0x7FFF;  // flat gaps a table entry can hold (kNoEvent & ~kHasCopy is none of them)
+
+__device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+
+__device__ __forceinline__ uint32_t link_bit(const GmgView &G, uint32_t a, uint32_t b) {
+  return (G.link_bits[a * G.link_words + (b >> 5)] >> (b & 31)) & 1u;
+}
+
+__device__ __forceinline__ uint32_t xfer_of(const GmgView &G, int u, int du, int d) {
+  const int K = G.n_link;
+  if (K == 1) return G.xfer32[u];
+  if (K == 2) return G.xfer32[2 * u + (int)link_bit(G, (uint32_t)du, (uint32_t)d)];
+  return G.xfer32[u * K + G.link_class[du * G.n_dev + d]];
+}
+
+// Orders a wave's LDS accesses (they complete in issue order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// #{k : S[k] < t} given that it is at most hi: the answer is hi itself for
+// about 85% of the copies and within three of it for nearly all others.
+__device__ __forceinline__ int gap_down(const uint32_t *S, int hi, uint32_t t) {
+  int g = hi;
+  for (int i = 0; i < 4; ++i) {
+    if (g == 0 || S[g - 1] < t) return g;
+    --g;
+  }
+  int lo = 0;  // the answer lies in [lo, g]
+  while (lo < g) {
+    const int mid = (lo + g) >> 1;
+    if (S[mid] < t)
+      lo = mid + 1;
+    else
+      g = mid;
+  }
+  return lo;
+}
+
+// #{k : S[k] < t} given that it is at least lo (S[m] is a sentinel above every t).
+__device__ __forceinline__ int gap_up(const uint32_t *S, int lo, int m, uint32_t t) {
+  int g = lo;
+  for (int i = 0; i < 4; ++i) {
+    if (S[g] >= t) return g;
+    ++g;
+  }
+  int hi = m;
+  while (g < hi) {
+    const int mid = (g + hi) >> 1;
+    if (S[mid] < t)
+      g = mid + 1;
+    else
+      hi = mid;
+  }
+  return g;
+}
+
+__device__ __forceinline__ void lds_add(uint32_t *p, uint32_t v) { atomicAdd(p, v); }
+__device__ __forceinline__ void lds_add(int64_t *p, int64_t v) {
+  atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
+}
+__device__ __forceinline__ void lds_max(uint32_t *p, uint32_t v) { atomicMax(p, v); }
+__device__ __forceinline__ void lds_max(int64_t *p, int64_t v) {
+  atomicMax(reinterpret_cast<long long *>(p), (long long)v);
+}
+__device__ __forceinline__ uint32_t shfl_up(uint32_t x, int o) { return (uint32_t)__shfl_up((int)x, o, kWave); }
+__device__ __forceinline__ int64_t shfl_up(int64_t x, int o) { return __shfl_up(x, o, kWave); }
+
+__device__ __forceinline__ uint64_t wave_max64(uint64_t x) {
+  for (int o = kWave / 2; o >= 1; o >>= 1) {
+    const uint64_t y = __shfl_xor(x, o, kWave);
+    x = y > x ? y : x;
+  }
+  return x;
+}
+
+// A wave's per-device arrays for ops with many successors: lowest consumer
+// rank (kInf32: none) and latest consumer (finish << 32 | rank).
+struct WideLds {
+  uint64_t *last;
+  uint32_t *low;
+};
+constexpr int kWide = 8;  // successors a lane walks alone (three nested walks of them); more are walked by the wave
+
+// The residency events of op v, passed to `ev` (an op per lane):
+//   ev.own_free(d, q, t, b)      the own output's free on v's device, flat gap q
+//   ev.copy(e, qa, ta, qf, tf, b)  a copy on device e: allocated in gap qa, freed in qf (from any lane)
+//   ev.copied()                  v has a copy
+// kCsr: any graph, successors from the CSR.  Otherwise at most two successors
+// per op, one device class and at most two link classes: the successors come
+// from succ2 and the fields of both are loaded unconditionally (absent ones
+// repeat v), with kShift the link class comes from the device ids.  kPorts:
+// arrivals of the transfers per predecessor edge in arow.
+template <bool kCsr, bool kShift, bool kPorts, class Ev>
+__device__ __forceinline__ void op_events(const GmgView &G, const uint8_t *prow, const uint32_t *frow,
+                                          const uint16_t *rk, const uint32_t *arow, int v, bool act, int sh,
+                                          const uint32_t *S, const int *gb, const WideLds &wl, Ev &&ev) {
+  const uint32_t d = prow[v], rv = rk[v], f = frow[v], b = G.bytes32[v] >> sh;
+  if (kCsr) {
+    const int x0 = G.succ_ptr[v], x1 = act ? G.succ_ptr[v + 1] : x0;
+    const int qd = gb[d];
+    if (x1 > x0 && x1 - x0 <= kWide) {  // (without consumers: kept for ever)
+      uint32_t L = f, A = 0, rl = rv;
+      bool remote = false;
+      for (int q = x0; q < x1; ++q) {
+        const int x = G.succ_idx[q];
+        const uint32_t dx = prow[x];
+        if (dx == d) {
+          if (frow[x] > L) {
+            L = frow[x];
+            rl = rk[x];
+          }
+        } else {
+          remote = true;
+          A = umax32(A, f + xfer_of(G, v, (int)d, (int)dx));
+        }
+      }
+      const bool arrive = A > L;
+      const int g = arrive ? gap_up(S + qd, (int)rv + 1, gb[d + 1] - qd - 1, A) : (int)rl + 1;
+      ev.own_free((int)d, qd + g, arrive ? A : L, b);
+      if (remote && b != 0) {
+        ev.copied();
+        for (int q = x0; q < x1; ++q) {
+          const int xf = G.succ_idx[q];
+          const uint32_t e = prow[xf];
+          if (e == d) continue;
+          bool first = true;
+          for (int q2 = x0; q2 < q; ++q2)
+            if (prow[G.succ_idx[q2]] == e) first = false;
+          if (!first) continue;
+          // allocated before the consumer on e that starts first (lowest
+          // rank), freed by the one that finishes last
+          int y = xf, ra = rk[xf];
+          for (int q2 = q + 1; q2 < x1; ++q2) {
+            const int x = G.succ_idx[q2];
+            if (prow[x] == e) {
+              if (frow[x] > frow[y]) y = x;
+              ra = min(ra, (int)rk[x]);
+            }
+          }
+          const int qe = gb[e];
+          ev.copy((int)e, qe + gap_down(S + qe, ra, f), f, qe + (int)rk[y] + 1, frow[y], b);
+        }
+      }
+    }
+    // ops with more successors: the wave walks them together, one op at a time
+    const int lane = threadIdx.x % kWave;
+    for (uint64_t wide = __ballot(x1 - x0 > kWide); wide; wide &= wide - 1) {
+      const int src = __ffsll((unsigned long long)wide) - 1;
+      const int u = __builtin_amdgcn_readlane(v, src);
+      const uint32_t du = (uint32_t)__builtin_amdgcn_readlane((int)d, src);
+      const uint32_t fu = (uint32_t)__builtin_amdgcn_readlane((int)f, src);
+      const uint32_t ru = (uint32_t)__builtin_amdgcn_readlane((int)rv, src);
+      const uint32_t bu = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
+      const int e1 = G.succ_ptr[u + 1];
+      uint64_t loc = (uint64_t)fu << 32 | ru;
+      uint32_t A = 0;
+      for (int q = G.succ_ptr[u] + lane; q < e1; q += kWave) {
+        const int x = G.succ_idx[q];
+        const uint32_t dx = prow[x];
+        const uint64_t key = (uint64_t)frow[x] << 32 | rk[x];
+        if (dx == du) {
+          loc = key > loc ? key : loc;
+        } else {
+          A = umax32(A, fu + xfer_of(G, u, (int)du, (int)dx));
+          atomicMin(&wl.low[dx], (uint32_t)key);
+          atomicMax(reinterpret_cast<unsigned long long *>(&wl.last[dx]), (unsigned long long)key);
+        }
+      }
+      loc = wave_max64(loc);
+      A = (uint32_t)wave_max64(A);
+      wave_lds_fence();
+      if (lane == src) {
+        const int qu = gb[du];
+        const uint32_t L = (uint32_t)(loc >> 32);
+        const bool arrive = A > L;
+        const int g = arrive ? gap_up(S + qu, (int)ru + 1, gb[du + 1] - qu - 1, A) : (int)(uint32_t)loc + 1;
+        ev.own_free((int)du, qu + g, arrive ? A : L, bu);
+        if (A != 0 && bu != 0) ev.copied();  // A is at least fu > 0 with a remote consumer
+      }
+      for (int e = lane; e < G.n_dev; e += kWave) {
+        const uint32_t ra = wl.low[e];
+        if (ra == kInf32) continue;
+        const uint64_t last = wl.last[e];
+        const int qe = gb[e];
+        if (bu != 0)
+          ev.copy(e, qe + gap_down(S + qe, (int)ra, fu), fu, qe + (int)(uint32_t)last + 1, (uint32_t)(last >> 32), bu);
+        wl.low[e] = kInf32;
+        wl.last[e] = 0;
+      }
+      wave_lds_fence();
+    }
+  } else {
+    const uint32_t s2 = G.succ2[v];
+    const uint32_t i0 = s2 & 0xFFFFu, i1 = s2 >> 16;
+    const bool has0 = act && i0 != 0xFFFFu, has1 = act && i1 != 0xFFFFu;
+    const int y0 = has0 ? (int)i0 : v, y1 = has1 ? (int)i1 : v;
+    const uint32_t dx0 = prow[y0], dx1 = prow[y1];
+    const uint32_t fx0 = frow[y0], fx1 = frow[y1];
+    const uint32_t rx0 = rk[y0], rx1 = rk[y1];
+    const bool loc0 = dx0 == d, loc1 = dx1 == d;
+    const bool rem0 = has0 && !loc0, rem1 = has1 && !loc1;
+    // own output: until the local consumer that finishes last (an absent
+    // successor repeats v itself, whose finish is f)
+    uint32_t L = f, rl = rv;
+    rl = loc0 && fx0 > L ? rx0 : rl;
+    L = loc0 && fx0 > L ? fx0 : L;
+    rl = loc1 && fx1 > L ? rx1 : rl;
+    L = loc1 && fx1 > L ? fx1 : L;
+    const int qd = gb[d];
+    int g = (int)rl + 1;
+    uint32_t F = L;
+    if (__any(rem0 || rem1)) {
+      auto cls = [&](uint32_t to) -> uint32_t {
+        if (!kShift) return link_bit(G, d, to);
+        const uint32_t s = (uint32_t)G.link_shift, same = (uint32_t)G.link_same;
+        return (d >> s) == (to >> s) ? same : 1u - same;
+      };
+      const int K = G.n_link;
+      const uint32_t xa = G.xfer32[v * K], xb = G.xfer32[v * K + K - 1];
+      const uint32_t X0 = cls(dx0) ? xb : xa, X1 = cls(dx1) ? xb : xa;
+      uint32_t T0 = f + X0, T1 = f + X1;  // arrivals
+      if (kPorts) {
+        const uint32_t pe = G.succ2_pe[v], e0 = pe & 0xFFFFu, e1 = pe >> 16;
+        T0 = arow[e0 == 0xFFFFu ? 0u : e0];  // (an absent one's is not used)
+        T1 = arow[e1 == 0xFFFFu ? 0u : e1];
+      }
+      // two successors on one remote device share the first one's transfer
+      uint32_t A = rem0 ? T0 : 0u;
+      A = rem1 ? umax32(A, T1) : A;
+      if (A > L) {
+        F = A;
+        g = gap_up(S + qd, (int)rv + 1, gb[d + 1] - qd - 1, A);
+      }
+      if (has0) ev.own_free((int)d, qd + g, F, b);
+      if ((rem0 || rem1) && b != 0) ev.copied();
+      const bool same = has1 && dx1 == dx0;
+      if (rem0 && b != 0) {
+        const bool late1 = same && fx1 > fx0;
+        const int ra = same ? (int)min(rx0, rx1) : (int)rx0;
+        const uint32_t st = kPorts ? T0 - X0 : f;  // the transfer's start
+        const int qe = gb[dx0];
+        ev.copy((int)dx0, qe + gap_down(S + qe, ra, st), st, qe + (int)(late1 ? rx1 : rx0) + 1, late1 ? fx1 : fx0, b);
+      }
+      if (rem1 && !same && b != 0) {
+        const uint32_t st = kPorts ? T1 - X1 : f;
+        const int qe = gb[dx1];
+        ev.copy((int)dx1, qe + gap_down(S + qe, (int)rx1, st), st, qe + (int)rx1 + 1, fx1, b);
+      }
+    } else if (has0) {
+      ev.own_free((int)d, qd + g, F, b);
+    }
+  }
+}
+
+// First walk: bytes allocated and freed per gap, and the gap table.
+template <class Acc>
+struct Accumulate {
+  Acc *A, *F;
+  uint32_t gap;  // this op's table entry
+  __device__ void own_free(int, int q, uint32_t, uint32_t b) {
+    lds_add(&F[q], (Acc)b);
+    gap = (gap & kHasCopy) | (uint32_t)q;
+  }
+  __device__ void copy(int, int qa, uint32_t, int qf, uint32_t, uint32_t b) {
+    lds_add(&A[qa], (Acc)b);
+    lds_add(&F[qf], (Acc)b);
+  }
+  __device__ void copied() { gap |= kHasCopy; }
+};
+
+// Second walk: the events of hard gaps, as a list per gap whose head replaces
+// the gap's sum in A.  Node: {time, bytes, flat gap | device << 16 |
+// allocation << 24, next}.
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;  // head of a hard gap without events yet
+constexpr uint32_t kEasy = 0xFFFFFFFEu;   // a gap that is not hard
+template <class Acc>
+struct Collect {
+  Acc *A;
+  uint4 *node;
+  uint32_t *count;
+  uint32_t cap;
+  __device__ void push(int d, int q, uint32_t t, uint32_t b, uint32_t alloc) {
+    uint32_t *head = reinterpret_cast<uint32_t *>(&A[q]);
+    if (*head == kEasy) return;
+    const uint32_t at = atomicAdd(count, 1u);
+    if (at >= cap) return;
+    const uint32_t next = atomicExch(head, at);
+    node[at] = make_uint4(t, b, (uint32_t)q | (uint32_t)d << 16 | alloc << 24, next);
+  }
+  __device__ void own_free(int d, int q, uint32_t t, uint32_t b) { push(d, q, t, b, 0); }
+  __device__ void copy(int e, int qa, uint32_t ta, int qf, uint32_t tf, uint32_t b) {
+    push(e, qa, ta, b, 1);
+    push(e, qf, tf, b, 0);
+  }
+  __device__ void copied() {}
+};
+
+template <bool kCsr, bool kGiven, bool kShift, bool kPorts, bool kNarrow>
+__global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t *__restrict__ P,
+                                                  const uint32_t *__restrict__ fin, int64_t fpitch,
+                                                  const uint32_t *__restrict__ arr, uint16_t *__restrict__ rank_all,
+                                                  uint16_t *__restrict__ gap_all, uint4 *__restrict__ node_all,
+                                                  int64_t node_cap, int lds_nodes, int64_t nb,
+                                                  uint32_t *__restrict__ ticket, int64_t *__restrict__ peak,
+                                                  uint8_t *__restrict__ violation) {
+  using Acc = typename std::conditional<kNarrow, uint32_t, int64_t>::type;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int D = G.n_dev, N = G.n_ops, C = G.n_class, n = N + D;
+  const int E = kPorts ? G.pred_ptr[N] : 0;
+  const int T = blockDim.x, W = T / kWave, tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+  const int n4 = (n + 3) & ~3;
+  Acc *A = reinterpret_cast<Acc *>(lds_raw);                 // [n4]
+  Acc *F = A + n4;                                           // [n4]
+  uint32_t *S = reinterpret_cast<uint32_t *>(F + n4);        // [n4]
+  uint4 *s_node = reinterpret_cast<uint4 *>(S + n4);         // [lds_nodes]
+  Acc *best = reinterpret_cast<Acc *>(s_node + lds_nodes);   // [D]
+  Acc *sb = best + D;                                        // [D] prefix sum before the device's first gap
+  Acc *wsum = sb + D;                                        // [16] sums of the waves' runs
+  int *gb = reinterpret_cast<int *>(wsum + 16);              // [D + 1] first flat entry of the device
+  uint32_t *misc = reinterpret_cast<uint32_t *>(gb + D + 1);  // [0] ticket, [1] hard gaps, [2] events, [3] violated
+  WideLds wl{nullptr, nullptr};
+  if (kCsr) {  // [W][D] each
+    unsigned char *p = reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(misc + 4) + 7) & ~uintptr_t(7));
+    wl.last = reinterpret_cast<uint64_t *>(p) + (size_t)w * D;
+    wl.low = reinterpret_cast<uint32_t *>(p + (size_t)W * D * 8) + (size_t)w * D;
+    for (int d = lane; d < D; d += kWave) {
+      wl.last[d] = 0;
+      wl.low[d] = kInf32;
+    }
+  }
+  // while the ranks are made: op counts [W][D] on A and F, lane masks [W][D] past them
+  uint64_t *mask = reinterpret_cast<uint64_t *>(A) + (size_t)w * D;
+  uint32_t *hist = reinterpret_cast<uint32_t *>(reinterpret_cast<uint64_t *>(A) + (size_t)W * D);
+  uint32_t *whist = hist + (size_t)w * D;
+  const int sh = kNarrow ? G.peak_shift : 0;
+  uint16_t *gap_of = gap_all + (int64_t)blockIdx.x * N;
+  const int seg = ((N + T - 1) / T) * kWave;  // ops of a wave while ranks are made
+
+  for (;;) {
+    __syncthreads();  // the last candidate's LDS state has been read
+    if (tid == 0) {
+      misc[0] = atomicAdd(ticket, 1u);
+      misc[1] = misc[2] = misc[3] = 0;
+    }
+    for (int d = lane; d < D; d += kWave) {
+      whist[d] = 0;
+      mask[d] = 0;
+    }
+    __syncthreads();
+    const int64_t c = misc[0];
+    if (c >= nb) return;
+    if (violation[c] & SS_VIOLATION_INVALID) {
+      if (peak)
+        for (int d = tid; d < D; d += T) peak[c * D + d] = 0;
+      continue;
+    }
+    const uint8_t *prow = P + c * N;
+    const uint32_t *frow = fin + c * fpitch;
+    const uint32_t *arow = kPorts ? arr + c * E : nullptr;
+    uint16_t *rk = rank_all + (kGiven ? c : (int64_t)blockIdx.x) * N;
+
+    // ops per device, and with index ranks per wave's segment of the ops
+    const int v_lo = min(w * seg, N), v_hi = min(v_lo + seg, N);
+    for (int v = v_lo + lane; v < v_hi; v += kWave) atomicAdd(&whist[prow[v]], 1u);
+    __syncthreads();
+    for (int d = tid; d < D; d += T) {
+      uint32_t s = 0;
+      for (int k = 0; k < W; ++k) {
+        const uint32_t t = hist[(size_t)k * D + d];
+        hist[(size_t)k * D + d] = s;
+        s += t;
+      }
+      gb[d] = (int)s + 1;
+    }
+    __syncthreads();
+    if (w == 0) {  // counts to first flat entries
+      int carry = 0;
+      for (int d0 = 0; d0 < D; d0 += kWave) {
+        const int d = d0 + lane, x = d < D ? gb[d] : 0;
+        int s = x;
+        for (int o = 1; o < kWave; o <<= 1) {
+          const int y = __shfl_up(s, o, kWave);
+          if (lane >= o) s += y;
+        }
+        if (d < D) {
+          gb[d] = carry + s - x;
+          S[carry + s - 1] = kInf32;  // sentinel past the device's last start
+        }
+        carry += __shfl(s, kWave - 1, kWave);
+      }
+      if (lane == 0) gb[D] = carry;
+    }
+    __syncthreads();
+    // every op's rank on its device and its start
+    for (int v0 = v_lo; v0 < v_hi; v0 += kWave) {
+      const int v = v0 + lane;
+      const bool act = v < v_hi;
+      const int vc = act ? v : v_hi - 1;
+      const uint32_t d = prow[vc];
+      uint32_t r;
+      if (kGiven) {
+        r = rk[vc];
+      } else {
+        // the lanes of this chunk on d, from a lane mask per device
+        if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
+        wave_lds_fence();
+        const uint64_t peers = mask[d];
+        const uint32_t before = whist[d];
+        wave_lds_fence();
+        r = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+        if (act) {
+          mask[d] = 0;
+          atomicAdd(&whist[d], 1u);
+          rk[v] = (uint16_t)r;
+        }
+      }
+      const uint32_t dur = !kCsr || C == 1 ? G.dur32[vc] : G.dur32[(int64_t)vc * C + G.dev_class[d]];
+      if (act) S[gb[d] + r] = frow[vc] - dur;
+    }
+    __syncthreads();
+    for (int q = tid; q < n; q += T) {
+      A[q] = 0;
+      F[q] = 0;
+    }
+    __syncthreads();
+
+    // bytes allocated and freed per gap
+    for (int v0 = w * kWave; v0 < N; v0 += T) {
+      const int v = v0 + lane, vc = min(v, N - 1);
+      const bool act = v < N;
+      Accumulate<Acc> ev{A, F, kNoEvent & ~kHasCopy};
+      op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, sh, S, gb, wl, ev);
+      if (act) {
+        lds_add(&A[gb[prow[v]] + rk[v] + 1], (Acc)(G.bytes32[v] >> sh));  // the own output opens gap rank + 1
+        gap_of[v] = (uint16_t)ev.gap;
+      }
+    }
+    __syncthreads();
+
+    // prefix sums over the flat entries (modulo 2^32 with 32-bit sums): each
+    // thread a run, of odd length so that the lanes' accesses spread over the banks
+    {
+      const int per = ((n + T - 1) / T) | 1, lo = min(tid * per, n), hi = min(lo + per, n);
+      Acc s = 0;
+      for (int q = lo; q < hi; ++q) s += A[q] - F[q];
+      Acc incl = s;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const Acc y = shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      if (lane == kWave - 1) wsum[w] = incl;
+      __syncthreads();
+      Acc run = incl - s;
+      for (int k = 0; k < w; ++k) run += wsum[k];
+      for (int q = lo; q < hi; ++q) {
+        run += A[q] - F[q];
+        A[q] = run;
+      }
+    }
+    __syncthreads();
+    for (int d = tid; d < D; d += T) {
+      sb[d] = d > 0 ? A[gb[d] - 1] : (Acc)0;
+      best[d] = 0;
+    }
+    __syncthreads();
+    // the exact values: live bytes at every own start
+    for (int v = tid; v < N; v += T) {
+      const uint32_t d = prow[v];
+      lds_max(&best[d], (Acc)(A[gb[d] + rk[v]] - sb[d] + (Acc)(G.bytes32[v] >> sh)));
+    }
+    __syncthreads();
+    // hard gaps: their bound replaces their frees, an empty list their sum
+    for (int d = w; d < D; d += W) {
+      const Acc base = sb[d], top = best[d];
+      const int q1 = gb[d + 1];
+      bool any = false;
+      for (int q = gb[d] + lane; q < q1; q += kWave) {
+        const Acc U = A[q] - base + F[q];
+        const bool hard = U > top;
+        F[q] = U;
+        *reinterpret_cast<uint32_t *>(&A[q]) = hard ? kEmpty : kEasy;
+        any |= hard;
+      }
+      if (any) misc[1] = 1;
+    }
+    __syncthreads();
+    if (misc[1]) {
+      // the events of the hard gaps: an op whose own free falls into one, or
+      // that has copies
+      auto collect = [&](uint4 *node, uint32_t cap) {
+        for (int v0 = w * kWave; v0 < N; v0 += T) {
+          const int v = v0 + lane, vc = min(v, N - 1);
+          const uint32_t e = gap_of[vc], q = e & ~kHasCopy;
+          const bool own = q != (kNoEvent & ~kHasCopy) && *reinterpret_cast<const uint32_t *>(&A[q]) != kEasy;
+          const bool act = v < N && (own || (e & kHasCopy));
+          if (!__any(act)) continue;
+          op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, sh, S, gb, wl,
+                                          Collect<Acc>{A, node, &misc[2], cap});
+        }
+        __syncthreads();
+      };
+      // live bytes at each collected allocation: the gap's bound less the
+      // copies allocated later and the frees at or before it
+      auto sweep = [&](const uint4 *node, uint32_t cnt) {
+        for (uint32_t i = tid; i < cnt; i += T) {
+          const uint4 me = node[i];
+          if (!(me.z >> 24)) continue;
+          const uint32_t q = me.z & 0xFFFFu;
+          Acc live = F[q];
+          for (uint32_t z = *reinterpret_cast<const uint32_t *>(&A[q]); z != kEmpty;) {
+            const uint4 o = node[z];
+            if ((o.z >> 24) ? o.x > me.x : o.x <= me.x) live -= (Acc)o.y;
+            z = o.w;
+          }
+          lds_max(&best[(me.z >> 16) & 0xFFu], live);
+        }
+      };
+      collect(s_node, (uint32_t)lds_nodes);
+      const uint32_t cnt = misc[2];
+      if (cnt <= (uint32_t)lds_nodes) {
+        sweep(s_node, cnt);
+      } else {  // more events than the LDS holds: once more, into the block's global list
+        __syncthreads();
+        if (tid == 0) misc[2] = 0;
+        for (int q = tid; q < n; q += T) {
+          uint32_t *head = reinterpret_cast<uint32_t *>(&A[q]);
+          if (*head != kEasy) *head = kEmpty;
+        }
+        __syncthreads();
+        uint4 *node = node_all + (int64_t)blockIdx.x * node_cap;
+        collect(node, (uint32_t)node_cap);
+        sweep(node, misc[2]);
+      }
+      __syncthreads();
+    }
+    bool over = false;
+    for (int d = tid; d < D; d += T) {
+      const int64_t pk = kNarrow ? (int64_t)best[d] << sh : (int64_t)best[d];
+      if (peak) peak[c * D + d] = pk;
+      over |= pk > G.cap[d];
+    }
+    if (over) misc[3] = 1;
+    __syncthreads();
+    if (tid == 0) violation[c] = misc[3] ? SS_VIOLATION_MEMORY : 0;
+  }
+}
+
+template <bool kNarrow>
+const void *peaks_fn(bool csr, bool given, bool shift, bool ports) {
+#define SS_PEAKS(c, g, s, p) reinterpret_cast<const void *>(&lds_peaks<c, g, s, p, kNarrow>)
+  if (csr) return given ? SS_PEAKS(true, true, false, false) : SS_PEAKS(true, false, false, false);
+  if (ports) return shift ? SS_PEAKS(false, false, true, true) : SS_PEAKS(false, false, false, true);
+  if (given) return shift ? SS_PEAKS(false, true, true, false) : SS_PEAKS(false, true, false, false);
+  return shift ? SS_PEAKS(false, false, true, false) : SS_PEAKS(false, false, false, false);
+#undef SS_PEAKS
+}
+
+int hip_fail(hipError_t err, const char *what) {
+  return ss_set_error(err == hipErrorOutOfMemory ? SS_ERR_OOM : SS_ERR_DEVICE,
+                      std::string(what) + ": " + hipGetErrorString(err));
+}
+
+}  // namespace
+
+PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_block, int64_t lds_cu) {
+  PeaksShape s;
+  const int64_t N = g->n_ops, D = g->n_dev, n4 = (N + D + 3) / 4 * 4;
+  const int64_t acc = g->view.peak_narrow ? 4 : 8;
+  s.csr = !(g->n_class == 1 && g->n_link <= 2 && g->max_outdeg <= 2);
+  if (N == 0 || N + D >= kMaxFlat || (ports && (s.csr || !g->view.succ2_pe))) return s;
+  // about one event per ten ops falls into hard gaps when every op is placed at random
+  s.lds_nodes = (int)std::max<int64_t>(64, N / 8);
+  int64_t lds = n4 * (2 * acc + 4) + s.lds_nodes * 16 + (2 * D + 16) * acc + (D + 1) * 4 + 32;
+  const int64_t wave_lds = s.csr ? 12 * D : 0;  // the device arrays of ops with many successors
+  if (lds + wave_lds > lds_block) return s;
+  // about sixteen waves per CU, none with less than two chunks of 64 ops; the
+  // ranks' counts and masks (12 bytes per wave and device) lie on A and F
+  const int64_t fit = std::max<int64_t>(1, lds_cu / lds);
+  int64_t waves = std::min<int64_t>(16, std::max<int64_t>(1, 16 / fit));
+  waves = std::min(waves, (N + 2 * kWave - 1) / (2 * kWave));
+  waves = std::max<int64_t>(1, std::min(waves, 2 * acc * n4 / (12 * D)));
+  if (s.csr) waves = std::min(waves, (lds_block - lds) / wave_lds);
+  lds += waves * wave_lds;
+  s.lds = (size_t)lds;
+  s.threads = (int)waves * kWave;
+  s.blocks = (int64_t)cus * std::max<int64_t>(1, std::min<int64_t>(lds_cu / lds, 32 / waves));
+  s.node_cap = N + 2 * g->n_edges + 1;
+  s.ok = 12 * D * waves <= 2 * acc * n4;
+  return s;
+}
+
+size_t ss_peaks_slot_bytes(const ss_gmg *g, const PeaksShape &s, bool given_ranks) {
+  auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const size_t N = (size_t)g->n_ops;
+  return align(N * 2) * (given_ranks ? 1 : 2) + align((size_t)s.node_cap * sizeof(uint4));
+}
+
+int ss_launch_peaks(const ss_gmg *g, const PeaksShape &s, const uint8_t *P, const uint32_t *fin, int64_t fpitch,
+                    const uint32_t *arr, uint16_t *given, void *slots, int64_t n_slots, int64_t nb, uint32_t *ticket,
+                    int64_t *peak, uint8_t *violation, hipStream_t stream) {
+  const GmgView &G = g->view;
+  auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const int64_t N = g->n_ops, slots_n = std::min(n_slots, nb);
+  auto *p = static_cast<unsigned char *>(slots);
+  auto *node = reinterpret_cast<uint4 *>(p);
+  p += align((size_t)s.node_cap * sizeof(uint4)) * (size_t)n_slots;
+  auto *gap = reinterpret_cast<uint16_t *>(p);
+  p += align((size_t)N * 2) * (size_t)n_slots;
+  uint16_t *rank = given ? given : reinterpret_cast<uint16_t *>(p);
+  const bool shift = G.link_shift >= 0;
+  const void *fn = G.peak_narrow ? peaks_fn<true>(s.csr, given, shift, arr) : peaks_fn<false>(s.csr, given, shift, arr);
+  int64_t node_cap = s.node_cap;
+  int lds_nodes = s.lds_nodes;
+  void *args[] = {const_cast<GmgView *>(&G), &P, &fin, &fpitch, &arr, &rank, &gap, &node, &node_cap, &lds_nodes, &nb,
+                  &ticket, &peak, &violation};
+  hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
+  if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
+  SsTimingRec *t = ss_timing_start(SS_KERNEL_MEMORY, stream);
+  err = hipLaunchKernel(fn, dim3((unsigned)slots_n), dim3((unsigned)s.threads), args, s.lds, stream);
+  ss_timing_stop(t, stream);
+  if (err == hipSuccess) err = hipGetLastError();
+  return err == hipSuccess ? SS_OK : hip_fail(err, "lds_peaks launch");
+}

@@ -14,9 +14,11 @@
 //                 software pipeline).  Finish times are written op-major
 //                 (the schedule's own reads) and, eight ops at a time from
 //                 registers, into each candidate's row for the memory passes.
-//   transpose     finish times to candidate rows instead when N % 4 != 0
-//                 (rows not 16-byte aligned)
-// then per sub-chunk of candidates:
+// then lds_peaks (peaks.hip), one workgroup per candidate, when the graph's gap
+// table fits a CU's LDS (up to about 11,600 ops): 131,072 candidates of the
+// 10,000-op workload take 18.7 ms in it against 38.2 ms in the two passes
+// below, 65,536 of a 322-op graph 0.91 against 2.8 ms.  Larger graphs take, per
+// sub-chunk of candidates:
 //   fast_intervals one wave per candidate, lanes = consecutive ops (coalesced
 //                 row reads).  Pass A ranks every op among the ops of its
 //                 device (lanes sharing a device from a 64-bit lane mask per
@@ -54,6 +56,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "peaks.h"
 #include "ss_internal.h"
 
 namespace {
@@ -103,58 +106,6 @@ __global__ __launch_bounds__(256) void transpose_tiles(const T *__restrict__ in,
   for (int i = ty; i < 64; i += 4) {
     const int64_t c = c0 + i, r = r0 + tx;
     if (c < cols && r < rows) out[c * rows + r] = tile[tx][i];
-  }
-}
-
-// 32-bit matrices whose row and column counts and pitch are multiples of 4
-// (16-byte aligned buffers): a workgroup takes a strip of 64 columns and walks
-// kStripTiles tiles of 64 rows down it, each tile read and written as 16-byte
-// vectors through LDS (a wave moves four 256-byte row segments per access).
-// The next tile's loads are in flight while the current one is written out,
-// and the output segments of consecutive tiles, which share the lines where a
-// row's segments meet, are written by the same workgroup.
-constexpr int kStripTiles = 16;
-__global__ __launch_bounds__(256) void transpose_u32_strips(const uint32_t *__restrict__ in, int64_t rows,
-                                                            int64_t cols, int64_t pitch, uint32_t *__restrict__ out) {
-  __shared__ uint32_t tile[64][65];
-  const int64_t c0 = (int64_t)blockIdx.x * 64, rb = (int64_t)blockIdx.y * (64 * kStripTiles);
-  const int t = threadIdx.x, sub = t & 15, grp = t >> 4;
-  // read side: rows grp + 16j of the tile, columns 4 sub .. 4 sub + 3;
-  // write side: columns grp + 16j of the tile (output rows), rows 4 sub .. 4 sub + 3
-  const bool col_in = c0 + 4 * sub < cols;
-  auto load = [&](int64_t r0, uint4 (&v)[4]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t r = r0 + grp + 16 * j;
-      v[j] = (col_in && r < rows) ? *reinterpret_cast<const uint4 *>(in + r * pitch + c0 + 4 * sub)
-                                  : uint4{0u, 0u, 0u, 0u};
-    }
-  };
-  const int64_t left = (rows - rb + 63) / 64;  // >= 1: the grid covers the rows
-  const int ntile = left < kStripTiles ? (int)left : kStripTiles;
-  uint4 v[4];
-  load(rb, v);
-  for (int k = 0; k < ntile; ++k) {
-    const int64_t r0 = rb + (int64_t)k * 64;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t *row = tile[grp + 16 * j] + 4 * sub;
-      row[0] = v[j].x;
-      row[1] = v[j].y;
-      row[2] = v[j].z;
-      row[3] = v[j].w;
-    }
-    __syncthreads();
-    if (k + 1 < ntile) load(r0 + 64, v);
-    const int64_t r = r0 + 4 * sub;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int oc = grp + 16 * j;
-      if (c0 + oc < cols && r < rows)
-        *reinterpret_cast<uint4 *>(out + (c0 + oc) * rows + r) =
-            uint4{tile[4 * sub][oc], tile[4 * sub + 1][oc], tile[4 * sub + 2][oc], tile[4 * sub + 3][oc]};
-    }
-    __syncthreads();
   }
 }
 
@@ -238,6 +189,9 @@ constexpr int kPipePre = 2;  // predecessors handled by the pipeline; more go th
 constexpr int kRowOps = 8;   // finish times a lane gathers in registers before it writes them to its own row
 constexpr int kWindowStep = 32;  // ops per advance of the op-field window
 
+// Pitch of the candidates' finish rows: whole groups of the schedule's row stores.
+int64_t fin_pitch(int64_t N) { return (N + kRowOps - 1) & ~int64_t(kRowOps - 1); }
+
 struct SchedPipe {
   uint32_t dq[4];                // device of the target op (raw byte)
   uint32_t pf[4][kPipePre];      // predecessor finish times (raw loads)
@@ -257,10 +211,12 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
                                                        int64_t nb,
                                                        uint32_t *__restrict__ finT, int64_t *__restrict__ makespan,
                                                        int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
-                                                       uint8_t *__restrict__ violation, uint32_t *__restrict__ finR) {
+                                                       uint8_t *__restrict__ violation, uint32_t *__restrict__ finR,
+                                                       int64_t rpitch, uint32_t *__restrict__ ticket) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = kOneClass ? 1 : G.n_class, K = G.n_link;
   const int lane = threadIdx.x;
+  if (blockIdx.x == 0 && lane == 0) *ticket = 0;  // the memory pass takes its candidates from it
   uint32_t *clk = reinterpret_cast<uint32_t *>(lds_raw);                  // [D][64]
   uint32_t *comp = clk + (size_t)D * kWave;                               // [R][64]
   int32_t *sbase = reinterpret_cast<int32_t *>(comp + (size_t)R * kWave);  // [D+1] slice ranges of the devices
@@ -314,7 +270,7 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
   const uint64_t nbu = (uint64_t)(uint32_t)nb;  // a chunk holds fewer than 2^32 candidates
   const uint8_t *const PTc = PT + c;
   uint32_t *const finTc = finT + c;
-  uint32_t *const finRc = finR ? finR + (uint64_t)(uint32_t)c * (uint32_t)N : nullptr;
+  uint32_t *const finRc = finR + (uint64_t)(uint32_t)c * (uint32_t)rpitch;
   const uint64_t ppu = (uint64_t)ppitch;  // placement rows: the caller's op-major pitch, or the chunk's
   auto row = [&](int t) -> uint64_t { return (uint64_t)(uint32_t)t * nbu; };
   auto prow = [&](int t) -> uint64_t { return (uint64_t)(uint32_t)t * ppu; };
@@ -329,10 +285,16 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
     for (int i = 0; i < kPipePre; ++i) S.pf[q][i] = S.pd[q][i] = S.lc[q][i] = 0;
   }
 
-  // with finR: the lane's finish times of ops 8k .. 8k+7 (op T in slot T mod 8)
+  // the lane's finish times of ops 8k .. 8k+7 (op T in slot T mod 8)
   uint32_t rb[kRowOps];
 #pragma unroll
   for (int k = 0; k < kRowOps; ++k) rb[k] = 0;
+  // rows are padded to whole groups of kRowOps
+  auto store_row = [&](int t) {
+    uint4 *dst = reinterpret_cast<uint4 *>(finRc + t);
+    dst[0] = make_uint4(rb[0], rb[1], rb[2], rb[3]);
+    dst[1] = make_uint4(rb[4], rb[5], rb[6], rb[7]);
+  };
   // Results of the last three ops: h1 = op T (after its step), h2 and h3 before it.
   uint32_t h1f = 0, h1d = 0, h2f = 0, h2d = 0, h3f = 0, h3d = 0;
 
@@ -475,17 +437,13 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
     const uint32_t f = s + w;
     clk[slot] = f;
     finTc[row(T)] = f;
-    if (finRc) {  // the candidate's own row, kRowOps finish times at a time
+    {  // the candidate's own row, kRowOps finish times at a time
       // T mod 4 is q0 (steps come four to a block that starts at a multiple
       // of 4), so the slot is q0 or q0 + 4 by the wave-uniform bit T & 4
       const bool hi = (T & 4) != 0;
       rb[q0] = hi ? rb[q0] : f;
       rb[q0 + 4] = hi ? f : rb[q0 + 4];
-      if (q0 == 3 && hi) {
-        uint4 *dst = reinterpret_cast<uint4 *>(finRc + (T - (kRowOps - 1)));
-        dst[0] = make_uint4(rb[0], rb[1], rb[2], rb[3]);
-        dst[1] = make_uint4(rb[4], rb[5], rb[6], rb[7]);
-      }
+      if (q0 == 3 && hi) store_row(T - (kRowOps - 1));
     }
     atomicMax(&comp[r * kWave + lane], f);
     ms = umax32(ms, f);
@@ -530,11 +488,7 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
       if (T + 3 < N) step(std::integral_constant<int, 3>(), T + 3);
     }
   }
-  if (finRc) {  // the last N mod kRowOps finish times
-#pragma unroll
-    for (int k = 0; k < kRowOps; ++k)
-      if (k < (N & (kRowOps - 1))) finRc[(N & ~(kRowOps - 1)) + k] = rb[k];
-  }
+  if (N & (kRowOps - 1)) store_row(N & ~(kRowOps - 1));  // the last N mod kRowOps, and padding
   if (!live) return;
   if (invalid) {
     makespan[c] = INT64_MAX;
@@ -1126,7 +1080,7 @@ constexpr int kCpShift = 1, kCpRecs = 1 << kCpShift;
 // its transfer's start (arrival minus estimate).
 template <bool kFast, bool kGivenRanks, bool kShiftLinks, bool kPorts, bool kStageCp>
 __global__ __launch_bounds__(kWave) void fast_intervals(const GmgView G, const uint8_t *__restrict__ P,
-                                                        const uint32_t *__restrict__ fin, int64_t j0,
+                                                        const uint32_t *__restrict__ fin, int64_t fpitch, int64_t j0,
                                                         Rec *__restrict__ own_all, Rec *__restrict__ cp_all,
                                                         int32_t *__restrict__ meta, uint16_t *__restrict__ rank_all,
                                                         const uint8_t *__restrict__ violation,
@@ -1159,7 +1113,7 @@ __global__ __launch_bounds__(kWave) void fast_intervals(const GmgView G, const u
   const int64_t j = blockIdx.x, c = j0 + j;
   if (violation[c] & SS_VIOLATION_INVALID) return;
   const uint8_t *prow = P + c * N;
-  const uint32_t *frow = fin + c * N;
+  const uint32_t *frow = fin + c * fpitch;
   const uint32_t *arow = kPorts ? arr + c * E : nullptr;
   uint16_t *rk = rank_all + j * N;
   Rec *own = own_all + j * own_stride(N);
@@ -2015,7 +1969,7 @@ size_t intervals_lds(int D, bool stage, bool stage_cp) {
 // arr (rows of arrivals per predecessor edge, transfers arbitrated over
 // ports) is null in the latency model; with it, the branch-free writer with
 // index ranks is required.
-int memory_passes(const ss_gmg *g, MemPass &M, const uint8_t *Pc, const uint32_t *fin, int64_t nb,
+int memory_passes(const ss_gmg *g, MemPass &M, const uint8_t *Pc, const uint32_t *fin, int64_t fpitch, int64_t nb,
                   bool given_ranks, int64_t *peak, uint8_t *violation, hipStream_t stream,
                   const uint32_t *arr = nullptr) {
   const GmgView &G = g->view;
@@ -2051,7 +2005,7 @@ int memory_passes(const ss_gmg *g, MemPass &M, const uint8_t *Pc, const uint32_t
     Rec *own = M.own[set], *cp = M.cp[set];
     int32_t *meta = M.meta[set];
     void *args[] = {const_cast<GmgView *>(&G), const_cast<uint8_t **>(&Pc), const_cast<uint32_t **>(&fin),
-                    &j0, &own, &cp, &meta, &rank, &vi, const_cast<uint32_t **>(&arr)};
+                    &fpitch, &j0, &own, &cp, &meta, &rank, &vi, const_cast<uint32_t **>(&arr)};
     // the branch-free writer with index ranks stages its stores
     const size_t lds = intervals_lds((int)g->n_dev, M.iv_fast && !given_ranks, M.iv_fast && !given_ranks && scp);
     err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2097,7 +2051,7 @@ size_t ss_fast_schedule_lds(const ss_gmg *g) {
 struct FastPlan {
   int64_t chunk = 0, sub = 0, nslots = 0, n_ticket = 0;
   int sets = kRecSets;
-  size_t sz_pt = 0, sz_fin = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
+  size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
          total = 0;
 };
 
@@ -2119,9 +2073,14 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   int lds_cu = 0;
   err = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device);
   if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
-  // the schedule writes the candidates' finish-time rows itself (no
-  // transpose) when each row is 16-byte aligned
-  const bool sched_rows = N > 0 && N % 4 == 0;
+  int lds_block = 0;
+  err = hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device);
+  if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
+  // the memory pass: one workgroup per candidate when its gap table fits the
+  // LDS, else interval records and peaks in sub-chunks
+  const PeaksShape pk = ss_peaks_shape(g, false, cus, lds_block, lds_cu);
+  const size_t pk_slot = pk.ok ? ss_peaks_slot_bytes(g, pk, false) : 0;
+  const int64_t pitch = fin_pitch(N);  // of the finish rows
   const size_t sched_lds = ss_fast_schedule_lds(g);
   // kernel variant: link classes from device groups, a bit table or (more
   // than two classes) xfer32; in-degrees above the pipelined count go
@@ -2137,7 +2096,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   // chunk: placements (op-major for the schedule from row-major input, rows
   // for the memory passes from op-major input), op-major and row-major finish
   // times
-  const int64_t per_cand = N * (1 + 4 + 4);
+  const int64_t per_cand = N * (1 + 4) + pitch * 4;
   // A schedule launch is best a whole number of rounds of the waves the chip
   // holds at once (every wave runs about as long as any other).
   const int64_t round =
@@ -2157,9 +2116,19 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     int64_t sub = std::min<int64_t>(std::max<int64_t>(1, sub_cap), chunk);
     const int64_t n = std::max<int64_t>((chunk + sub - 1) / sub, chunk >= 8192 && !W.single ? 2 : 1);
     q.sub = sub = (chunk + n - 1) / n;
-    q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
     q.sz_pt = align((size_t)chunk * N + 1);
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
+    q.sz_row = align((size_t)chunk * pitch * 4 + 4);
+    if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
+      q.sub = chunk;
+      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
+      q.sz_slots = pk_slot * (size_t)q.nslots;
+      q.n_ticket = 1;
+      q.sz_tk = 256;
+      q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_slots + q.sz_tk;
+      return q;
+    }
+    q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
     q.sz_own = align((size_t)sub * own_stride(N) * sizeof(Rec));
     q.sz_cp = align((size_t)sub * cp_stride(E) * sizeof(Rec));
     q.sz_meta = align((size_t)sub * 3 * (D + 1) * 4);
@@ -2167,8 +2136,8 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_wk = align((size_t)q.nslots * 2 * (slot_cap + 2) * 4);
     q.sz_wb = align((size_t)q.nslots * slot_cap * 8);
     q.n_ticket = (B + chunk - 1) / chunk * ((chunk + sub - 1) / sub);
-    q.sz_tk = align((size_t)q.n_ticket * 4);
-    q.total = q.sz_pt + 2 * q.sz_fin + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
+    q.sz_tk = align(((size_t)q.n_ticket + 1) * 4);
+    q.total = q.sz_pt + q.sz_fin + q.sz_row + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
               q.sz_rank + q.sz_wk + q.sz_wb + q.sz_tk;
     return q;
   };
@@ -2203,9 +2172,11 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       chunk = chunk > round ? chunk - round : std::max<int64_t>(kWave, chunk / 2 / kWave * kWave);
     }
   };
-  // the pool path's budget: up to the preferred layout, within seven eighths
-  // of the memory the call can get now
-  auto pool_budget = [&] { return ss_scratch_budget(g->device, g->pool, (int64_t)pref.total, 7); };
+  // the pool path's budget: up to the preferred layout, within the memory the
+  // call can get now: seven eighths of it with interval records, whose
+  // preferred layout is most of the device; five with the far smaller one
+  // without, since a new block takes a quarter of headroom and is rounded up
+  auto pool_budget = [&] { return ss_scratch_budget(g->device, g->pool, (int64_t)pref.total, pk.ok ? 5 : 7); };
   if (W.query) {
     W.need_min = pmin.total;
     W.need_pref = pref.total;
@@ -2246,7 +2217,8 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   };
   auto *PT = reinterpret_cast<uint8_t *>(take(pl.sz_pt));  // op-major copy, or candidate rows of op-major input
   auto *finT = reinterpret_cast<uint32_t *>(take(pl.sz_fin));
-  auto *fin = reinterpret_cast<uint32_t *>(take(pl.sz_fin));
+  auto *fin = reinterpret_cast<uint32_t *>(take(pl.sz_row));
+  void *const slots = take(pl.sz_slots);
   MemPass M{};
   for (int k = 0; k < pl.sets; ++k) {
     M.own[k] = reinterpret_cast<Rec *>(take(pl.sz_own));
@@ -2262,12 +2234,12 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   M.nslots = pl.nslots;
   M.slot_cap = slot_cap;
   M.iv_fast = iv_fast;
-  M.single = W.single;
+  M.single = W.single || pk.ok;
   M.sets = pl.sets;
   M.aux = g->aux;
 
   int rc = mem_pass_events(M);
-  if (rc == SS_OK) {
+  if (rc == SS_OK && !pk.ok) {
     hipLaunchKernelGGL(fill_zero_u32, dim3((unsigned)std::min<int64_t>((pl.n_ticket + 255) / 256, 1024)), dim3(256),
                        0, stream, M.ticket, pl.n_ticket);
     const hipError_t fe = hipGetLastError();
@@ -2316,30 +2288,21 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       int64_t *ms_out = makespan + b0, *sf_out = sumfin ? sumfin + b0 : nullptr,
               *sl_out = slack ? slack + b0 * R : nullptr;
       uint8_t *vi_out = violation + b0;
-      uint32_t *rows_out = sched_rows ? fin : nullptr;
+      uint32_t *rows_out = fin, *tk = pk.ok ? M.ticket : M.ticket + M.n_ticket;  // the last one is spare
+      int64_t rpitch = pitch;
       void *args[] = {const_cast<GmgView *>(&G), &sched_P, &ppitch, const_cast<int64_t *>(&nb), &finT, &ms_out,
-                      &sf_out, &sl_out, &vi_out, &rows_out};
+                      &sf_out, &sl_out, &vi_out, &rows_out, &rpitch, &tk};
       const hipError_t le = hipLaunchKernel(sched_fn, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave), args,
                                             sched_lds, stream);
       if (le != hipSuccess && rc == SS_OK) rc = hip_fail(le, "fast_schedule launch");
     }
     ss_timing_stop(ts, stream);
     if (!check("fast_schedule launch")) break;
-    if (N > 0 && !sched_rows) {  // op-major -> candidates' rows for the memory passes
-      SsTimingRec *tt = ss_timing_start(SS_KERNEL_TRANSPOSE, stream);
-      if (N % 4 == 0 && nb % 4 == 0) {  // scratch buffers are 256-byte aligned
-        const dim3 tg((unsigned)((nb + 63) / 64), (unsigned)((N + 64 * kStripTiles - 1) / (64 * kStripTiles)));
-        hipLaunchKernelGGL(transpose_u32_strips, tg, dim3(256), 0, stream, static_cast<const uint32_t *>(finT),
-                           (int64_t)N, nb, nb, fin);
-      } else {
-        const dim3 tg((unsigned)((nb + 63) / 64), (unsigned)((N + 63) / 64));
-        hipLaunchKernelGGL(transpose_tiles<uint32_t>, tg, dim3(256), 0, stream, static_cast<const uint32_t *>(finT),
-                           (int64_t)N, nb, nb, fin);
-      }
-      ss_timing_stop(tt, stream);
-      if (!check("transpose launch")) break;
-    }
-    rc = memory_passes(g, M, Pc, fin, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    if (pk.ok)
+      rc = ss_launch_peaks(g, pk, Pc, fin, pitch, nullptr, nullptr, slots, pl.nslots, nb, M.ticket,
+                           peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    else
+      rc = memory_passes(g, M, Pc, fin, pitch, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream);
   }
   const int jrc = mem_pass_join(M, stream);
   if (rc == SS_OK) rc = jrc;
@@ -2362,6 +2325,13 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   hipError_t err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device);
   if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
   const bool iv_fast = g->n_class == 1 && g->n_link <= 2 && g->max_outdeg <= 2;
+  int lds_blk = 0, lds_cu = 0;
+  err = hipDeviceGetAttribute(&lds_blk, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device);
+  if (err == hipSuccess)
+    err = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device);
+  if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
+  const PeaksShape pk = ss_peaks_shape(g, false, cus, lds_blk, lds_cu);
+  const size_t pk_slot = pk.ok ? ss_peaks_slot_bytes(g, pk, true) : 0;
   // chunk: finish times, ranks, missing-predecessor counts and the spill list
   // of each candidate (candidate rows), and with op-major input the chunk's
   // placement rows
@@ -2376,13 +2346,10 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   const char *rmode = std::getenv("SS_READY");
   const bool lanes_env = !(rmode && std::strcmp(rmode, "wave") == 0);
   const size_t lane_lds = (size_t)(D + R) * kWave * 4;
-  int lds_blk = 0;
-  err = hipDeviceGetAttribute(&lds_blk, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device);
-  if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
   const bool lanes = lanes_env && lane_lds <= (size_t)lds_blk;  // else one wave per candidate throughout
   struct Plan {
     int64_t chunk, sub, nslots, n_ticket;
-    size_t sz_fin, sz_rank, sz_miss, sz_spill, sz_rows, sz_own, sz_cp, sz_meta, sz_wk, sz_wb, sz_tk, sz_lane, total;
+    size_t sz_fin, sz_rank, sz_miss, sz_spill, sz_rows, sz_own, sz_cp, sz_meta, sz_wk, sz_wb, sz_tk, sz_lane, sz_slots, total;
   };
   auto plan_of = [&](int64_t chunk, int64_t sub_cap) {
     Plan q{};
@@ -2396,6 +2363,16 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     q.sz_miss = align(((size_t)chunk * N + 1) * 2);
     q.sz_spill = align((size_t)chunk * N * 8 + 8);
     q.sz_rows = src.op_major ? align((size_t)chunk * N + 1) : 0;
+    q.sz_lane = lanes ? align((size_t)chunk * D * 2) + align((size_t)chunk * 4) : 0;
+    if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
+      q.sub = chunk;
+      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
+      q.sz_slots = pk_slot * (size_t)q.nslots;
+      q.n_ticket = (B + chunk - 1) / chunk;
+      q.sz_tk = align((size_t)q.n_ticket * 4);
+      q.total = q.sz_fin + q.sz_rank + q.sz_miss + q.sz_spill + q.sz_rows + q.sz_slots + q.sz_tk + q.sz_lane;
+      return q;
+    }
     q.sz_own = align((size_t)sub * own_stride(N) * sizeof(Rec));
     q.sz_cp = align((size_t)sub * cp_stride(E) * sizeof(Rec));
     q.sz_meta = align((size_t)sub * 3 * (D + 1) * 4);
@@ -2403,7 +2380,6 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     q.sz_wb = align((size_t)q.nslots * slot_cap * 8);
     q.n_ticket = (B + chunk - 1) / chunk * ((chunk + sub - 1) / sub);
     q.sz_tk = align((size_t)q.n_ticket * 4);
-    q.sz_lane = lanes ? align((size_t)chunk * D * 2) + align((size_t)chunk * 4) : 0;
     q.total = q.sz_fin + q.sz_rank + q.sz_miss + q.sz_spill + q.sz_rows +
               (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) + q.sz_wk + q.sz_wb + q.sz_tk + q.sz_lane;
     return q;
@@ -2438,7 +2414,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       chunk = chunk > kWave ? chunk / 2 / kWave * kWave : chunk / 2;
     }
   };
-  const int64_t budget0 = ss_scratch_budget(g->device, g->pool, (int64_t)ppref.total, 7);
+  const int64_t budget0 = ss_scratch_budget(g->device, g->pool, (int64_t)ppref.total, pk.ok ? 5 : 7);
   if (W.query) {
     W.need_min = pmin.total;
     W.need_pref = ppref.total;
@@ -2495,6 +2471,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     lcnt = reinterpret_cast<uint16_t *>(take(align((size_t)chunk * D * 2)));
     lovf = reinterpret_cast<uint32_t *>(take(align((size_t)chunk * 4)));
   }
+  void *const slots = take(pl.sz_slots);
   MemPass M{};
   for (int k = 0; k < sets; ++k) {
     M.own[k] = reinterpret_cast<Rec *>(take(pl.sz_own));
@@ -2510,7 +2487,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   M.nslots = pl.nslots;
   M.slot_cap = slot_cap;
   M.iv_fast = iv_fast;
-  M.single = W.single;
+  M.single = W.single || pk.ok;
   M.sets = sets;
   M.aux = g->aux;
 
@@ -2558,7 +2535,11 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       rc = hip_fail(err, "ready_schedule launch");
       break;
     }
-    rc = memory_passes(g, M, Pc, fin, nb, true, peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    if (pk.ok)
+      rc = ss_launch_peaks(g, pk, Pc, fin, N, nullptr, rank, slots, pl.nslots, nb, M.ticket + M.it++,
+                           peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    else
+      rc = memory_passes(g, M, Pc, fin, N, nb, true, peak ? peak + b0 * D : nullptr, violation + b0, stream);
   }
   const int jrc = mem_pass_join(M, stream);
   if (rc == SS_OK) rc = jrc;
@@ -2611,10 +2592,18 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
   const bool ports = arr64 != nullptr && E > 0;
   if (ports && (!iv_fast || !g->view.succ2_pe))
     return ss_set_error(SS_ERR_UNSUPPORTED, "port arrivals need the branch-free interval writer");
+  int lds_blk = 0, lds_cu = 0;
+  err = hipDeviceGetAttribute(&lds_blk, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device);
+  if (err == hipSuccess)
+    err = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device);
+  if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
+  const PeaksShape pk = ss_peaks_shape(g, ports, cus, lds_blk, lds_cu);
   const int64_t rec_per_cand = (own_stride(N) + cp_stride(E)) * (int64_t)sizeof(Rec) + 3 * (D + 1) * 4 + N * 2;
-  const int64_t sub = std::min<int64_t>(B, std::max<int64_t>(1, kRecordBudget / std::max<int64_t>(1, rec_per_cand)));
+  const int64_t sub = pk.ok ? B
+                            : std::min<int64_t>(B, std::max<int64_t>(1, kRecordBudget / std::max<int64_t>(1, rec_per_cand)));
   const int64_t chunk = std::min<int64_t>(B, std::max<int64_t>(1, kScratchBudget / ((N + (ports ? E : 0)) * 4)));
-  const int64_t nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
+  const int64_t nslots = pk.ok ? std::min(pk.blocks, chunk)
+                               : std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
   const int64_t slot_cap = N + E + 1;
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t sz_fin = align((size_t)chunk * N * 4 + 4);
@@ -2628,10 +2617,10 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
   const int64_t n_ticket = n_chunk * ((chunk + sub - 1) / sub);
   const size_t sz_tk = align((size_t)n_ticket * 4);
   const size_t sz_arr = ports ? align((size_t)chunk * E * 4) : 0;
+  const size_t sz_mem = pk.ok ? ss_peaks_slot_bytes(g, pk, false) * (size_t)nslots
+                              : kRecSets * (sz_own + sz_cp + sz_meta) + sz_rank + sz_wk + sz_wb;
   SsScratch scr;
-  err = ss_scratch_get(g->device, g->pool,
-                       sz_fin + sz_arr + kRecSets * (sz_own + sz_cp + sz_meta) + sz_rank + sz_wk + sz_wb + sz_tk,
-                       stream, &scr);
+  err = ss_scratch_get(g->device, g->pool, sz_fin + sz_arr + sz_tk + sz_mem, stream, &scr);
   void *scratch = scr.p;
   if (err != hipSuccess) return hip_fail(err, "allocating the memory-pass scratch");
   unsigned char *p = static_cast<unsigned char *>(scratch);
@@ -2643,21 +2632,24 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
   auto *fin = reinterpret_cast<uint32_t *>(take(sz_fin));
   auto *arr = ports ? reinterpret_cast<uint32_t *>(take(sz_arr)) : nullptr;
   MemPass M{};
-  for (int k = 0; k < kRecSets; ++k) {
-    M.own[k] = reinterpret_cast<Rec *>(take(sz_own));
-    M.cp[k] = reinterpret_cast<Rec *>(take(sz_cp));
-    M.meta[k] = reinterpret_cast<int32_t *>(take(sz_meta));
-  }
-  M.rank = reinterpret_cast<uint16_t *>(take(sz_rank));
-  M.wk = reinterpret_cast<uint32_t *>(take(sz_wk));
-  M.wb = reinterpret_cast<int64_t *>(take(sz_wb));
   M.ticket = reinterpret_cast<uint32_t *>(take(sz_tk));
+  void *const slots = p;
+  if (!pk.ok) {
+    for (int k = 0; k < kRecSets; ++k) {
+      M.own[k] = reinterpret_cast<Rec *>(take(sz_own));
+      M.cp[k] = reinterpret_cast<Rec *>(take(sz_cp));
+      M.meta[k] = reinterpret_cast<int32_t *>(take(sz_meta));
+    }
+    M.rank = reinterpret_cast<uint16_t *>(take(sz_rank));
+    M.wk = reinterpret_cast<uint32_t *>(take(sz_wk));
+    M.wb = reinterpret_cast<int64_t *>(take(sz_wb));
+  }
   M.n_ticket = n_ticket;
   M.sub = sub;
   M.nslots = nslots;
   M.slot_cap = slot_cap;
   M.iv_fast = iv_fast;
-  M.single = false;
+  M.single = pk.ok;
   M.sets = kRecSets;
   M.aux = g->aux;
   int rc = mem_pass_events(M);
@@ -2685,7 +2677,11 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
         break;
       }
     }
-    rc = memory_passes(g, M, P + b0 * N, fin, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream, arr);
+    if (pk.ok)
+      rc = ss_launch_peaks(g, pk, P + b0 * N, fin, N, arr, nullptr, slots, nslots, nb, M.ticket + M.it++,
+                           peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    else
+      rc = memory_passes(g, M, P + b0 * N, fin, N, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream, arr);
   }
   const int jrc = mem_pass_join(M, stream);
   if (rc == SS_OK) rc = jrc;

@@ -1,0 +1,89 @@
+"""The memory pass whose gap table lies in LDS, where it can go wrong: sizes
+around its chunks, its waves and the largest table a workgroup holds, one
+device with every op, ops with many successors, and more events in one gap
+than the LDS list holds.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_15762_amd import ss, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("makespan", "peak", "violation", "slack", "sumfin")
+
+
+def check(g, P, dispatch="index", links="latency"):
+    mode = {"ready": oracle.READY_ORDER, "ports": oracle.LINK_PORTS}.get(dispatch if links == "latency" else links, 0)
+    ref = oracle.simulate_batch(g, P, dispatch=mode, n_threads=8)
+    out = ss.simulate_batch(ss.Gmg(g), torch.from_numpy(P).cuda(), dispatch=dispatch, links=links)
+    torch.cuda.synchronize()
+    for f in FIELDS:
+        a = out[f].cpu().numpy()
+        assert np.array_equal(a, ref[f]), (f, np.argwhere(a != ref[f])[:3].tolist())
+
+
+def random_case(seed, n, D, B, **kw):
+    kw = dict(dict(n_req=3, n_slices=4, n_link=2, edge_p=0.25, max_span=9, slice_scale=400, cap_scale=20_000), **kw)
+    g = synth.random_gmg(seed, n_ops=n, n_dev=D, **kw)
+    P = np.random.default_rng(seed).integers(0, D, (B, n)).astype(np.uint8)
+    P[0] = 0  # every op on one device
+    P[1, n // 2:] = P[1, n // 2]
+    return g, P
+
+
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+@pytest.mark.parametrize("outdeg", [2, None])
+@pytest.mark.parametrize("n,D", [(1, 1), (63, 2), (64, 255), (65, 3), (127, 128), (129, 5), (513, 64), (1100, 7),
+                                 (2049, 33)])
+def test_sizes(n, D, outdeg, dispatch):
+    print(f"{n} ops on {D} devices, out-degree {outdeg}, {dispatch}", flush=True)
+    check(*random_case(n + D, n, D, 37, max_outdeg=outdeg), dispatch=dispatch)
+
+
+@pytest.mark.parametrize("max_bytes", [1000, 1 << 31])  # 32- and 64-bit byte sums
+@pytest.mark.parametrize("step", [-600, -1, 0, 1, 600])
+def test_largest_table(step, max_bytes):
+    """12 (20 with 64-bit sums) bytes an entry, two an op of event list: about
+    11,600 (7,400) ops on three devices fill 160 KB; both sides of it."""
+    n = (11_600 if max_bytes == 1000 else 7_400) + step
+    print(f"{n} ops, sizes up to {max_bytes}", flush=True)
+    check(*random_case(5, n, 3, 6, max_bytes=max_bytes, max_outdeg=2, edge_p=0.1, cap_scale=max_bytes * 100))
+
+
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+@pytest.mark.parametrize("fan,D", [(8, 4), (9, 4), (64, 48), (200, 255)])
+def test_many_successors(fan, D, dispatch):
+    """Ops with `fan` consumers, beside ops with few."""
+    rng = np.random.default_rng(fan)
+    n = 3 * (fan + 2)
+    edges = [(0, v) for v in range(1, fan + 1)] + [(fan + 1, v) for v in range(fan + 2, 2 * fan + 2)]
+    edges += [(v, v + fan + 2) for v in range(fan + 2, 2 * fan) if v + fan + 2 < n]
+    g = synth.make_gmg(D, ["op"] * n, edges, rng.integers(0, 2, n), [[int(x)] for x in rng.integers(1, 90, n)],
+                       rng.integers(0, 5000, n), [[(int(rng.integers(0, 300)), synth.TIME_INF)] for _ in range(D)],
+                       [20_000] * D, [0, 50], [5_000, 9_000],
+                       link_class=rng.integers(0, 3, (D, D)).astype(np.uint8), bw=(50, 10, 7), lat=(0, 3, 1))
+    P = rng.integers(0, D, (29, n)).astype(np.uint8)
+    P[::4, :fan] %= min(D, 3)
+    check(g, P, dispatch=dispatch)
+
+
+@pytest.mark.parametrize("links", ["latency", "ports"])
+@pytest.mark.parametrize("copies", [20, 200, 900])
+def test_events_of_one_gap(copies, links):
+    """A long op on device 0 during which the copies for every later op of the
+    device arrive, and whose large input is freed at its finish: all in one
+    gap whose bound exceeds every exact value (the list holds 64 events, or
+    one per eight ops)."""
+    n = 2 + 2 * copies
+    edges = [(0, 1)] + [(2 + i, 2 + copies + i) for i in range(copies)]
+    dur = [[2], [100_000]] + [[1 + i % 7] for i in range(copies)] + [[1]] * copies
+    out = [1 << 20, 8] + [64 + 8 * (i % 5) for i in range(copies)] + [8] * copies
+    g = synth.make_gmg(4, ["op"] * n, edges, [0] * n, dur, out, [[(0, synth.TIME_INF)]] * 4,
+                       [1 << 19, 1 << 24, 1 << 24, 1 << 24], [0], [1 << 20], bw=(1000,), lat=(1,))
+    P = np.zeros((9, n), np.uint8)
+    for c in range(9):
+        P[c, 0] = 1 + c % 3
+        P[c, 2:2 + copies] = 1 + (np.arange(copies) + c) % 3
+    check(g, P, links=links)
