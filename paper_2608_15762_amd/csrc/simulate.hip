@@ -37,9 +37,11 @@
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kMemCap = 2048;                     // endpoints of one device sorted in LDS
+constexpr int kMemWaves = 16;                     // waves of a memory-pass workgroup
+constexpr int kMemThreads = kMemWaves * kWave;
+constexpr int kMemCap = 512;                      // endpoints a wave sorts in its share of the LDS
+constexpr size_t kMemLds = (size_t)kMemWaves * kMemCap * 16;  // keys and deltas: 128 KB
 constexpr int64_t kFinBudget = int64_t(16) << 30; // bytes of finish-time scratch per chunk
-constexpr int kMemBlocksPerCU = 4;
 
 __device__ __forceinline__ int64_t imax(int64_t a, int64_t b) { return a > b ? a : b; }
 
@@ -738,42 +740,34 @@ __global__ __launch_bounds__(kWave) void port_event_schedule(const GmgView G, co
 // finishes need not follow index order, the last consumer is the one with the
 // latest (finish, index); every time is clipped to t_now, from which on the
 // peak is taken (t_now = 0 otherwise, where no time is negative).
-template <bool kWrite, bool kReady, bool kPorts, class KP, class VP>
-__device__ int op_events(const GmgView &G, const uint8_t *prow, const int64_t *frow, int y, int e, KP keys,
-                         VP vals, int w, const int64_t *arr, int64_t nb, int64_t c) {
+// push(key, delta) takes an endpoint.
+template <bool kReady, bool kPorts, class Push>
+__device__ void op_events(const GmgView &G, const uint8_t *prow, const int64_t *frow, int y, int e,
+                          const int64_t *arr, int64_t nb, int64_t c, Push &&push) {
   const int C = G.n_class, K = G.n_link, D = G.n_dev;
   const int64_t T0 = G.t_now;
-  int n = 0;
   const int64_t fy = frow[y];
   const int64_t by = G.out_bytes[y];
   if (by > 0) {
-    if (kWrite) {
-      keys[w] = 2 * imax(fy - G.dur[(int64_t)y * C + G.dev_class[e]], T0) + 1;
-      vals[w] = by;
-    }
-    ++n;
+    push(2 * imax(fy - G.dur[(int64_t)y * C + G.dev_class[e]], T0) + 1, by);
     const int x0 = G.succ_ptr[y], x1 = G.succ_ptr[y + 1];
     if (x1 > x0) {
-      if (kWrite) {
-        int64_t F = fy;
-        for (int q = x0; q < x1; ++q) {
-          const int x = G.succ_idx[q];
-          const int dx = prow[x];
-          int64_t t;
-          if (dx == e) {
-            t = frow[x];
-          } else if (kPorts) {
-            t = arr[(int64_t)G.succ_pe[q] * nb + c];
-          } else {
-            t = G.issue_at ? imax(fy, xfer_floor(G, prow, y, dx)) : fy;
-            t += G.xfer[(int64_t)y * K + G.link_class[e * D + dx]];
-          }
-          F = imax(F, t);
+      int64_t F = fy;
+      for (int q = x0; q < x1; ++q) {
+        const int x = G.succ_idx[q];
+        const int dx = prow[x];
+        int64_t t;
+        if (dx == e) {
+          t = frow[x];
+        } else if (kPorts) {
+          t = arr[(int64_t)G.succ_pe[q] * nb + c];
+        } else {
+          t = G.issue_at ? imax(fy, xfer_floor(G, prow, y, dx)) : fy;
+          t += G.xfer[(int64_t)y * K + G.link_class[e * D + dx]];
         }
-        keys[w + n] = 2 * imax(F, T0);
-        vals[w + n] = -by;
+        F = imax(F, t);
       }
-      ++n;
+      push(2 * imax(F, T0), -by);
     }
   }
   const int p1 = G.pred_ptr[y + 1];
@@ -811,20 +805,14 @@ __device__ int op_events(const GmgView &G, const uint8_t *prow, const int64_t *f
       }
     }
     if (!last) continue;
-    if (kWrite) {
-      int64_t t0;
-      if (kPorts)
-        t0 = arr[(int64_t)q * nb + c] - G.xfer[(int64_t)u * K + G.link_class[prow[u] * D + e]];
-      else
-        t0 = G.issue_at ? imax(frow[u], xfer_floor(G, prow, u, e)) : frow[u];
-      keys[w + n] = 2 * imax(t0, T0) + 1;
-      vals[w + n] = bu;
-      keys[w + n + 1] = 2 * imax(fy, T0);
-      vals[w + n + 1] = -bu;
-    }
-    n += 2;
+    int64_t t0;
+    if (kPorts)
+      t0 = arr[(int64_t)q * nb + c] - G.xfer[(int64_t)u * K + G.link_class[prow[u] * D + e]];
+    else
+      t0 = G.issue_at ? imax(frow[u], xfer_floor(G, prow, u, e)) : frow[u];
+    push(2 * imax(t0, T0) + 1, bu);
+    push(2 * imax(fy, T0), -bu);
   }
-  return n;
 }
 
 template <class KP, class VP>
@@ -839,36 +827,50 @@ __device__ __forceinline__ void compare_swap(KP keys, VP vals, int i, int l) {
   }
 }
 
-// Ascending bitonic sort of n (key, value) pairs by one wave.  Every
-// comparator puts the smaller key at the lower index, so the virtual padding
-// up to the next power of two (keys = +inf) never moves and pairs that reach
-// into it are skipped.
-template <class KP, class VP>
-__device__ void sort_pairs(KP keys, VP vals, int n, int lane) {
+// What evaluates one device: a wave of the workgroup, or the whole workgroup.
+struct WaveTeam {
+  int id;  // lane
+  static constexpr int size = kWave;
+  __device__ void sync() const {  // orders the wave's LDS accesses (they complete in issue order)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+struct BlockTeam {
+  int id;  // thread
+  static constexpr int size = kMemThreads;
+  __device__ void sync() const { __syncthreads(); }
+};
+
+// Ascending bitonic sort of n (key, value) pairs.  Every comparator puts the
+// smaller key at the lower index, so the virtual padding up to the next power
+// of two (keys = +inf) never moves and pairs that reach into it are skipped.
+template <class Team, class KP, class VP>
+__device__ void sort_pairs(const Team &team, KP keys, VP vals, int n) {
   if (n < 2) return;
   int lg = 0;
   while ((1 << lg) < n) ++lg;
   const int half_total = 1 << (lg - 1);
   for (int kb = 1; kb <= lg; ++kb) {
     const int k = 1 << kb, hmask = (k >> 1) - 1;
-    for (int q = lane; q < half_total; q += kWave) {
+    for (int q = team.id; q < half_total; q += Team::size) {
       const int base = (q >> (kb - 1)) << kb, off = q & hmask;
       const int l = base + k - 1 - off;
       if (l < n) compare_swap(keys, vals, base + off, l);
     }
-    __syncthreads();
+    team.sync();
     for (int jb = kb - 2; jb >= 0; --jb) {
       const int j = 1 << jb;
-      for (int q = lane; q < half_total; q += kWave) {
+      for (int q = team.id; q < half_total; q += Team::size) {
         const int i = ((q >> jb) << (jb + 1)) + (q & (j - 1));
         if (i + j < n) compare_swap(keys, vals, i, i + j);
       }
-      __syncthreads();
+      team.sync();
     }
   }
 }
 
-// Maximum over prefixes of the sorted deltas (= peak live bytes, >= 0).
+// Maximum over prefixes of the sorted deltas (= peak live bytes, >= 0), for one wave.
 template <class VP>
 __device__ int64_t max_prefix_sum(VP vals, int n, int lane) {
   int64_t carry = 0, best = 0;
@@ -888,29 +890,60 @@ __device__ int64_t max_prefix_sum(VP vals, int n, int lane) {
   return best;
 }
 
-__device__ __forceinline__ int wave_exclusive_scan(int x, int lane, int *total) {
-  int s = x;
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(s, o, kWave);
-    if (lane >= o) s += y;
+// The same by the workgroup, each thread a run of the deltas; part holds two
+// values per wave.  Every thread gets the result.
+template <class VP>
+__device__ int64_t max_prefix_block(VP vals, int n, int64_t *part) {
+  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  const int per = (n + kMemThreads - 1) / kMemThreads, lo = min(tid * per, n), hi = min(lo + per, n);
+  int64_t s = 0, best = 0;
+  for (int i = lo; i < hi; ++i) {
+    s += vals[i];
+    best = imax(best, s);  // from the run's start
   }
-  *total = __shfl(s, kWave - 1, kWave);
-  return s - x;
+  int64_t incl = s;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int64_t y = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += y;
+  }
+  if (lane == kWave - 1) part[w] = incl;
+  __syncthreads();
+  int64_t before = incl - s;
+  for (int k = 0; k < w; ++k) before += part[k];
+  best = imax(0, before + best);
+  for (int o = kWave / 2; o >= 1; o >>= 1) best = imax(best, __shfl_xor(best, o, kWave));
+  if (lane == 0) part[kMemWaves + w] = best;
+  __syncthreads();
+  for (int k = 0; k < kMemWaves; ++k) best = imax(best, part[kMemWaves + k]);
+  __syncthreads();
+  return best;
 }
 
+// One workgroup per candidate: the ops grouped by device, then a wave per
+// device, whose endpoints are pushed into the wave's share of the LDS in any
+// order, sorted and summed.  A device with more endpoints than a wave's share
+// (a batch placed whole on one device) is evaluated by the whole workgroup in
+// all of the LDS, and beyond that in the workgroup's global buffer.
+// Bound: the waves' chains of dependent loads and LDS round trips, so all
+// sixteen waves of a CU work on devices of one candidate instead of four on
+// candidates of their own (240 candidates of 2,000 ops on 128 devices 1.18 ms
+// before, 16,384 of 2,052 ops on 32 devices 8.64 ms).
 template <bool kReady, bool kPorts>
-__global__ __launch_bounds__(kWave) void memory_kernel(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
-                                                       const int64_t *__restrict__ fin,
-                                                       const int64_t *__restrict__ arr, int32_t *__restrict__ bydev_all,
-                                                       int64_t *__restrict__ gkeys_all,
-                                                       int64_t *__restrict__ gvals_all, int64_t slot_cap,
-                                                       int64_t *__restrict__ peak, uint8_t *__restrict__ violation) {
-  __shared__ int64_t skeys[kMemCap];
-  __shared__ int64_t svals[kMemCap];
+__global__ __launch_bounds__(kMemThreads) void memory_kernel(
+    const GmgView G, const uint8_t *__restrict__ P, int64_t nb, const int64_t *__restrict__ fin,
+    const int64_t *__restrict__ arr, int32_t *__restrict__ bydev_all, int64_t *__restrict__ gkeys_all,
+    int64_t *__restrict__ gvals_all, int64_t slot_cap, int64_t *__restrict__ peak, uint8_t *__restrict__ violation) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  int64_t *skeys = reinterpret_cast<int64_t *>(lds_raw);  // [kMemWaves * kMemCap]
+  int64_t *svals = skeys + kMemWaves * kMemCap;
+  __shared__ int64_t part[2 * kMemWaves];
   __shared__ int32_t start[257];
   __shared__ int32_t fillp[256];
+  __shared__ int32_t count[kMemWaves + 1];  // endpoints pushed by each wave, by the workgroup
+  __shared__ int32_t viol, n_large;
+  __shared__ uint8_t large[256];  // devices left to the workgroup
   const int D = G.n_dev, N = G.n_ops;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   int32_t *bydev = bydev_all + (int64_t)blockIdx.x * N;
   int64_t *gkeys = gkeys_all + (int64_t)blockIdx.x * slot_cap;
   int64_t *gvals = gvals_all + (int64_t)blockIdx.x * slot_cap;
@@ -919,59 +952,101 @@ __global__ __launch_bounds__(kWave) void memory_kernel(const GmgView G, const ui
     const int64_t *frow = fin + c * N;
     if (violation[c] & SS_VIOLATION_INVALID) {
       if (peak)
-        for (int d = lane; d < D; d += kWave) peak[c * D + d] = 0;
+        for (int d = tid; d < D; d += kMemThreads) peak[c * D + d] = 0;
       continue;
     }
     // group the ops by device (order inside a device is irrelevant: the
     // endpoints are sorted afterwards)
-    for (int d = lane; d <= D; d += kWave) start[d] = 0;
+    for (int d = tid; d <= D; d += kMemThreads) start[d] = 0;
+    if (tid == 0) viol = n_large = 0;
     __syncthreads();
-    for (int v = lane; v < N; v += kWave) atomicAdd(&start[prow[v]], 1);
+    for (int v = tid; v < N; v += kMemThreads) atomicAdd(&start[prow[v]], 1);
     __syncthreads();
-    if (lane == 0) {
-      int s = 0;
-      for (int d = 0; d < D; ++d) {
-        const int t = start[d];
-        start[d] = s;
-        fillp[d] = s;
-        s += t;
+    if (w == 0) {
+      int carry = 0;
+      for (int d0 = 0; d0 < D; d0 += kWave) {
+        const int d = d0 + lane, x = d < D ? start[d] : 0;
+        int s = x;
+        for (int o = 1; o < kWave; o <<= 1) {
+          const int y = __shfl_up(s, o, kWave);
+          if (lane >= o) s += y;
+        }
+        if (d < D) start[d] = fillp[d] = carry + s - x;
+        carry += __shfl(s, kWave - 1, kWave);
       }
-      start[D] = s;
+      if (lane == 0) start[D] = carry;
     }
     __syncthreads();
-    for (int v = lane; v < N; v += kWave) bydev[atomicAdd(&fillp[prow[v]], 1)] = v;
+    for (int v = tid; v < N; v += kMemThreads) bydev[atomicAdd(&fillp[prow[v]], 1)] = v;
     __syncthreads();
 
-    uint8_t viol = 0;
-    for (int e = 0; e < D; ++e) {
+    int64_t *wkeys = skeys + w * kMemCap, *wvals = svals + w * kMemCap;
+    const WaveTeam wave{lane};
+    for (int e = w; e < D; e += kMemWaves) {
       const int lo = start[e], hi = start[e + 1];
       int64_t pk = 0;
       if (hi > lo) {
-        int mine = 0;
+        if (lane == 0) count[w] = 0;
+        wave.sync();
         for (int q = lo + lane; q < hi; q += kWave)
-          mine += op_events<false, kReady, kPorts>(G, prow, frow, bydev[q], e, (int64_t *)nullptr, (int64_t *)nullptr,
-                                                   0, arr, nb, c);
-        int total;
-        int w = wave_exclusive_scan(mine, lane, &total);
-        if (total <= kMemCap) {
-          for (int q = lo + lane; q < hi; q += kWave)
-            w += op_events<true, kReady, kPorts>(G, prow, frow, bydev[q], e, skeys, svals, w, arr, nb, c);
-          __syncthreads();
-          sort_pairs(skeys, svals, total, lane);
-          pk = max_prefix_sum(svals, total, lane);
-        } else {
-          for (int q = lo + lane; q < hi; q += kWave)
-            w += op_events<true, kReady, kPorts>(G, prow, frow, bydev[q], e, gkeys, gvals, w, arr, nb, c);
-          __syncthreads();
-          sort_pairs(gkeys, gvals, total, lane);
-          pk = max_prefix_sum(gvals, total, lane);
+          op_events<kReady, kPorts>(G, prow, frow, bydev[q], e, arr, nb, c, [&](int64_t key, int64_t val) {
+            const int at = atomicAdd(&count[w], 1);
+            if (at < kMemCap) {
+              wkeys[at] = key;
+              wvals[at] = val;
+            }
+          });
+        wave.sync();
+        const int total = count[w];
+        if (total > kMemCap) {
+          if (lane == 0) large[atomicAdd(&n_large, 1)] = (uint8_t)e;
+          continue;
         }
-        __syncthreads();
+        sort_pairs(wave, wkeys, wvals, total);
+        pk = max_prefix_sum(wvals, total, lane);
       }
-      if (peak && lane == 0) peak[c * D + e] = pk;
-      if (pk > G.cap[e]) viol = SS_VIOLATION_MEMORY;
+      if (lane == 0) {
+        if (peak) peak[c * D + e] = pk;
+        if (pk > G.cap[e]) viol = 1;
+      }
     }
-    if (lane == 0) violation[c] = viol;
+    __syncthreads();
+    const int nl = n_large;
+    for (int i = 0; i < nl; ++i) {
+      const int e = large[i], lo = start[e], hi = start[e + 1];
+      auto gather = [&](int64_t *keys, int64_t *vals, int cap) {
+        if (tid == 0) count[kMemWaves] = 0;
+        __syncthreads();
+        for (int q = lo + tid; q < hi; q += kMemThreads)
+          op_events<kReady, kPorts>(G, prow, frow, bydev[q], e, arr, nb, c, [&](int64_t key, int64_t val) {
+            const int at = atomicAdd(&count[kMemWaves], 1);
+            if (at < cap) {
+              keys[at] = key;
+              vals[at] = val;
+            }
+          });
+        __syncthreads();
+        return count[kMemWaves];
+      };
+      const BlockTeam team{tid};
+      int64_t pk;
+      int total = gather(skeys, svals, kMemWaves * kMemCap);
+      if (total <= kMemWaves * kMemCap) {
+        sort_pairs(team, skeys, svals, total);
+        pk = max_prefix_block(svals, total, part);
+      } else {
+        __syncthreads();
+        total = gather(gkeys, gvals, (int)slot_cap);
+        sort_pairs(team, gkeys, gvals, total);
+        pk = max_prefix_block(gvals, total, part);
+      }
+      if (tid == 0) {
+        if (peak) peak[c * D + e] = pk;
+        if (pk > G.cap[e]) viol = 1;
+      }
+    }
+    __syncthreads();
+    if (tid == 0) violation[c] = viol ? SS_VIOLATION_MEMORY : 0;
     __syncthreads();
   }
 }
@@ -1031,7 +1106,7 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
   auto plan_of = [&](int64_t chunk) {
     Plan q{};
     q.chunk = chunk = std::min<int64_t>(std::max<int64_t>(1, chunk), B);
-    q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kMemBlocksPerCU, chunk));
+    q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus, chunk));
     q.sz_fin = align((size_t)chunk * N * 8 + 8);
     q.sz_comp = align((size_t)chunk * R * 8 + 8);
     q.sz_miss = ready ? align((size_t)chunk * N * 4 + 4) : 0;
@@ -1177,7 +1252,13 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
     const int64_t grid = std::min<int64_t>(nb, nslots);
     SsTimingRec *t_mem = ss_timing_start(SS_KERNEL_MEMORY, stream);
     auto *mem_fn = ready ? &memory_kernel<true, false> : ports ? &memory_kernel<false, true> : &memory_kernel<false, false>;
-    hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3(kWave), 0, stream, G, Pc, nb,
+    err = hipFuncSetAttribute(reinterpret_cast<const void *>(mem_fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kMemLds);
+    if (err != hipSuccess) {
+      rc = hip_fail(err, "hipFuncSetAttribute");
+      break;
+    }
+    hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3(kMemThreads), kMemLds, stream, G, Pc, nb,
                        static_cast<const int64_t *>(fin), static_cast<const int64_t *>(arr), bydev, gkeys, gvals,
                        slot_cap, peak ? peak + b0 * D : nullptr, violation + b0);
     err = hipGetLastError();
