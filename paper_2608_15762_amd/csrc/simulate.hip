@@ -202,6 +202,199 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
   }
 }
 
+// The same schedule with one wave per candidate, for batches too small to fill
+// the chip with a lane each (a round of the incremental loop has a candidate
+// per partition, 240 at cluster scale).  The lanes take 64 consecutive ops:
+// each lane reads its op's fields and folds every input that an earlier chunk
+// produced into the op's earliest start, so that what is left of an op in turn
+// is its inputs from the same chunk (kept as lane, floor and transfer time),
+// the device clock and the slice, all wave-uniform; the next op's device state
+// is read from LDS while the current op is placed.
+// Bound: that serial chain, about 0.1 us an op whatever the batch; a lane per
+// candidate walks it in dependent global loads, 1 us an op (240 candidates of
+// 2,000 ops: 2.03 ms before).  Above kWaveCandidates the waves' shared issue
+// slots cost more than the lanes' latency.
+constexpr int64_t kWaveCandidates = 4096;
+constexpr int64_t kWaveReq = 512;  // requests whose completions fit the LDS beside the devices
+
+__device__ __forceinline__ int64_t lane_value(int64_t x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+struct DevState {  // a device's clock and its current slice
+  int64_t clk, begin, end;
+};
+
+size_t schedule_wave_lds(int64_t D, int64_t R) { return (size_t)D * (sizeof(DevState) + 4) + (size_t)R * 8 + 8; }
+
+__global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
+                                                       int64_t *__restrict__ fin, int64_t *__restrict__ comp,
+                                                       const Resume RS, int64_t *__restrict__ makespan,
+                                                       int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
+                                                       uint8_t *__restrict__ violation) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = G.n_class, K = G.n_link;
+  const int lane = threadIdx.x;
+  DevState *dev = reinterpret_cast<DevState *>(lds_raw);       // [D]
+  int64_t *lcomp = reinterpret_cast<int64_t *>(dev + D);       // [R]
+  int32_t *cur = reinterpret_cast<int32_t *>(lcomp + R);       // [D]
+  const int64_t c = blockIdx.x;
+  const uint8_t *prow = P + c * N;
+  int64_t *frow = fin + c * N;
+  const bool from = RS.clk != nullptr;
+  for (int d = lane; d < D; d += kWave) {
+    const int k = from ? RS.cur[d] : 0, q = G.slice_ptr[d] + k;
+    dev[d] = DevState{from ? RS.clk[d] : 0, G.slice_begin[q], G.slice_end[q]};
+    cur[d] = k;
+  }
+  for (int r = lane; r < R; r += kWave) lcomp[r] = from ? RS.comp[r] : G.release[r];
+  bool invalid = RS.bad ? RS.bad[c] != 0 : false;  // the prefix is not walked, but must name devices
+  int64_t ms = from && lane == 0 ? RS.scal[0] : 0, sum = from && lane == 0 ? RS.scal[1] : 0;
+  __syncthreads();
+  for (int v0 = RS.k0; v0 < N; v0 += kWave) {
+    const int v = v0 + lane, n = min(kWave, N - v0);
+    const bool act = v < N;
+    int d = act ? prow[v] : 0;
+    if (d >= D) {  // not a device of the set: finish the walk on device 0, report sentinels
+      invalid = true;
+      d = 0;
+    }
+    const int r = act ? G.op_req[v] : 0;
+    const int64_t done = act && G.done_fin ? G.done_fin[v] : -1;
+    int64_t w = 1, base = 0;
+    // inputs from this chunk: producer's lane, earliest transfer start, transfer time
+    int n_in = 0, l0 = 0, l1 = 0;
+    int64_t t0 = 0, x0 = 0, t1 = 0, x1 = 0;
+    if (act && done < 0) {
+      w = G.dur[(int64_t)v * C + G.dev_class[d]];
+      base = G.release[r];
+      if (G.issue_at) base = imax(base, G.issue_at[v]);
+      const int e1 = G.pred_ptr[v + 1];
+      for (int e = G.pred_ptr[v]; e < e1; ++e) {
+        const int u = G.pred_idx[e];
+        int du = prow[u];
+        if (du >= D) du = 0;
+        int64_t floor = 0, x = 0;
+        if (du != d) {
+          if (G.issue_at) floor = xfer_floor(G, prow, u, d);
+          x = G.xfer[(int64_t)u * K + G.link_class[du * D + d]];
+        }
+        if (u < v0) {
+          base = imax(base, imax(frow[u], floor) + x);
+        } else {
+          if (n_in == 0) {
+            l0 = u - v0;
+            t0 = floor;
+            x0 = x;
+          } else if (n_in == 1) {
+            l1 = u - v0;
+            t1 = floor;
+            x1 = x;
+          }
+          ++n_in;
+        }
+      }
+    }
+    int64_t f = 0;  // finish of the lane's op
+    int di = __builtin_amdgcn_readlane(d, 0);
+    DevState st = dev[di];
+    for (int i = 0; i < n; ++i) {
+      const int dn = __builtin_amdgcn_readlane(d, min(i + 1, n - 1));
+      const DevState nx = dev[dn];  // in flight while op i is placed
+      const int64_t di_done = lane_value(done, i);
+      int64_t fi;
+      if (di_done >= 0) {
+        // done (running schedule): it finished at its recorded time; the
+        // device is free from then on
+        fi = di_done;
+        st.clk = imax(st.clk, fi);
+      } else {
+        const int ni = __builtin_amdgcn_readlane(n_in, i);
+        int64_t ready = lane_value(base, i);
+        if (ni > 0) {
+          const int64_t fu = lane_value(f, __builtin_amdgcn_readlane(l0, i));
+          ready = imax(ready, imax(fu, lane_value(t0, i)) + lane_value(x0, i));
+        }
+        if (ni > 1) {
+          const int64_t fu = lane_value(f, __builtin_amdgcn_readlane(l1, i));
+          ready = imax(ready, imax(fu, lane_value(t1, i)) + lane_value(x1, i));
+        }
+        if (ni > 2) {  // all inputs from this chunk again, past the two kept
+          const int e1 = G.pred_ptr[v0 + i + 1];
+          for (int e = G.pred_ptr[v0 + i]; e < e1; ++e) {
+            const int u = G.pred_idx[e];
+            if (u < v0) continue;
+            int du = prow[u];
+            if (du >= D) du = 0;
+            int64_t t = lane_value(f, __builtin_amdgcn_readfirstlane(u - v0));
+            if (du != di) {
+              if (G.issue_at) t = imax(t, xfer_floor(G, prow, u, di));
+              t += G.xfer[(int64_t)u * K + G.link_class[du * D + di]];
+            }
+            ready = imax(ready, t);
+          }
+        }
+        // one op at a time, in the first idle slice that holds it
+        const int64_t wi = lane_value(w, i), t = imax(ready, st.clk);
+        int64_t s = imax(t, st.begin);
+        if (s + wi > st.end) {
+          int k = cur[di];
+          const int sbase = G.slice_ptr[di];
+          do {
+            ++k;
+            st.begin = G.slice_begin[sbase + k];
+            st.end = G.slice_end[sbase + k];
+            s = imax(t, st.begin);
+          } while (s + wi > st.end);
+          cur[di] = k;
+        }
+        fi = s + wi;
+        st.clk = fi;
+      }
+      f = lane == i ? fi : f;
+      dev[di] = st;
+      st.clk = dn == di ? st.clk : nx.clk;
+      st.begin = dn == di ? st.begin : nx.begin;
+      st.end = dn == di ? st.end : nx.end;
+      di = dn;
+    }
+    if (act) {
+      frow[v] = f;
+      ms = imax(ms, f);
+      sum += f;
+      atomicMax(reinterpret_cast<unsigned long long *>(&lcomp[r]), (unsigned long long)f);  // times are >= 0
+    }
+    __syncthreads();  // the row's stores before the next chunk reads them
+  }
+  for (int o = kWave / 2; o >= 1; o >>= 1) {
+    ms = imax(ms, (int64_t)__shfl_xor(ms, o, kWave));
+    sum += (int64_t)__shfl_xor(sum, o, kWave);
+  }
+  invalid = __any(invalid);
+  __syncthreads();
+  for (int r = lane; r < R; r += kWave) {
+    comp[(int64_t)r * nb + c] = lcomp[r];
+    if (slack) slack[c * R + r] = invalid ? INT64_MIN : G.deadline[r] - lcomp[r];
+  }
+  if (RS.cap_clk) {  // one candidate: its state after its last op
+    for (int d = lane; d < D; d += kWave) {
+      RS.cap_clk[d] = dev[d].clk;
+      RS.cap_cur[d] = cur[d];
+    }
+    if (lane == 0) {
+      RS.cap_scal[0] = ms;
+      RS.cap_scal[1] = sum;
+    }
+  }
+  if (lane == 0) {
+    makespan[c] = invalid ? INT64_MAX : ms;
+    if (sumfin) sumfin[c] = invalid ? INT64_MAX : sum;
+    violation[c] = invalid ? SS_VIOLATION_INVALID : 0;
+  }
+}
+
 // ------------------------------------------------------------------ ready-time dispatch
 // The dispatch rule of Sec. 3.3.2 on the general path: among the ops whose
 // predecessors have all been scheduled, the one with the earliest ready time
@@ -1221,6 +1414,10 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
                                                   align((size_t)chunk * N * 4 + 4));
         hipLaunchKernelGGL(port_event_schedule, dim3((unsigned)nb), dim3(kWave), sched_lds, stream, G, Pc, nb, fin,
                            arr, lists, pend, E + 1, makespan + b0, sumfin ? sumfin + b0 : nullptr,
+                           slack ? slack + b0 * R : nullptr, violation + b0);
+      } else if (nb <= kWaveCandidates && R <= kWaveReq) {
+        hipLaunchKernelGGL(schedule_wave, dim3((unsigned)nb), dim3(kWave), schedule_wave_lds(D, R), stream, G, Pc, nb,
+                           fin, comp, RS, makespan + b0, sumfin ? sumfin + b0 : nullptr,
                            slack ? slack + b0 * R : nullptr, violation + b0);
       } else {
         hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave),
