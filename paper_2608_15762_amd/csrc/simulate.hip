@@ -45,6 +45,12 @@ constexpr int64_t kFinBudget = int64_t(16) << 30; // bytes of finish-time scratc
 
 __device__ __forceinline__ int64_t imax(int64_t a, int64_t b) { return a > b ? a : b; }
 
+// Orders the LDS accesses of one wave (they complete in issue order).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Running schedule (GMG issue times given): the transfer of u's output to
 // device e starts no earlier than the first issue time among u's consumers
 // placed on e, the moment its Intent exists.  0 when none is there.
@@ -206,28 +212,26 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
 // the chip with a lane each (a round of the incremental loop has a candidate
 // per partition, 240 at cluster scale).  The lanes take 64 consecutive ops:
 // each lane reads its op's fields and folds every input that an earlier chunk
-// produced into the op's earliest start, so that what is left of an op in turn
-// is its inputs from the same chunk (kept as lane, floor and transfer time),
-// the device clock and the slice, all wave-uniform; the next op's device state
-// is read from LDS while the current op is placed.
-// Bound: that serial chain, about 0.1 us an op whatever the batch; a lane per
-// candidate walks it in dependent global loads, 1 us an op (240 candidates of
-// 2,000 ops: 2.03 ms before).  Above kWaveCandidates the waves' shared issue
-// slots cost more than the lanes' latency.
-constexpr int64_t kWaveCandidates = 4096;
+// produced into the op's earliest start.  What is left depends on ops of the
+// same chunk only, the inputs among them and the op before on the same device:
+// the chunk runs in steps, each placing every op whose dependencies are
+// placed, with finish times and device states in LDS.
+// Bound: the latency of those steps, as many as the chunk's longest chain
+// (about 0.15 us each); a lane per candidate walks every op in dependent global
+// loads, 1 us an op.  Measured, a wave and a lane per candidate: 240 candidates
+// of 2,000 ops of 16 requests 0.21 and 2.03 ms, 4,096 of 2,052 ops of 4
+// requests 0.74 and 2.2 ms; 16,384 of those 2.17 and 2.35 ms, 16,384 of one
+// chain of 322 ops 0.50 and 0.50 ms, beyond which the lanes win.
+constexpr int64_t kWaveCandidates = 16384;
 constexpr int64_t kWaveReq = 512;  // requests whose completions fit the LDS beside the devices
-
-__device__ __forceinline__ int64_t lane_value(int64_t x, int lane) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
-  return (int64_t)((uint64_t)hi << 32 | lo);
-}
 
 struct DevState {  // a device's clock and its current slice
   int64_t clk, begin, end;
 };
 
-size_t schedule_wave_lds(int64_t D, int64_t R) { return (size_t)D * (sizeof(DevState) + 4) + (size_t)R * 8 + 8; }
+size_t schedule_wave_lds(int64_t D, int64_t R) {
+  return (size_t)D * (sizeof(DevState) + 8 + 4) + (size_t)(R + kWave) * 8 + 8;
+}
 
 __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
                                                        int64_t *__restrict__ fin, int64_t *__restrict__ comp,
@@ -238,8 +242,10 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = G.n_class, K = G.n_link;
   const int lane = threadIdx.x;
   DevState *dev = reinterpret_cast<DevState *>(lds_raw);       // [D]
-  int64_t *lcomp = reinterpret_cast<int64_t *>(dev + D);       // [R]
-  int32_t *cur = reinterpret_cast<int32_t *>(lcomp + R);       // [D]
+  uint64_t *mask = reinterpret_cast<uint64_t *>(dev + D);      // [D] the chunk's lanes on each device
+  int64_t *lcomp = reinterpret_cast<int64_t *>(mask + D);      // [R]
+  int64_t *lfin = lcomp + R;                                   // [64] finish times of the chunk
+  int32_t *cur = reinterpret_cast<int32_t *>(lfin + kWave);    // [D]
   const int64_t c = blockIdx.x;
   const uint8_t *prow = P + c * N;
   int64_t *frow = fin + c * N;
@@ -248,13 +254,14 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
     const int k = from ? RS.cur[d] : 0, q = G.slice_ptr[d] + k;
     dev[d] = DevState{from ? RS.clk[d] : 0, G.slice_begin[q], G.slice_end[q]};
     cur[d] = k;
+    mask[d] = 0;
   }
   for (int r = lane; r < R; r += kWave) lcomp[r] = from ? RS.comp[r] : G.release[r];
   bool invalid = RS.bad ? RS.bad[c] != 0 : false;  // the prefix is not walked, but must name devices
   int64_t ms = from && lane == 0 ? RS.scal[0] : 0, sum = from && lane == 0 ? RS.scal[1] : 0;
   __syncthreads();
   for (int v0 = RS.k0; v0 < N; v0 += kWave) {
-    const int v = v0 + lane, n = min(kWave, N - v0);
+    const int v = v0 + lane;
     const bool act = v < N;
     int d = act ? prow[v] : 0;
     if (d >= D) {  // not a device of the set: finish the walk on device 0, report sentinels
@@ -264,9 +271,20 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
     const int r = act ? G.op_req[v] : 0;
     const int64_t done = act && G.done_fin ? G.done_fin[v] : -1;
     int64_t w = 1, base = 0;
+    uint64_t dep = 0;  // lanes of this chunk the op waits for
     // inputs from this chunk: producer's lane, earliest transfer start, transfer time
     int n_in = 0, l0 = 0, l1 = 0;
     int64_t t0 = 0, x0 = 0, t1 = 0, x1 = 0;
+    auto transfer = [&](int u, int64_t &floor, int64_t &x) {
+      int du = prow[u];
+      if (du >= D) du = 0;
+      floor = x = 0;
+      if (du != d) {
+        if (G.issue_at) floor = xfer_floor(G, prow, u, d);
+        x = G.xfer[(int64_t)u * K + G.link_class[du * D + d]];
+      }
+    };
+    if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
     if (act && done < 0) {
       w = G.dur[(int64_t)v * C + G.dev_class[d]];
       base = G.release[r];
@@ -274,16 +292,12 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
       const int e1 = G.pred_ptr[v + 1];
       for (int e = G.pred_ptr[v]; e < e1; ++e) {
         const int u = G.pred_idx[e];
-        int du = prow[u];
-        if (du >= D) du = 0;
-        int64_t floor = 0, x = 0;
-        if (du != d) {
-          if (G.issue_at) floor = xfer_floor(G, prow, u, d);
-          x = G.xfer[(int64_t)u * K + G.link_class[du * D + d]];
-        }
+        int64_t floor, x;
+        transfer(u, floor, x);
         if (u < v0) {
           base = imax(base, imax(frow[u], floor) + x);
         } else {
+          dep |= 1ull << (u - v0);
           if (n_in == 0) {
             l0 = u - v0;
             t0 = floor;
@@ -297,68 +311,58 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
         }
       }
     }
+    wave_fence();
+    const uint64_t before = mask[d] & ((1ull << lane) - 1);
+    wave_fence();
+    mask[d] = 0;
+    if (before) dep |= 1ull << (63 - __clzll((long long)before));  // the op before it on its device
     int64_t f = 0;  // finish of the lane's op
-    int di = __builtin_amdgcn_readlane(d, 0);
-    DevState st = dev[di];
-    for (int i = 0; i < n; ++i) {
-      const int dn = __builtin_amdgcn_readlane(d, min(i + 1, n - 1));
-      const DevState nx = dev[dn];  // in flight while op i is placed
-      const int64_t di_done = lane_value(done, i);
-      int64_t fi;
-      if (di_done >= 0) {
-        // done (running schedule): it finished at its recorded time; the
-        // device is free from then on
-        fi = di_done;
-        st.clk = imax(st.clk, fi);
-      } else {
-        const int ni = __builtin_amdgcn_readlane(n_in, i);
-        int64_t ready = lane_value(base, i);
-        if (ni > 0) {
-          const int64_t fu = lane_value(f, __builtin_amdgcn_readlane(l0, i));
-          ready = imax(ready, imax(fu, lane_value(t0, i)) + lane_value(x0, i));
-        }
-        if (ni > 1) {
-          const int64_t fu = lane_value(f, __builtin_amdgcn_readlane(l1, i));
-          ready = imax(ready, imax(fu, lane_value(t1, i)) + lane_value(x1, i));
-        }
-        if (ni > 2) {  // all inputs from this chunk again, past the two kept
-          const int e1 = G.pred_ptr[v0 + i + 1];
-          for (int e = G.pred_ptr[v0 + i]; e < e1; ++e) {
-            const int u = G.pred_idx[e];
-            if (u < v0) continue;
-            int du = prow[u];
-            if (du >= D) du = 0;
-            int64_t t = lane_value(f, __builtin_amdgcn_readfirstlane(u - v0));
-            if (du != di) {
-              if (G.issue_at) t = imax(t, xfer_floor(G, prow, u, di));
-              t += G.xfer[(int64_t)u * K + G.link_class[du * D + di]];
+    for (uint64_t todo = __ballot(act); todo;) {
+      // a lane waits for lower lanes only, so the lowest one left always goes
+      const bool go = ((todo >> lane) & 1) && !(dep & todo);
+      if (go) {
+        DevState st = dev[d];
+        if (done >= 0) {
+          // done (running schedule): it finished at its recorded time; the
+          // device is free from then on
+          f = done;
+          st.clk = imax(st.clk, f);
+        } else {
+          int64_t ready = base;
+          if (n_in > 0) ready = imax(ready, imax(lfin[l0], t0) + x0);
+          if (n_in > 1) ready = imax(ready, imax(lfin[l1], t1) + x1);
+          if (n_in > 2) {  // all inputs from this chunk again, past the two kept
+            const int e1 = G.pred_ptr[v + 1];
+            for (int e = G.pred_ptr[v]; e < e1; ++e) {
+              const int u = G.pred_idx[e];
+              if (u < v0) continue;
+              int64_t floor, x;
+              transfer(u, floor, x);
+              ready = imax(ready, imax(lfin[u - v0], floor) + x);
             }
-            ready = imax(ready, t);
           }
+          // one op at a time, in the first idle slice that holds it
+          const int64_t t = imax(ready, st.clk);
+          int64_t s = imax(t, st.begin);
+          if (s + w > st.end) {
+            int k = cur[d];
+            const int sbase = G.slice_ptr[d];
+            do {
+              ++k;
+              st.begin = G.slice_begin[sbase + k];
+              st.end = G.slice_end[sbase + k];
+              s = imax(t, st.begin);
+            } while (s + w > st.end);
+            cur[d] = k;
+          }
+          f = s + w;
+          st.clk = f;
         }
-        // one op at a time, in the first idle slice that holds it
-        const int64_t wi = lane_value(w, i), t = imax(ready, st.clk);
-        int64_t s = imax(t, st.begin);
-        if (s + wi > st.end) {
-          int k = cur[di];
-          const int sbase = G.slice_ptr[di];
-          do {
-            ++k;
-            st.begin = G.slice_begin[sbase + k];
-            st.end = G.slice_end[sbase + k];
-            s = imax(t, st.begin);
-          } while (s + wi > st.end);
-          cur[di] = k;
-        }
-        fi = s + wi;
-        st.clk = fi;
+        dev[d] = st;
+        lfin[lane] = f;
       }
-      f = lane == i ? fi : f;
-      dev[di] = st;
-      st.clk = dn == di ? st.clk : nx.clk;
-      st.begin = dn == di ? st.begin : nx.begin;
-      st.end = dn == di ? st.end : nx.end;
-      di = dn;
+      todo &= ~__ballot(go);
+      wave_fence();
     }
     if (act) {
       frow[v] = f;
@@ -1024,10 +1028,7 @@ __device__ __forceinline__ void compare_swap(KP keys, VP vals, int i, int l) {
 struct WaveTeam {
   int id;  // lane
   static constexpr int size = kWave;
-  __device__ void sync() const {  // orders the wave's LDS accesses (they complete in issue order)
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-  }
+  __device__ void sync() const { wave_fence(); }
 };
 struct BlockTeam {
   int id;  // thread

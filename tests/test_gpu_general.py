@@ -1,5 +1,5 @@
 """The general (int64) kernels where their variants meet: the schedule with a
-wave per candidate and with a lane per candidate (up to 4,096 candidates and
+wave per candidate and with a lane per candidate (up to 16,384 candidates and
 512 requests, and beyond), its 64-op chunks, inputs from the same chunk, and
 the memory pass's three ways to hold a device's endpoints (a wave's share of
 the LDS, all of it, the global buffer).  Bit-exact against the oracle."""
@@ -41,7 +41,7 @@ def batch(g, B, seed=0):
     return P
 
 
-@pytest.mark.parametrize("B", [1, 4096, 4097])
+@pytest.mark.parametrize("B", [1, 16384, 16385])
 @pytest.mark.parametrize("snapshot", [False, True])
 def test_batch_sizes(B, snapshot):
     print(f"{B} candidates, snapshot {snapshot}", flush=True)
@@ -49,7 +49,7 @@ def test_batch_sizes(B, snapshot):
     check(synth.random_snapshot(g, 5, done_p=0.5) if snapshot else g, batch(g, B) if B > 1 else batch(g, 2)[:1])
 
 
-@pytest.mark.parametrize("B", [40, 4099])
+@pytest.mark.parametrize("B", [40, 16400])
 def test_resumed(B):
     """Candidates resumed after a prefix that ends inside a chunk."""
     print(f"{B} candidates resumed", flush=True)
