@@ -84,6 +84,12 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Bucket of the time -> slice lookup that holds time t (times reach past 2^31).
+__device__ __forceinline__ uint32_t lut_bucket(const GmgView &G, uint32_t t) {
+  const uint32_t b = t >> G.lut_shift, last = (uint32_t)G.lut_nb - 1u;
+  return b < last ? b : last;
+}
+
 // Zero fill (used for counters that kernels take work tickets from).
 __global__ __launch_bounds__(256) void fill_zero_u32(uint32_t *__restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
@@ -337,7 +343,7 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
     }
     S.wq[q2] = kOneClass ? meta(kMetaDur, t) : G.dur32[(int64_t)t * C + dcls[dt]];
     lb = umax32(lb, clk[(int)dt * kWave + lane]) + (kOneClass ? meta(kMetaDur, t) : 0u);
-    const uint32_t e = dt * (uint32_t)G.lut_nb + (uint32_t)min((int)(lb >> G.lut_shift), G.lut_nb - 1);
+    const uint32_t e = dt * (uint32_t)G.lut_nb + lut_bucket(G, lb);
     S.le[q2] = e;
     S.lw[q2] = G.lut_w[e];
   };
@@ -629,7 +635,7 @@ __global__ __launch_bounds__(kWave) void ready_schedule(const GmgView G, const u
     uint32_t s = umax32(ready, clk[d]);
     {  // the first idle slice that holds [s', s' + w) with s' >= s; slices
        // before the table's entry end before s + w
-      const uint32_t e = (uint32_t)d * (uint32_t)G.lut_nb + (uint32_t)min((int)((s + w) >> G.lut_shift), G.lut_nb - 1);
+      const uint32_t e = (uint32_t)d * (uint32_t)G.lut_nb + lut_bucket(G, s + w);
       const uint4 lw = G.lut_w[e];
       const uint32_t t0 = umax32(s, lw.x), t1 = umax32(s, lw.z);
       if (t0 + w <= lw.y) {
@@ -841,7 +847,7 @@ __global__ __launch_bounds__(kWave) void ready_lanes(const GmgView G, const uint
     const uint32_t w = C == 1 ? G.dur32[v] : G.dur32[(int64_t)v * C + G.dev_class[d]];
     uint32_t s = umax32(ready, clk[d * kWave + lane]);
     {  // the first idle slice that holds [s', s' + w) with s' >= s
-      const uint32_t e = (uint32_t)d * (uint32_t)G.lut_nb + (uint32_t)min((int)((s + w) >> G.lut_shift), G.lut_nb - 1);
+      const uint32_t e = (uint32_t)d * (uint32_t)G.lut_nb + lut_bucket(G, s + w);
       const uint4 lw = G.lut_w[e];
       const uint32_t t0 = umax32(s, lw.x), t1 = umax32(s, lw.z);
       if (t0 + w <= lw.y) {

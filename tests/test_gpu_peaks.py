@@ -87,3 +87,13 @@ def test_events_of_one_gap(copies, links):
         P[c, 0] = 1 + c % 3
         P[c, 2:2 + copies] = 1 + (np.arange(copies) + c) % 3
     check(g, P, links=links)
+
+
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+def test_times_past_2_31_with_short_slices(dispatch):
+    """Finite slices that end early (so the slice lookup has buckets of 1 us)
+    and finishes between 2^31 and 2^32."""
+    n = 5
+    g = synth.make_gmg(2, ["op"] * n, [(0, 1), (1, 2), (2, 3), (3, 4)], [0] * n, [[820_000_000]] * n, [100] * n,
+                       [[(0, 40), (90, synth.TIME_INF)], [(7, synth.TIME_INF)]], [150, 1000], [0], [1 << 40])
+    check(g, np.array([[0] * n, [1] * n, [0, 1, 0, 1, 0], [0, 0, 1, 1, 1]], np.uint8), dispatch=dispatch)
