@@ -425,8 +425,35 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     // 32-bit time path: every time the simulation can produce is <= horizon
     int64_t max_bytes = 0;
     for (int64_t v = 0; v < N; ++v) max_bytes = std::max(max_bytes, d->out_bytes[v]);
-    const bool time32 = !snapshot && horizon < (i128)UINT32_MAX && N <= 65535 && E <= 65535 && max_slices <= 65535 &&
+    const bool fits32 = !snapshot && N <= 65535 && E <= 65535 && max_slices <= 65535 &&
                         max_bytes <= (int64_t)UINT32_MAX;
+    const bool time32 = fits32 && horizon < (i128)UINT32_MAX;
+    // a longer horizon, most of it idle windows that no candidate need reach:
+    // the 32-bit tables up to a limit below which no sum wraps, when an
+    // average load that every candidate has (the least work spread over all
+    // devices, from the first idle slice on) stays within half of it
+    uint32_t time_limit = 0;
+    if (fits32 && !time32 && N > 0 && R <= 512) {
+      i128 step = 0, work = 0, first = kTimeLimit;
+      for (int64_t v = 0; v < N; ++v) {
+        int64_t wmin = d->dur[v * C], wmax = 0;
+        for (int64_t c = 0; c < C; ++c) {
+          wmin = std::min(wmin, d->dur[v * C + c]);
+          wmax = std::max(wmax, d->dur[v * C + c]);
+        }
+        int64_t xmax = 0;
+        for (int64_t k = 0; k < K; ++k) xmax = std::max(xmax, xfer[v * K + k]);
+        step = std::max<i128>(step, (i128)wmax + xmax);
+        work += wmin;
+      }
+      // one op's largest duration and another's largest transfer
+      step = 2 * step + 2;
+      for (int64_t x = 0; x < D; ++x) first = std::min<i128>(first, d->slice_begin[d->slice_ptr[x]]);
+      const i128 limit = (i128)UINT32_MAX - step;
+      if (limit > 0 && max_rel < limit && 2 * (std::max(first, max_rel) + work / D) < limit)
+        time_limit = (uint32_t)limit;
+    }
+    const bool tab32 = time32 || time_limit > 0;
     std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe, lutk, lutw;
     std::vector<uint8_t> lgrp;
     // ready-time dispatch: the ops without predecessors by (release of their
@@ -448,7 +475,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     // common power of two, what can be live on one device at once (each output
     // and at most one copy per consumer edge) sums below 2^32
     int32_t pshift = 0, pnarrow = 0;
-    if (time32) {
+    if (tab32) {
       uint64_t any_bits = 0;
       for (int64_t v = 0; v < N; ++v) any_bits |= (uint64_t)d->out_bytes[v];
       pshift = any_bits ? __builtin_ctzll(any_bits) : 0;
@@ -457,7 +484,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
       pnarrow = total < ((i128)1 << 32) ? 1 : 0;
     }
     const int64_t meta_stride = std::max<int64_t>(128, (N + 63) / 64 * 64 + 64);  // two blocks of 64 past any op
-    if (time32) {
+    if (tab32) {
       meta.assign((size_t)kOpMetaFields * meta_stride, 0);
       auto M = [&](int f, int64_t v) -> uint32_t & { return meta[(size_t)f * meta_stride + v]; };
       for (int64_t v = 0; v < N; ++v) {
@@ -539,8 +566,12 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
       se32.assign(S + 1, UINT32_MAX);
 
       for (int64_t k = 0; k < S; ++k) {
-        sb32[k] = (uint32_t)d->slice_begin[k];
-        se32[k] = d->slice_end[k] == SS_TIME_INF ? UINT32_MAX : (uint32_t)d->slice_end[k];
+        // with a limit, a slice that begins past it is an open one at the
+        // limit, and one that ends past 32 bits is open: what is placed there
+        // finishes past the limit or is placed as without it
+        const bool past = time_limit > 0 && d->slice_begin[k] >= (int64_t)time_limit;
+        sb32[k] = past ? time_limit : (uint32_t)d->slice_begin[k];
+        se32[k] = past || d->slice_end[k] >= (int64_t)UINT32_MAX ? UINT32_MAX : (uint32_t)d->slice_end[k];
       }
       // time -> slice lookup: about 128K buckets in all (at least 64 per device)
       uint32_t max_end = 0;
@@ -645,6 +676,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     V.issue_at = d->issue_at ? reinterpret_cast<const int64_t *>(base + o_issue) : nullptr;
     V.t_now = d->t_now;
     V.time32 = time32 ? 1 : 0;
+    V.time_limit = time_limit;
     V.dur32 = reinterpret_cast<const uint32_t *>(base + o_dur32);
     V.xfer32 = reinterpret_cast<const uint32_t *>(base + o_xfer32);
     V.slice_begin32 = reinterpret_cast<const uint32_t *>(base + o_sb32);

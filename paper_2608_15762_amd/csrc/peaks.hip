@@ -404,7 +404,7 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     __syncthreads();
     const int64_t c = misc[0];
     if (c >= nb) return;
-    if (violation[c] & SS_VIOLATION_INVALID) {
+    if (violation[c] & (SS_VIOLATION_INVALID | SS_VIOLATION_RETRY)) {
       if (peak)
         for (int d = tid; d < D; d += T) peak[c * D + d] = 0;
       continue;

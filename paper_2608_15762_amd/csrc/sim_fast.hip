@@ -1,5 +1,9 @@
-// Fast path of the batched what-if simulation (gfx950), used when the loader
-// proved that every simulated time fits in 32 bits and N <= 65535.
+// Fast path of the batched what-if simulation (gfx950), used when N <= 65535
+// and the loader proved that every simulated time fits in 32 bits, or found
+// that a candidate's times very likely do (a horizon stretched by far idle
+// windows): there the schedule marks candidates that pass the limit, and the
+// int64 kernels simulate them after the memory pass (16,384 candidates of
+// 2,052 ops with a day of idle windows 10.9 ms on the int64 kernels, 2.1 ms here).
 //
 // Index-order dispatch, per chunk of candidates:
 //   transpose     candidates' placement rows -> op-major [op][candidate]
@@ -507,7 +511,7 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
     if (sumfin) sumfin[c] = (int64_t)sum;
     if (slack)
       for (int rr = 0; rr < R; ++rr) slack[c * R + rr] = G.deadline[rr] - (int64_t)comp[rr * kWave + lane];
-    violation[c] = 0;
+    violation[c] = G.time_limit && ms >= G.time_limit ? SS_VIOLATION_RETRY : 0;
   }
 }
 
@@ -1117,7 +1121,7 @@ __global__ __launch_bounds__(kWave) void fast_intervals(const GmgView G, const u
   const int D = G.n_dev, N = G.n_ops, E = G.pred_ptr[G.n_ops], K = G.n_link;
   const int lane = threadIdx.x;
   const int64_t j = blockIdx.x, c = j0 + j;
-  if (violation[c] & SS_VIOLATION_INVALID) return;
+  if (violation[c] & (SS_VIOLATION_INVALID | SS_VIOLATION_RETRY)) return;
   const uint8_t *prow = P + c * N;
   const uint32_t *frow = fin + c * fpitch;
   const uint32_t *arow = kPorts ? arr + c * E : nullptr;
@@ -1849,7 +1853,7 @@ __global__ __launch_bounds__(kWave) void fast_peaks(const GmgView G, int64_t j0,
   for (int64_t j = (uint32_t)__shfl((int)tk, 0, kWave); j < nj; j = (uint32_t)__shfl((int)tk, 0, kWave)) {
     tk = lane == 0 ? atomicAdd(ticket, 1u) : 0u;
     const int64_t c = j0 + j;
-    if (violation[c] & SS_VIOLATION_INVALID) {
+    if (violation[c] & (SS_VIOLATION_INVALID | SS_VIOLATION_RETRY)) {
       if (peak)
         for (int d = lane; d < D; d += kWave) peak[c * D + d] = 0;
       continue;
@@ -2055,9 +2059,9 @@ size_t ss_fast_schedule_lds(const ss_gmg *g) {
 // Scratch of one fast-path call, laid out for a chunk of `chunk` candidates
 // and memory-pass sub-chunks of `sub`.
 struct FastPlan {
-  int64_t chunk = 0, sub = 0, nslots = 0, n_ticket = 0;
+  int64_t chunk = 0, sub = 0, nslots = 0, n_ticket = 0, retry_slots = 0;
   int sets = kRecSets;
-  size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
+  size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_retry = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
          total = 0;
 };
 
@@ -2102,7 +2106,8 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   // chunk: placements (op-major for the schedule from row-major input, rows
   // for the memory passes from op-major input), op-major and row-major finish
   // times
-  const int64_t per_cand = N * (1 + 4) + pitch * 4;
+  const bool retry = G.time_limit > 0;  // int64 kernels for candidates whose times pass 32 bits
+  const int64_t per_cand = N * (1 + 4) + pitch * 4 + (retry ? (N + R) * 8 : 0);
   // A schedule launch is best a whole number of rounds of the waves the chip
   // holds at once (every wave runs about as long as any other).
   const int64_t round =
@@ -2125,13 +2130,15 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_pt = align((size_t)chunk * N + 1);
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
     q.sz_row = align((size_t)chunk * pitch * 4 + 4);
+    q.retry_slots = std::min<int64_t>({(int64_t)cus, chunk, chunk > kWave ? chunk : std::max<int64_t>(1, sub_cap)});
+    q.sz_retry = retry ? align(ss_retry_scratch(g, chunk, q.retry_slots)) : 0;
     if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
       q.sub = chunk;
       q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
       q.n_ticket = 1;
       q.sz_tk = 256;
-      q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_slots + q.sz_tk;
+      q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + q.sz_slots + q.sz_tk;
       return q;
     }
     q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
@@ -2143,7 +2150,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_wb = align((size_t)q.nslots * slot_cap * 8);
     q.n_ticket = (B + chunk - 1) / chunk * ((chunk + sub - 1) / sub);
     q.sz_tk = align(((size_t)q.n_ticket + 1) * 4);
-    q.total = q.sz_pt + q.sz_fin + q.sz_row + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
+    q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
               q.sz_rank + q.sz_wk + q.sz_wb + q.sz_tk;
     return q;
   };
@@ -2224,6 +2231,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   auto *PT = reinterpret_cast<uint8_t *>(take(pl.sz_pt));  // op-major copy, or candidate rows of op-major input
   auto *finT = reinterpret_cast<uint32_t *>(take(pl.sz_fin));
   auto *fin = reinterpret_cast<uint32_t *>(take(pl.sz_row));
+  void *const retry_mem = take(pl.sz_retry);
   void *const slots = take(pl.sz_slots);
   MemPass M{};
   for (int k = 0; k < pl.sets; ++k) {
@@ -2309,6 +2317,15 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
                            peak ? peak + b0 * D : nullptr, violation + b0, stream);
     else
       rc = memory_passes(g, M, Pc, fin, pitch, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream);
+    if (retry && rc == SS_OK) {
+      if (!M.single && M.it > 0) {  // after the chunk's last peak pass
+        const hipError_t we = hipStreamWaitEvent(stream, M.pk_done[(M.it - 1) % M.sets], 0);
+        if (we != hipSuccess) rc = hip_fail(we, "hipStreamWaitEvent");
+      }
+      if (rc == SS_OK)
+        rc = ss_run_retry(g, Pc, nb, retry_mem, pl.retry_slots, cus, makespan + b0, peak ? peak + b0 * D : nullptr, violation + b0,
+                          slack ? slack + b0 * R : nullptr, sumfin ? sumfin + b0 : nullptr, stream);
+    }
   }
   const int jrc = mem_pass_join(M, stream);
   if (rc == SS_OK) rc = jrc;

@@ -235,8 +235,9 @@ size_t schedule_wave_lds(int64_t D, int64_t R) {
 
 __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
                                                        int64_t *__restrict__ fin, int64_t *__restrict__ comp,
-                                                       const Resume RS, int64_t *__restrict__ makespan,
-                                                       int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
+                                                       const Resume RS, bool retry,
+                                                       int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
+                                                       int64_t *__restrict__ slack,
                                                        uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = G.n_class, K = G.n_link;
@@ -246,156 +247,159 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
   int64_t *lcomp = reinterpret_cast<int64_t *>(mask + D);      // [R]
   int64_t *lfin = lcomp + R;                                   // [64] finish times of the chunk
   int32_t *cur = reinterpret_cast<int32_t *>(lfin + kWave);    // [D]
-  const int64_t c = blockIdx.x;
-  const uint8_t *prow = P + c * N;
-  int64_t *frow = fin + c * N;
-  const bool from = RS.clk != nullptr;
-  for (int d = lane; d < D; d += kWave) {
-    const int k = from ? RS.cur[d] : 0, q = G.slice_ptr[d] + k;
-    dev[d] = DevState{from ? RS.clk[d] : 0, G.slice_begin[q], G.slice_end[q]};
-    cur[d] = k;
-    mask[d] = 0;
-  }
-  for (int r = lane; r < R; r += kWave) lcomp[r] = from ? RS.comp[r] : G.release[r];
-  bool invalid = RS.bad ? RS.bad[c] != 0 : false;  // the prefix is not walked, but must name devices
-  int64_t ms = from && lane == 0 ? RS.scal[0] : 0, sum = from && lane == 0 ? RS.scal[1] : 0;
-  __syncthreads();
-  for (int v0 = RS.k0; v0 < N; v0 += kWave) {
-    const int v = v0 + lane;
-    const bool act = v < N;
-    int d = act ? prow[v] : 0;
-    if (d >= D) {  // not a device of the set: finish the walk on device 0, report sentinels
-      invalid = true;
-      d = 0;
-    }
-    const int r = act ? G.op_req[v] : 0;
-    const int64_t done = act && G.done_fin ? G.done_fin[v] : -1;
-    int64_t w = 1, base = 0;
-    uint64_t dep = 0;  // lanes of this chunk the op waits for
-    // inputs from this chunk: producer's lane, earliest transfer start, transfer time
-    int n_in = 0, l0 = 0, l1 = 0;
-    int64_t t0 = 0, x0 = 0, t1 = 0, x1 = 0;
-    auto transfer = [&](int u, int64_t &floor, int64_t &x) {
-      int du = prow[u];
-      if (du >= D) du = 0;
-      floor = x = 0;
-      if (du != d) {
-        if (G.issue_at) floor = xfer_floor(G, prow, u, d);
-        x = G.xfer[(int64_t)u * K + G.link_class[du * D + d]];
-      }
-    };
-    if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
-    if (act && done < 0) {
-      w = G.dur[(int64_t)v * C + G.dev_class[d]];
-      base = G.release[r];
-      if (G.issue_at) base = imax(base, G.issue_at[v]);
-      const int e1 = G.pred_ptr[v + 1];
-      for (int e = G.pred_ptr[v]; e < e1; ++e) {
-        const int u = G.pred_idx[e];
-        int64_t floor, x;
-        transfer(u, floor, x);
-        if (u < v0) {
-          base = imax(base, imax(frow[u], floor) + x);
-        } else {
-          dep |= 1ull << (u - v0);
-          if (n_in == 0) {
-            l0 = u - v0;
-            t0 = floor;
-            x0 = x;
-          } else if (n_in == 1) {
-            l1 = u - v0;
-            t1 = floor;
-            x1 = x;
-          }
-          ++n_in;
-        }
-      }
-    }
-    wave_fence();
-    const uint64_t before = mask[d] & ((1ull << lane) - 1);
-    wave_fence();
-    mask[d] = 0;
-    if (before) dep |= 1ull << (63 - __clzll((long long)before));  // the op before it on its device
-    int64_t f = 0;  // finish of the lane's op
-    for (uint64_t todo = __ballot(act); todo;) {
-      // a lane waits for lower lanes only, so the lowest one left always goes
-      const bool go = ((todo >> lane) & 1) && !(dep & todo);
-      if (go) {
-        DevState st = dev[d];
-        if (done >= 0) {
-          // done (running schedule): it finished at its recorded time; the
-          // device is free from then on
-          f = done;
-          st.clk = imax(st.clk, f);
-        } else {
-          int64_t ready = base;
-          if (n_in > 0) ready = imax(ready, imax(lfin[l0], t0) + x0);
-          if (n_in > 1) ready = imax(ready, imax(lfin[l1], t1) + x1);
-          if (n_in > 2) {  // all inputs from this chunk again, past the two kept
-            const int e1 = G.pred_ptr[v + 1];
-            for (int e = G.pred_ptr[v]; e < e1; ++e) {
-              const int u = G.pred_idx[e];
-              if (u < v0) continue;
-              int64_t floor, x;
-              transfer(u, floor, x);
-              ready = imax(ready, imax(lfin[u - v0], floor) + x);
-            }
-          }
-          // one op at a time, in the first idle slice that holds it
-          const int64_t t = imax(ready, st.clk);
-          int64_t s = imax(t, st.begin);
-          if (s + w > st.end) {
-            int k = cur[d];
-            const int sbase = G.slice_ptr[d];
-            do {
-              ++k;
-              st.begin = G.slice_begin[sbase + k];
-              st.end = G.slice_end[sbase + k];
-              s = imax(t, st.begin);
-            } while (s + w > st.end);
-            cur[d] = k;
-          }
-          f = s + w;
-          st.clk = f;
-        }
-        dev[d] = st;
-        lfin[lane] = f;
-      }
-      todo &= ~__ballot(go);
-      wave_fence();
-    }
-    if (act) {
-      frow[v] = f;
-      ms = imax(ms, f);
-      sum += f;
-      atomicMax(reinterpret_cast<unsigned long long *>(&lcomp[r]), (unsigned long long)f);  // times are >= 0
-    }
-    __syncthreads();  // the row's stores before the next chunk reads them
-  }
-  for (int o = kWave / 2; o >= 1; o >>= 1) {
-    ms = imax(ms, (int64_t)__shfl_xor(ms, o, kWave));
-    sum += (int64_t)__shfl_xor(sum, o, kWave);
-  }
-  invalid = __any(invalid);
-  __syncthreads();
-  for (int r = lane; r < R; r += kWave) {
-    comp[(int64_t)r * nb + c] = lcomp[r];
-    if (slack) slack[c * R + r] = invalid ? INT64_MIN : G.deadline[r] - lcomp[r];
-  }
-  if (RS.cap_clk) {  // one candidate: its state after its last op
+  for (int64_t c = blockIdx.x; c < nb; c += gridDim.x) {
+    if (retry && violation[c] != SS_VIOLATION_RETRY) continue;
+    __syncthreads();  // the candidate before has been written
+    const uint8_t *prow = P + c * N;
+    int64_t *frow = fin + c * N;
+    const bool from = RS.clk != nullptr;
     for (int d = lane; d < D; d += kWave) {
-      RS.cap_clk[d] = dev[d].clk;
-      RS.cap_cur[d] = cur[d];
+      const int k = from ? RS.cur[d] : 0, q = G.slice_ptr[d] + k;
+      dev[d] = DevState{from ? RS.clk[d] : 0, G.slice_begin[q], G.slice_end[q]};
+      cur[d] = k;
+      mask[d] = 0;
+    }
+    for (int r = lane; r < R; r += kWave) lcomp[r] = from ? RS.comp[r] : G.release[r];
+    bool invalid = RS.bad ? RS.bad[c] != 0 : false;  // the prefix is not walked, but must name devices
+    int64_t ms = from && lane == 0 ? RS.scal[0] : 0, sum = from && lane == 0 ? RS.scal[1] : 0;
+    __syncthreads();
+    for (int v0 = RS.k0; v0 < N; v0 += kWave) {
+      const int v = v0 + lane;
+      const bool act = v < N;
+      int d = act ? prow[v] : 0;
+      if (d >= D) {  // not a device of the set: finish the walk on device 0, report sentinels
+        invalid = true;
+        d = 0;
+      }
+      const int r = act ? G.op_req[v] : 0;
+      const int64_t done = act && G.done_fin ? G.done_fin[v] : -1;
+      int64_t w = 1, base = 0;
+      uint64_t dep = 0;  // lanes of this chunk the op waits for
+      // inputs from this chunk: producer's lane, earliest transfer start, transfer time
+      int n_in = 0, l0 = 0, l1 = 0;
+      int64_t t0 = 0, x0 = 0, t1 = 0, x1 = 0;
+      auto transfer = [&](int u, int64_t &floor, int64_t &x) {
+        int du = prow[u];
+        if (du >= D) du = 0;
+        floor = x = 0;
+        if (du != d) {
+          if (G.issue_at) floor = xfer_floor(G, prow, u, d);
+          x = G.xfer[(int64_t)u * K + G.link_class[du * D + d]];
+        }
+      };
+      if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
+      if (act && done < 0) {
+        w = G.dur[(int64_t)v * C + G.dev_class[d]];
+        base = G.release[r];
+        if (G.issue_at) base = imax(base, G.issue_at[v]);
+        const int e1 = G.pred_ptr[v + 1];
+        for (int e = G.pred_ptr[v]; e < e1; ++e) {
+          const int u = G.pred_idx[e];
+          int64_t floor, x;
+          transfer(u, floor, x);
+          if (u < v0) {
+            base = imax(base, imax(frow[u], floor) + x);
+          } else {
+            dep |= 1ull << (u - v0);
+            if (n_in == 0) {
+              l0 = u - v0;
+              t0 = floor;
+              x0 = x;
+            } else if (n_in == 1) {
+              l1 = u - v0;
+              t1 = floor;
+              x1 = x;
+            }
+            ++n_in;
+          }
+        }
+      }
+      wave_fence();
+      const uint64_t before = mask[d] & ((1ull << lane) - 1);
+      wave_fence();
+      mask[d] = 0;
+      if (before) dep |= 1ull << (63 - __clzll((long long)before));  // the op before it on its device
+      int64_t f = 0;  // finish of the lane's op
+      for (uint64_t todo = __ballot(act); todo;) {
+        // a lane waits for lower lanes only, so the lowest one left always goes
+        const bool go = ((todo >> lane) & 1) && !(dep & todo);
+        if (go) {
+          DevState st = dev[d];
+          if (done >= 0) {
+            // done (running schedule): it finished at its recorded time; the
+            // device is free from then on
+            f = done;
+            st.clk = imax(st.clk, f);
+          } else {
+            int64_t ready = base;
+            if (n_in > 0) ready = imax(ready, imax(lfin[l0], t0) + x0);
+            if (n_in > 1) ready = imax(ready, imax(lfin[l1], t1) + x1);
+            if (n_in > 2) {  // all inputs from this chunk again, past the two kept
+              const int e1 = G.pred_ptr[v + 1];
+              for (int e = G.pred_ptr[v]; e < e1; ++e) {
+                const int u = G.pred_idx[e];
+                if (u < v0) continue;
+                int64_t floor, x;
+                transfer(u, floor, x);
+                ready = imax(ready, imax(lfin[u - v0], floor) + x);
+              }
+            }
+            // one op at a time, in the first idle slice that holds it
+            const int64_t t = imax(ready, st.clk);
+            int64_t s = imax(t, st.begin);
+            if (s + w > st.end) {
+              int k = cur[d];
+              const int sbase = G.slice_ptr[d];
+              do {
+                ++k;
+                st.begin = G.slice_begin[sbase + k];
+                st.end = G.slice_end[sbase + k];
+                s = imax(t, st.begin);
+              } while (s + w > st.end);
+              cur[d] = k;
+            }
+            f = s + w;
+            st.clk = f;
+          }
+          dev[d] = st;
+          lfin[lane] = f;
+        }
+        todo &= ~__ballot(go);
+        wave_fence();
+      }
+      if (act) {
+        frow[v] = f;
+        ms = imax(ms, f);
+        sum += f;
+        atomicMax(reinterpret_cast<unsigned long long *>(&lcomp[r]), (unsigned long long)f);  // times are >= 0
+      }
+      __syncthreads();  // the row's stores before the next chunk reads them
+    }
+    for (int o = kWave / 2; o >= 1; o >>= 1) {
+      ms = imax(ms, (int64_t)__shfl_xor(ms, o, kWave));
+      sum += (int64_t)__shfl_xor(sum, o, kWave);
+    }
+    invalid = __any(invalid);
+    __syncthreads();
+    for (int r = lane; r < R; r += kWave) {
+      comp[(int64_t)r * nb + c] = lcomp[r];
+      if (slack) slack[c * R + r] = invalid ? INT64_MIN : G.deadline[r] - lcomp[r];
+    }
+    if (RS.cap_clk) {  // one candidate: its state after its last op
+      for (int d = lane; d < D; d += kWave) {
+        RS.cap_clk[d] = dev[d].clk;
+        RS.cap_cur[d] = cur[d];
+      }
+      if (lane == 0) {
+        RS.cap_scal[0] = ms;
+        RS.cap_scal[1] = sum;
+      }
     }
     if (lane == 0) {
-      RS.cap_scal[0] = ms;
-      RS.cap_scal[1] = sum;
+      makespan[c] = invalid ? INT64_MAX : ms;
+      if (sumfin) sumfin[c] = invalid ? INT64_MAX : sum;
+      violation[c] = invalid ? SS_VIOLATION_INVALID : retry ? SS_VIOLATION_RETRY : 0;
     }
-  }
-  if (lane == 0) {
-    makespan[c] = invalid ? INT64_MAX : ms;
-    if (sumfin) sumfin[c] = invalid ? INT64_MAX : sum;
-    violation[c] = invalid ? SS_VIOLATION_INVALID : 0;
   }
 }
 
@@ -1126,7 +1130,8 @@ template <bool kReady, bool kPorts>
 __global__ __launch_bounds__(kMemThreads) void memory_kernel(
     const GmgView G, const uint8_t *__restrict__ P, int64_t nb, const int64_t *__restrict__ fin,
     const int64_t *__restrict__ arr, int32_t *__restrict__ bydev_all, int64_t *__restrict__ gkeys_all,
-    int64_t *__restrict__ gvals_all, int64_t slot_cap, int64_t *__restrict__ peak, uint8_t *__restrict__ violation) {
+    int64_t *__restrict__ gvals_all, int64_t slot_cap, bool retry, int64_t *__restrict__ peak,
+    uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   int64_t *skeys = reinterpret_cast<int64_t *>(lds_raw);  // [kMemWaves * kMemCap]
   int64_t *svals = skeys + kMemWaves * kMemCap;
@@ -1144,6 +1149,7 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
   for (int64_t c = blockIdx.x; c < nb; c += gridDim.x) {
     const uint8_t *prow = P + c * N;
     const int64_t *frow = fin + c * N;
+    if (retry && violation[c] != SS_VIOLATION_RETRY) continue;
     if (violation[c] & SS_VIOLATION_INVALID) {
       if (peak)
         for (int d = tid; d < D; d += kMemThreads) peak[c * D + d] = 0;
@@ -1418,7 +1424,7 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
                            slack ? slack + b0 * R : nullptr, violation + b0);
       } else if (nb <= kWaveCandidates && R <= kWaveReq) {
         hipLaunchKernelGGL(schedule_wave, dim3((unsigned)nb), dim3(kWave), schedule_wave_lds(D, R), stream, G, Pc, nb,
-                           fin, comp, RS, makespan + b0, sumfin ? sumfin + b0 : nullptr,
+                           fin, comp, RS, false, makespan + b0, sumfin ? sumfin + b0 : nullptr,
                            slack ? slack + b0 * R : nullptr, violation + b0);
       } else {
         hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave),
@@ -1458,7 +1464,7 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
     }
     hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3(kMemThreads), kMemLds, stream, G, Pc, nb,
                        static_cast<const int64_t *>(fin), static_cast<const int64_t *>(arr), bydev, gkeys, gvals,
-                       slot_cap, peak ? peak + b0 * D : nullptr, violation + b0);
+                       slot_cap, false, peak ? peak + b0 * D : nullptr, violation + b0);
     err = hipGetLastError();
     ss_timing_stop(t_mem, stream);
     if (err != hipSuccess) rc = hip_fail(err, "memory_kernel launch");
@@ -1468,6 +1474,50 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
     if (rc == SS_OK && err != hipSuccess) rc = hip_fail(err, "releasing the scratch");
   }
   return rc;
+}
+
+size_t ss_retry_scratch(const ss_gmg *g, int64_t nb, int64_t slots) {
+  auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const int64_t N = g->n_ops, R = g->n_req;
+  return align((size_t)(nb * N) * 8) + align((size_t)(nb * R) * 8 + 8) + align((size_t)(slots * N) * 4) +
+         2 * align((size_t)(slots * (2 * (N + g->n_edges) + 2)) * 8);
+}
+
+int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, void *scratch, int64_t slots, int cus,
+                 int64_t *makespan, int64_t *peak, uint8_t *violation, int64_t *slack, int64_t *sumfin, hipStream_t stream) {
+  const GmgView &G = g->view;
+  auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const int64_t N = g->n_ops, R = g->n_req, D = g->n_dev;
+  const int64_t slot_cap = 2 * (N + g->n_edges) + 2;
+  auto *p = static_cast<unsigned char *>(scratch);
+  auto take = [&](size_t bytes) {
+    unsigned char *q = p;
+    p += align(bytes);
+    return q;
+  };
+  auto *fin = reinterpret_cast<int64_t *>(take((size_t)(nb * N) * 8));
+  auto *comp = reinterpret_cast<int64_t *>(take((size_t)(nb * R) * 8 + 8));
+  auto *bydev = reinterpret_cast<int32_t *>(take((size_t)(slots * N) * 4));
+  auto *gkeys = reinterpret_cast<int64_t *>(take((size_t)(slots * slot_cap) * 8));
+  auto *gvals = reinterpret_cast<int64_t *>(take((size_t)(slots * slot_cap) * 8));
+  // resident waves walk the chunk's verdict bytes for marked candidates
+  SsTimingRec *t = ss_timing_start(SS_KERNEL_SCHEDULE, stream);
+  hipLaunchKernelGGL(schedule_wave, dim3((unsigned)std::min<int64_t>(nb, (int64_t)cus * 16)), dim3(kWave),
+                     schedule_wave_lds(D, R), stream, G, P, nb, fin, comp, Resume(), true, makespan, sumfin, slack,
+                     violation);
+  ss_timing_stop(t, stream);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return hip_fail(err, "schedule launch");
+  err = hipFuncSetAttribute(reinterpret_cast<const void *>(&memory_kernel<false, false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMemLds);
+  if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
+  t = ss_timing_start(SS_KERNEL_MEMORY, stream);
+  hipLaunchKernelGGL((memory_kernel<false, false>), dim3((unsigned)slots), dim3(kMemThreads), kMemLds, stream, G, P, nb,
+                     static_cast<const int64_t *>(fin), static_cast<const int64_t *>(nullptr), bydev, gkeys, gvals,
+                     slot_cap, true, peak, violation);
+  ss_timing_stop(t, stream);
+  err = hipGetLastError();
+  return err == hipSuccess ? SS_OK : hip_fail(err, "memory_kernel launch");
 }
 
 // Path choice: the 32-bit fast path when the loader enabled it and its LDS
@@ -1486,6 +1536,10 @@ static int simulate_route(const ss_gmg *g, bool ready_dispatch, bool link_ports,
   int lds_max = 0;
   hipError_t err = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device);
   if (err != hipSuccess) return hip_fail(err, "hipDeviceGetAttribute");
+  // past a 32-bit horizon, index order on the 32-bit kernels too while a
+  // candidate's own times stay below the limit (SS_PATH=fast asks for the proof)
+  const bool limited = g->view.time_limit > 0 && !ready_dispatch && !link_ports &&
+                       ss_fast_schedule_lds(g) <= (size_t)lds_max;
   const bool fast_ok = g->view.time32 && (ready_dispatch ? ss_ready_schedule_lds(g) : ss_fast_schedule_lds(g)) <=
                                              (size_t)lds_max;
   const char *path = std::getenv("SS_PATH");
@@ -1495,7 +1549,7 @@ static int simulate_route(const ss_gmg *g, bool ready_dispatch, bool link_ports,
   // memory pass is the 32-bit one when the GMG fits the branch-free interval
   // writer (SS_PATH=generic: the general kernels throughout)
   const bool force_generic = path && std::strcmp(path, "generic") == 0;
-  *generic = !fast_ok || link_ports || force_generic;
+  *generic = !(fast_ok || limited) || link_ports || force_generic;
   *ports_mem_fast = link_ports && !force_generic && g->view.time32 && g->n_ops > 0 && g->n_class == 1 &&
                     g->n_link <= 2 && g->max_outdeg <= 2 && g->view.succ2_pe;
   return SS_OK;
@@ -1504,7 +1558,7 @@ static int simulate_route(const ss_gmg *g, bool ready_dispatch, bool link_ports,
 int ss_simulate_time_bits_of(const ss_gmg *g, bool ready_dispatch, bool link_ports, int *bits) {
   bool generic = false, ports_mem_fast = false;
   const int rc = simulate_route(g, ready_dispatch, link_ports, &generic, &ports_mem_fast);
-  if (rc == SS_OK) *bits = generic ? 64 : 32;
+  if (rc == SS_OK) *bits = generic || !g->view.time32 ? 64 : 32;
   return rc;
 }
 

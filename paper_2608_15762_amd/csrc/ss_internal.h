@@ -32,6 +32,13 @@ struct GmgView {
   // slices per device, and every output size fits in 32 bits; the open slice end becomes 0xFFFFFFFF.  The 32-bit slice
   // arrays hold one spare entry past the last slice.
   int32_t time32;
+  // 0: every time is proven to stay below.  Else the horizon alone is beyond
+  // 32 bits (idle windows far ahead) and the 32-bit tables are there all the
+  // same, exact for a candidate whose finishes stay below time_limit: no slice
+  // begins later than that in them, and no sum of such a finish, a transfer
+  // and a duration wraps, so the first finish past it is seen.  A candidate
+  // with one is marked SS_VIOLATION_RETRY and simulated with int64 times.
+  uint32_t time_limit;
   const uint32_t *dur32, *xfer32, *slice_begin32, *slice_end32, *release32;
   // Per-op fields of the 32-bit path, field-major [kOpMetaFields][meta_stride]
   // so a wave reads the fields of 64 consecutive ops with one coalesced load
@@ -174,6 +181,10 @@ struct ss_state {
 int ss_set_error(int code, const std::string &msg);
 void ss_clear_error();
 
+// Verdict byte of a candidate that a 32-bit pass left to the int64 kernels
+// (never seen by a caller).
+#define SS_VIOLATION_RETRY 0x80
+
 // Optional per-kernel event timing (abi.cpp): returns a started record or
 // nullptr when timing is off; ss_timing_stop closes it on the same stream.
 struct SsTimingRec;
@@ -217,6 +228,13 @@ int ss_simulate_time_bits_of(const ss_gmg *g, bool ready_dispatch, bool link_por
 int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,
                     int64_t *slack, int64_t *sumfin, hipStream_t stream, bool ready_dispatch, bool link_ports,
                     SsWork &W);
+// The candidates marked SS_VIOLATION_RETRY of a chunk of nb (placement rows P),
+// simulated by the general index-order kernels with `slots` workgroups of the
+// memory pass.
+size_t ss_retry_scratch(const ss_gmg *g, int64_t nb, int64_t slots);
+int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, void *scratch, int64_t slots, int cus,
+                 int64_t *makespan,
+                 int64_t *peak, uint8_t *violation, int64_t *slack, int64_t *sumfin, hipStream_t stream);
 // Resumption from a captured state (general schedule kernel; the 32-bit
 // memory passes when the GMG has a 32-bit horizon); from may be null or empty.
 int ss_run_simulate_resume(const ss_gmg *g, const ss_state *from, const uint8_t *placements, int64_t B,

@@ -97,3 +97,42 @@ def test_times_past_2_31_with_short_slices(dispatch):
     g = synth.make_gmg(2, ["op"] * n, [(0, 1), (1, 2), (2, 3), (3, 4)], [0] * n, [[820_000_000]] * n, [100] * n,
                        [[(0, 40), (90, synth.TIME_INF)], [(7, synth.TIME_INF)]], [150, 1000], [0], [1 << 40])
     check(g, np.array([[0] * n, [1] * n, [0, 1, 0, 1, 0], [0, 0, 1, 1, 1]], np.uint8), dispatch=dispatch)
+
+
+@pytest.mark.parametrize("outdeg,n_class", [(2, 1), (None, 2)])
+@pytest.mark.parametrize("ahead", [0.2, 0.55, 0.9, 1.0])
+def test_horizon_past_32_bits(ahead, outdeg, n_class):
+    """Idle windows beyond 2^32 us: candidates whose times stay below the
+    32-bit limit, pass it at the last ops, or pass it everywhere (`ahead` of
+    the devices' short windows end near 2^32), alone and mixed in a batch."""
+    n, D = 150, 4
+    print(f"windows up to {ahead} of 2^32", flush=True)
+    g = synth.random_gmg(8, n_ops=n, n_dev=D, n_req=3, n_class=n_class, n_link=2, max_outdeg=outdeg, edge_p=0.2,
+                         open_only=True, cap_scale=9000)
+    rng = np.random.default_rng(int(ahead * 100))
+    begin, end, ptr = [], [], [0]
+    for d in range(D):  # windows that hold a few ops each, then a gap, up to well past 2^32
+        t = 10 * d
+        step = max(200, int(ahead * (1 << 32) / 40)) if d % 2 else 200
+        while t < 3 << 31:
+            w = int(rng.integers(40, 120))
+            begin.append(t)
+            end.append(t + w)
+            t += w + step + int(rng.integers(0, 50))
+            if len(begin) - ptr[-1] > 60:
+                step = 1 << 30
+        begin.append(t)
+        end.append(synth.TIME_INF)
+        ptr.append(len(begin))
+    g.slice_ptr, g.slice_begin, g.slice_end = (np.array(x, np.int64) for x in (ptr, begin, end))
+    P = rng.integers(0, D, (61, n)).astype(np.uint8)
+    P[::3] = P[::3] // 2 * 2  # only devices with windows close together
+    P[5] = 0
+    P[6] = 1
+    P[7, -1] = D
+    h = ss.Gmg(g)
+    assert ss.time_bits(h) == 64
+    ref = oracle.simulate_batch(g, P, n_threads=8)
+    late = ref["makespan"] >= 1 << 32
+    print(f"{int(late.sum())} of {len(P)} candidates pass 2^32", flush=True)
+    check(g, P)
