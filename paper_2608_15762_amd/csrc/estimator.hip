@@ -7,10 +7,22 @@
 //                 samples per estimator): its lanes stride over the estimator's
 //                 samples (grouped by estimator), sum in registers, and reduce
 //                 across the group in a fixed order (results do not depend on
-//                 scheduling), then add to the state.
+//                 scheduling), then add to the state.  Bound: HBM, once the
+//                 reduction is cheap: 20 sums of 64 lanes through LDS shuffles
+//                 cost more than reading the samples, so a group is at most
+//                 16 lanes (a DPP row: rotations on the VALU) while that
+//                 fills the chip (8,388,608 samples of 65,536 five-feature
+//                 estimators, 435.7 MB: 189 us with groups of 64, 120 us with
+//                 16, 3.6 TB/s).
 // est_solve       one lane per estimator: Cholesky factorisation of the Gram
-//                 matrix and two triangular solves for the coefficients.
-// est_predict     one lane per query: integer microseconds for the simulator.
+//                 matrix and two triangular solves for the coefficients, all
+//                 in registers, a wave to a block.  Bound: latency of the
+//                 strided loads and of the divisions and roots in turn (the
+//                 same estimators: 21 us with indexed arrays, 6.3 us).
+// est_predict     one lane per query: integer microseconds for the simulator;
+//                 a query's features and coefficients in flight together.
+//                 Bound: the gathered coefficients' lines (1,048,576 queries
+//                 40 us with one feature after the other, 23 us).
 #include <climits>
 #include <cmath>
 
@@ -27,6 +39,30 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr double kPivotRtol = 1e-12;  // relative pivot below which a Gram matrix is singular
+
+// Sum of v over each aligned group of kL lanes, in every lane of the group.
+// Within a row of 16 lanes by rotation (a DPP move on the VALU), beyond that
+// through the LDS permute network.
+template <int kCtrl>
+__device__ __forceinline__ double row_move(double v) {
+  const uint64_t x = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kCtrl, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), kCtrl, 0xF, 0xF, false);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+template <int kL>
+__device__ __forceinline__ double group_sum(double v) {
+  // quad_perm {1,0,3,2} and {2,3,0,1}; row_half_mirror and row_mirror, whose
+  // partners hold the other half's sum; then across rows
+  if (kL >= 2) v += row_move<0xB1>(v);
+  if (kL >= 4) v += row_move<0x4E>(v);
+  if (kL >= 8) v += row_move<0x141>(v);
+  if (kL >= 16) v += row_move<0x140>(v);
+  if (kL >= 32) v += __shfl_xor(v, 16, kWave);
+  if (kL >= 64) v += __shfl_xor(v, 32, kWave);
+  return v;
+}
 
 // kL lanes per estimator (a power of two dividing 64): each wave serves
 // 64 / kL estimators, lane t of a group takes samples t, t + kL, ...; the
@@ -62,21 +98,16 @@ __global__ __launch_bounds__(kWave) void est_accumulate(int64_t n_est, const int
       for (int j = i; j < F; ++j, ++k) g[k] = fma(v[i], v[j], g[k]);
     }
   }
-  auto group_sum = [&](double v) {
-#pragma unroll
-    for (int o = kL / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-  };
   double *ge = gram + ec * F * F, *me = mom + ec * F;
   const bool writer = live && t == 0;
   int k = 0;
 #pragma unroll
   for (int i = 0; i < F; ++i) {
-    const double mi = group_sum(m[i]);
+    const double mi = group_sum<kL>(m[i]);
     if (writer) me[i] += mi;
 #pragma unroll
     for (int j = i; j < F; ++j, ++k) {
-      const double gij = group_sum(g[k]);
+      const double gij = group_sum<kL>(g[k]);
       if (writer) {
         ge[i * F + j] += gij;
         if (j != i) ge[j * F + i] += gij;
@@ -87,46 +118,57 @@ __global__ __launch_bounds__(kWave) void est_accumulate(int64_t n_est, const int
 }
 
 template <int F>
-__global__ __launch_bounds__(256) void est_solve(int64_t n_est, const double *__restrict__ gram,
-                                                 const double *__restrict__ mom, const int64_t *__restrict__ count,
-                                                 double *__restrict__ coef, int32_t *__restrict__ status) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kWave) void est_solve(int64_t n_est, const double *__restrict__ gram,
+                                                   const double *__restrict__ mom, const int64_t *__restrict__ count,
+                                                   double *__restrict__ coef, int32_t *__restrict__ status) {
+  const int64_t e = (int64_t)blockIdx.x * kWave + threadIdx.x;
   if (e >= n_est) return;
   double L[F][F], z[F], beta[F];
   const double *a = gram + e * F * F, *b = mom + e * F;
-  int st = SS_EST_FITTED;
-  if (count[e] < F) st = SS_EST_UNDERDETERMINED;
-  for (int j = 0; j < F && st == SS_EST_FITTED; ++j) {
-    double d = a[j * F + j];
+#pragma unroll
+  for (int i = 0; i < F; ++i) {
+    z[i] = b[i];
+#pragma unroll
+    for (int j = 0; j <= i; ++j) L[i][j] = a[i * F + j];
+  }
+  int st = count[e] < F ? SS_EST_UNDERDETERMINED : SS_EST_FITTED;
+#pragma unroll
+  for (int j = 0; j < F; ++j) {
+    const double ajj = L[j][j];
+    double d = ajj;
+#pragma unroll
     for (int k = 0; k < j; ++k) d -= L[j][k] * L[j][k];
-    if (!(d > kPivotRtol * fabs(a[j * F + j])) || a[j * F + j] <= 0.0) {
-      st = SS_EST_SINGULAR;
-      break;
-    }
-    L[j][j] = sqrt(d);
+    if (st == SS_EST_FITTED && (!(d > kPivotRtol * fabs(ajj)) || ajj <= 0.0)) st = SS_EST_SINGULAR;
+    L[j][j] = sqrt(d);  // (what follows a refused pivot is not used)
+#pragma unroll
     for (int i = j + 1; i < F; ++i) {
-      double s = a[i * F + j];
+      double s = L[i][j];
+#pragma unroll
       for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
       L[i][j] = s / L[j][j];
     }
   }
-  if (st == SS_EST_FITTED) {
-    for (int i = 0; i < F; ++i) {  // L z = mom
-      double s = b[i];
-      for (int k = 0; k < i; ++k) s -= L[i][k] * z[k];
-      z[i] = s / L[i][i];
-    }
-    for (int i = F - 1; i >= 0; --i) {  // L^T beta = z
-      double s = z[i];
-      for (int k = i + 1; k < F; ++k) s -= L[k][i] * beta[k];
-      beta[i] = s / L[i][i];
-    }
+#pragma unroll
+  for (int i = 0; i < F; ++i) {  // L z = mom
+    double s = z[i];
+#pragma unroll
+    for (int k = 0; k < i; ++k) s -= L[i][k] * z[k];
+    z[i] = s / L[i][i];
   }
+#pragma unroll
+  for (int i = F - 1; i >= 0; --i) {  // L^T beta = z
+    double s = z[i];
+#pragma unroll
+    for (int k = i + 1; k < F; ++k) s -= L[k][i] * beta[k];
+    beta[i] = s / L[i][i];
+  }
+#pragma unroll
   for (int i = 0; i < F; ++i) coef[e * F + i] = st == SS_EST_FITTED ? beta[i] : 0.0;
   status[e] = st;
 }
 
-__global__ __launch_bounds__(256) void est_predict(const double *__restrict__ coef, int64_t n_est, int F,
+template <int F>
+__global__ __launch_bounds__(256) void est_predict(const double *__restrict__ coef, int64_t n_est,
                                                    const int32_t *__restrict__ est_of, const double *__restrict__ x,
                                                    int64_t M, int64_t *__restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -136,12 +178,19 @@ __global__ __launch_bounds__(256) void est_predict(const double *__restrict__ co
     out[i] = 0;  // unknown estimator
     return;
   }
+  double v[F], c[F];
+#pragma unroll
+  for (int j = 0; j < F; ++j) {
+    v[j] = x[i * F + j];
+    c[j] = coef[(int64_t)e * F + j];
+  }
   // products and sums rounded one by one, in feature order (no fused
   // multiply-add): the integer decision below is then reproducible bit for bit
   double t = 0.0;
-  for (int j = 0; j < F; ++j) t = __dadd_rn(t, __dmul_rn(x[i * F + j], coef[(int64_t)e * F + j]));
-  const double c = ceil(t);
-  out[i] = !(c < 4.611686018427388e18) ? 0 : c < 1.0 ? 1 : (int64_t)c;  // not finite or >= 2^62: 0
+#pragma unroll
+  for (int j = 0; j < F; ++j) t = __dadd_rn(t, __dmul_rn(v[j], c[j]));
+  const double r = ceil(t);
+  out[i] = !(r < 4.611686018427388e18) ? 0 : r < 1.0 ? 1 : (int64_t)r;  // not finite or >= 2^62: 0
 }
 
 int hip_fail(hipError_t err, const char *what) {
@@ -158,14 +207,15 @@ void launch_group(const ss_est *E, const int64_t *ptr, int64_t S, const double *
 }
 
 // Lanes per estimator from the average samples per estimator of the batch
-// (4 .. 64), so that most lanes have a sample.
+// (4 .. 16, so that most lanes have a sample); 32 and 64 only for batches of
+// fewer estimators, whose groups of 16 would leave the chip's waves idle.
 template <int F>
 void launch_accumulate(const ss_est *E, const int64_t *ptr, int64_t S, const double *x, const double *y,
                        hipStream_t stream) {
   const int64_t avg = S / E->n_est;
-  if (avg >= 48)
+  if (avg >= 48 && E->n_est < 2048)
     launch_group<F, 64>(E, ptr, S, x, y, stream);
-  else if (avg >= 24)
+  else if (avg >= 24 && E->n_est < 4096)
     launch_group<F, 32>(E, ptr, S, x, y, stream);
   else if (avg >= 12)
     launch_group<F, 16>(E, ptr, S, x, y, stream);
@@ -177,8 +227,15 @@ void launch_accumulate(const ss_est *E, const int64_t *ptr, int64_t S, const dou
 
 template <int F>
 void launch_solve(const ss_est *E, double *coef, int32_t *status, hipStream_t stream) {
-  hipLaunchKernelGGL(est_solve<F>, dim3((unsigned)((E->n_est + 255) / 256)), dim3(256), 0, stream, E->n_est, E->gram,
+  hipLaunchKernelGGL(est_solve<F>, dim3((unsigned)((E->n_est + kWave - 1) / kWave)), dim3(kWave), 0, stream, E->n_est, E->gram,
                      E->mom, E->count, coef, status);
+}
+
+template <int F>
+void launch_predict(const double *coef, int64_t n_est, const int32_t *est_of, const double *x, int64_t M,
+                    int64_t *out, hipStream_t stream) {
+  hipLaunchKernelGGL(est_predict<F>, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, stream, coef, n_est, est_of, x,
+                     M, out);
 }
 
 }  // namespace
@@ -252,9 +309,11 @@ int ss_run_est_solve(const ss_est *E, double *coef, int32_t *status, hipStream_t
 int ss_run_est_predict(const double *coef, int64_t n_est, int64_t n_feat, const int32_t *est_of, const double *x,
                        int64_t M, int64_t *out, hipStream_t stream) {
   if (M == 0) return SS_OK;
+  using L = void (*)(const double *, int64_t, const int32_t *, const double *, int64_t, int64_t *, hipStream_t);
+  static const L table[SS_EST_MAX_FEAT] = {launch_predict<1>, launch_predict<2>, launch_predict<3>, launch_predict<4>,
+                                           launch_predict<5>, launch_predict<6>, launch_predict<7>, launch_predict<8>};
   SsTimingRec *t = ss_timing_start(SS_KERNEL_ESTIMATOR, stream);
-  hipLaunchKernelGGL(est_predict, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, stream, coef, n_est, (int)n_feat,
-                     est_of, x, M, out);
+  table[n_feat - 1](coef, n_est, est_of, x, M, out, stream);
   ss_timing_stop(t, stream);
   const hipError_t err = hipGetLastError();
   return err == hipSuccess ? SS_OK : hip_fail(err, "est_predict launch");
