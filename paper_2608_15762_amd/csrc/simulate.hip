@@ -1568,6 +1568,8 @@ int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak
   bool generic = false, ports_mem_fast = false;
   const int route = simulate_route(g, ready_dispatch, link_ports, &generic, &ports_mem_fast);
   if (route != SS_OK) return route;
+  if (ports_mem_fast && ss_ports32_ok(g))
+    return ss_run_simulate_ports32(g, P, makespan, peak, violation, slack, sumfin, stream, W);
   if (generic)
     return run_simulate_generic(g, P, makespan, peak, violation, slack, sumfin, stream, ready_dispatch, link_ports, W,
                                 nullptr, nullptr, ports_mem_fast && !W.ptr && !W.query);

@@ -254,6 +254,10 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
 size_t ss_fast_schedule_lds(const ss_gmg *g);
 int ss_run_simulate_fast(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,
                          int64_t *slack, int64_t *sumfin, hipStream_t stream, SsWork &W);
+// Transfer ports on 32-bit times (ports.hip): whether a GMG takes it, and the call.
+bool ss_ports32_ok(const ss_gmg *g);
+int ss_run_simulate_ports32(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,
+                            int64_t *slack, int64_t *sumfin, hipStream_t stream, SsWork &W);
 // Ready-time dispatch on the fast path (sim_fast.hip).
 size_t ss_ready_schedule_lds(const ss_gmg *g);
 int ss_run_simulate_ready(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,

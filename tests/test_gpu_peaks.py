@@ -136,3 +136,28 @@ def test_horizon_past_32_bits(ahead, outdeg, n_class):
     late = ref["makespan"] >= 1 << 32
     print(f"{int(late.sum())} of {len(P)} candidates pass 2^32", flush=True)
     check(g, P)
+
+
+@pytest.mark.parametrize("D,fan", [(3, 127), (40, 130), (255, 600), (64, 2000)])
+def test_many_pending_transfers(D, fan):
+    """Producers of equal length on all devices but one, each with a consumer
+    on device 0 whose receive port takes the transfers one by one: more than
+    the 128 pending transfers held in LDS, every input count up to five."""
+    rng = np.random.default_rng(fan)
+    n = fan + fan // 3
+    edges, at = [], 0
+    for v in range(fan, n):
+        for u in range(at, min(fan, at + 1 + v % 5)):
+            edges.append((u, v))
+        at += 1 + v % 5
+    g = synth.make_gmg(D, ["op"] * n, edges, rng.integers(0, 3, n), [[3]] * fan + [[int(x)] for x in rng.integers(1, 9, n - fan)],
+                       rng.integers(0, 900, n), [[(int(rng.integers(0, 2)), synth.TIME_INF)] for _ in range(D)],
+                       [20_000] * D, [0, 2, 9], [5_000, 9_000, 0], link_class=rng.integers(0, 2, (D, D)).astype(np.uint8),
+                       bw=(40, 9), lat=(0, 2))
+    P = np.zeros((23, n), np.uint8)
+    for c in range(23):
+        P[c, :fan] = 1 + (np.arange(fan) * (c + 1)) % (D - 1)
+        P[c, fan:] = rng.integers(0, 2 if c % 2 else 1, n - fan)
+    P[4, 3] = D if D < 255 else 255  # names an unknown device
+    check(g, P, links="ports")
+    check(g, P)
