@@ -454,7 +454,8 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
         time_limit = (uint32_t)limit;
     }
     const bool tab32 = time32 || time_limit > 0;
-    std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe, lutk, lutw;
+    std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe, lutk, lutw, rrec;
+    int64_t rwidth = 0;
     std::vector<uint8_t> lgrp;
     // ready-time dispatch: the ops without predecessors by (release of their
     // request, index); on the 32-bit path also as keys release << 16 | op
@@ -518,6 +519,40 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
               const uint32_t pe = (uint32_t)succ_pe[succ_ptr[v] + q];
               succ2_pe[v] = q == 0 ? (0xFFFF0000u | pe) : ((succ2_pe[v] & 0xFFFFu) | pe << 16);
             }
+        }
+      }
+      // records of the ready-time lanes, and how many ops wait ready at once
+      // when ops run in index order
+      int64_t max_in = 0;
+      for (int64_t v = 0; v < N; ++v) max_in = std::max<int64_t>(max_in, d->pred_ptr[v + 1] - d->pred_ptr[v]);
+      if (time32 && K <= 2 && max_in <= 2 && max_outdeg <= 2) {
+        rrec.assign((size_t)N * 12, 0u);
+        for (int64_t v = 0; v < N; ++v) {
+          uint32_t *q = &rrec[(size_t)v * 12], other[2] = {0xFFFFu, 0xFFFFu};
+          q[0] = C == 1 ? (uint32_t)d->dur[v] : 0u;
+          q[1] = (uint32_t)xfer[v * K];
+          q[2] = (uint32_t)xfer[v * K + K - 1];
+          q[3] = succ2[v];
+          for (int64_t i = 0; i < outdeg[v]; ++i) {
+            const int64_t x = succ_idx[succ_ptr[v] + i], e0 = d->pred_ptr[x];
+            if (d->pred_ptr[x + 1] - e0 == 2) {
+              const int64_t u = d->pred_idx[e0] == v ? d->pred_idx[e0 + 1] : d->pred_idx[e0];
+              other[i] = (uint32_t)u;
+              q[8 + 2 * i] = (uint32_t)xfer[u * K];
+              q[9 + 2 * i] = (uint32_t)xfer[u * K + K - 1];
+            }
+            q[5 + i] = (uint32_t)d->release[d->op_req[x]];
+          }
+          q[4] = other[0] | other[1] << 16;
+          q[7] = (uint32_t)d->op_req[v];
+        }
+        std::vector<int32_t> left(N);
+        int64_t open = 0;
+        for (int64_t v = 0; v < N; ++v) left[v] = (int32_t)(d->pred_ptr[v + 1] - d->pred_ptr[v]);
+        for (int64_t v = 0; v < N; ++v) {
+          if (d->pred_ptr[v + 1] > d->pred_ptr[v]) --open;  // was ready, sources aside
+          for (int32_t q = succ_ptr[v]; q < succ_ptr[v + 1]; ++q)
+            if (--left[succ_idx[q]] == 0) rwidth = std::max(rwidth, ++open);
         }
       }
       if (K <= 2) {
@@ -622,7 +657,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     const size_t o_dur32 = pk.add(dur32), o_xfer32 = pk.add(xfer32), o_sb32 = pk.add(sb32), o_se32 = pk.add(se32),
                  o_rel32 = pk.add(rel32), o_meta = pk.add(meta), o_lbits = pk.add(lbits), o_b32 = pk.add(bytes32),
                  o_succ2 = pk.add(succ2), o_succ2_pe = pk.add(succ2_pe), o_lutk = pk.add(lutk), o_lutw = pk.add(lutw), o_lgrp = pk.add(lgrp),
-                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops);
+                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops), o_rrec = pk.add(rrec);
     pk.add(nullptr, 256);  // tail padding
 
     ss_gmg *g = new ss_gmg();
@@ -695,6 +730,8 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     V.src_keys = reinterpret_cast<const uint64_t *>(base + o_src);
     V.src_ops = reinterpret_cast<const int32_t *>(base + o_src_ops);
     V.n_src = (int32_t)src_ops.size();
+    V.ready_rec = rrec.empty() ? nullptr : reinterpret_cast<const uint4 *>(base + o_rrec);
+    V.ready_width = (int32_t)rwidth;
     V.link_same = lsame;
     V.link_shift = lshift;
     V.lut_k = reinterpret_cast<const uint32_t *>(base + o_lutk);

@@ -50,10 +50,14 @@
 // of resident waves, and waves placed late behind another kernel's would add
 // a second round.
 // Ready-time dispatch (the rule of Sec. 3.3.2), per chunk:
-//   ready_schedule one wave per candidate, the ready set in registers (a
-//                 spill list beyond), finish times in candidate rows and each
-//                 op's rank in dispatch order; then fast_intervals with those
-//                 ranks and fast_peaks as above.
+//   ready_ops     one lane per candidate, state op-major, for graphs of at
+//                 most two successors and predecessors per op; ready_lanes
+//                 (candidate rows) for others
+//   ready_schedule one wave per candidate, for candidates whose ready set
+//                 outgrows a lane's slots: the ready set in registers (a
+//                 spill list beyond)
+// each with finish times in candidate rows and each op's rank in dispatch
+// order; then the memory pass as above with those ranks.
 #include <atomic>
 #include <climits>
 #include <cstdlib>
@@ -933,6 +937,195 @@ __global__ __launch_bounds__(kWave) void ready_lanes(const GmgView G, const uint
   violation[c] = 0;
   if (slack)
     for (int r = 0; r < R; ++r) slack[c * R + r] = G.deadline[r] - (int64_t)comp[r * kWave + lane];
+}
+
+// The same rule, one lane per candidate, for graphs of at most two successors
+// and two predecessors per op, with the candidates' state op-major: placements
+// PT [op][pitch], finish times and ranks [op][candidate], transposed to rows
+// afterwards.  The lanes of a wave walk nearly the same ops at nearly the same
+// steps (all of them when candidates differ from a partition by a few moves),
+// so a step touches a few rows of 64 neighbours where rows per candidate
+// touch 64 lines for every access.  A step has two levels of dependent loads:
+// the op's record (ready_rec), then its successors' devices, their other
+// inputs' finishes and devices, and the idle slices.  A key holds ready << 24 |
+// op << 8 | device; ranks count in LDS beside the clocks.  kSlots keys per
+// lane, from the width the loader measured; candidates that need more are
+// redone by ready_schedule.
+// Bound: the two levels' latency and the lines they touch where candidates'
+// idle windows drive their orders apart (half the time is left when one wave
+// runs alone).  65,536 candidates of 10,000 ops with up to 8 moved: ready_lanes
+// 63.8 ms, this 26.2 ms and 3.3 ms of fill and transposes; 27,979 of 104 ops
+// at random 4.9 and 0.64 ms the whole call.
+template <int kSlots, bool kOneClass, bool kShift>
+__global__ __launch_bounds__(kWave) void ready_ops(const GmgView G, const uint8_t *__restrict__ PT, int64_t ppitch,
+                                                   int64_t nb, uint32_t *__restrict__ finT,
+                                                   uint16_t *__restrict__ rankT, uint32_t *__restrict__ ovf,
+                                                   int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
+                                                   int64_t *__restrict__ slack, uint8_t *__restrict__ violation) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = G.n_class;
+  uint32_t *clk = reinterpret_cast<uint32_t *>(lds_raw);                      // [D][64]
+  uint32_t *comp = clk + (size_t)D * kWave;                                   // [R][64]
+  uint16_t *cnt = reinterpret_cast<uint16_t *>(comp + (size_t)R * kWave);     // [D][64]
+  const int lane = threadIdx.x;
+  for (int d = 0; d < D; ++d) {
+    clk[d * kWave + lane] = 0;
+    cnt[d * kWave + lane] = 0;
+  }
+  for (int r = 0; r < R; ++r) comp[r * kWave + lane] = G.release32[r];
+  // a lane past the batch end shadows the last candidate, storing what its lane stores
+  const int64_t c_raw = (int64_t)blockIdx.x * kWave + lane;
+  const bool live = c_raw < nb;
+  const int64_t c = live ? c_raw : nb - 1;
+  const uint8_t *const Pc = PT + c;
+  uint32_t *const fc = finT + c;
+  uint16_t *const rc = rankT + c;
+  const uint64_t ppu = (uint64_t)ppitch, nbu = (uint64_t)nb;
+  const uint4 *const recs = G.ready_rec;
+  constexpr uint64_t kNone = ~0ull;
+  uint64_t slot[kSlots];
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) slot[k] = kNone;
+  bool bad = false, over = false;
+  auto device = [&](uint32_t raw) -> uint32_t {  // an unknown device: walked on device 0, reported invalid
+    bad |= raw >= (uint32_t)D;
+    return raw >= (uint32_t)D ? 0u : raw;
+  };
+  auto cls = [&](uint32_t a, uint32_t b) -> uint32_t {
+    if (!kShift) return link_bit(G, a, b);
+    const uint32_t s = (uint32_t)G.link_shift, same = (uint32_t)G.link_same;
+    return (a >> s) == (b >> s) ? same : 1u - same;
+  };
+  auto source = [&](int i) -> uint64_t {
+    if (i >= G.n_src) return kNone;
+    const uint64_t k = G.src_keys[i];
+    return k << 8 | device(Pc[(k & 0xFFFFu) * ppu]);
+  };
+  int sp = 0;
+  uint64_t sk = source(0);  // the next source's key, loaded a step ahead
+  uint32_t ms = 0;
+  uint64_t sum = 0;
+  for (int step = 0; step < N; ++step) {
+    uint64_t my = slot[0];
+#pragma unroll
+    for (int k = 1; k < kSlots; ++k) my = slot[k] < my ? slot[k] : my;
+    const bool from_src = sk < my;
+    const uint64_t key = from_src ? sk : my;
+    if (key == kNone) {  // nothing ready before every op ran: only after a lost key
+      over = true;
+      break;
+    }
+    if (from_src) sk = source(++sp);
+    const uint32_t d = (uint32_t)key & 0xFFu, v = (uint32_t)(key >> 8) & 0xFFFFu, ready = (uint32_t)(key >> 24);
+    const uint4 r0 = recs[3 * v], r1 = recs[3 * v + 1];
+    const uint32_t w = kOneClass ? r0.x : G.dur32[(int64_t)v * C + G.dev_class[d]];
+    uint32_t s = umax32(ready, clk[d * kWave + lane]);
+    const uint32_t e = d * (uint32_t)G.lut_nb + lut_bucket(G, s + w);
+    const uint4 lw = G.lut_w[e];
+    // the successors' devices and other inputs; lanes without one read op 0's
+    // row, a line they share
+    const uint32_t x0 = r0.w & 0xFFFFu, x1 = r0.w >> 16, o0 = r1.x & 0xFFFFu, o1 = r1.x >> 16;
+    const bool has0 = x0 != 0xFFFFu, has1 = x1 != 0xFFFFu, two0 = o0 != 0xFFFFu, two1 = o1 != 0xFFFFu;
+    const uint32_t y0 = has0 ? x0 : 0u, y1 = has1 ? x1 : 0u, u0 = two0 ? o0 : 0u, u1 = two1 ? o1 : 0u;
+    const uint32_t px0 = Pc[y0 * ppu], px1 = Pc[y1 * ppu], pu0 = Pc[u0 * ppu], pu1 = Pc[u1 * ppu];
+    const uint32_t fu0 = fc[u0 * nbu], fu1 = fc[u1 * nbu];
+    const uint4 r2 = recs[two0 || two1 ? 3 * v + 2 : 0u];  // the other inputs' transfer times
+    {  // the first idle slice that holds [s', s' + w) with s' >= s
+      const uint32_t t0 = umax32(s, lw.x), t1 = umax32(s, lw.z);
+      if (t0 + w <= lw.y) {
+        s = t0;
+      } else if (t1 + w <= lw.w) {
+        s = t1;
+      } else {
+        const int sb = G.slice_ptr[d];
+        for (int k = (int)G.lut_k[e] + 2;; ++k) {
+          const uint32_t t = umax32(s, G.slice_begin32[sb + k]);
+          if (t + w <= G.slice_end32[sb + k]) {
+            s = t;
+            break;
+          }
+        }
+      }
+    }
+    const uint32_t f = s + w;
+    clk[d * kWave + lane] = f;
+    const uint16_t rk = cnt[d * kWave + lane];
+    cnt[d * kWave + lane] = (uint16_t)(rk + 1);
+    fc[v * nbu] = f;
+    rc[v * nbu] = rk;
+    uint32_t *cr = comp + r1.w * kWave + lane;
+    *cr = umax32(*cr, f);
+    ms = umax32(ms, f);
+    sum += f;
+    // successors whose last unset predecessor this was become ready
+    auto next = [&](bool has, uint32_t x, uint32_t px, bool two, uint32_t fu, uint32_t pu, uint32_t xa, uint32_t xb,
+                    uint32_t rel) -> uint64_t {
+      const uint32_t dx = px >= (uint32_t)D ? 0u : px, du = pu >= (uint32_t)D ? 0u : pu;
+      uint32_t rx = umax32(rel, f + (d != dx ? (cls(d, dx) ? r0.z : r0.y) : 0u));
+      const uint32_t t = fu + (du != dx ? (cls(du, dx) ? xb : xa) : 0u);
+      rx = two ? umax32(rx, t) : rx;
+      const bool ok = has && (!two || fu != kFinUnset);
+      bad |= ok && px >= (uint32_t)D;
+      return ok ? (uint64_t)rx << 24 | x << 8 | dx : kNone;
+    };
+    const uint64_t n0 = next(has0, x0, px0, two0, fu0, pu0, r2.x, r2.y, r1.y);
+    const uint64_t n1 = next(has1, x1, px1, two1, fu1, pu1, r2.z, r2.w, r1.z);
+    // the first takes the slot of the op that ran (a source has none); what
+    // is left, seldom anything in any lane, looks for a free one
+    const uint64_t first = n0 != kNone ? n0 : n1, second = n0 != kNone ? n1 : kNone;
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) slot[k] = slot[k] == key ? first : slot[k];
+    auto insert = [&](uint64_t nk) {
+      if (!__any(nk != kNone)) return;
+      bool placed = nk == kNone;
+#pragma unroll
+      for (int k = 0; k < kSlots; ++k) {
+        const bool here = !placed && slot[k] == kNone;
+        slot[k] = here ? nk : slot[k];
+        placed |= here;
+      }
+      over |= !placed;
+    };
+    insert(from_src ? first : second);
+    insert(from_src ? second : kNone);
+    if (over) break;
+  }
+  if (!live) return;
+  ovf[c] = over ? 1u : 0u;
+  if (over) return;  // ready_schedule writes this candidate's outputs
+  if (bad) {
+    makespan[c] = INT64_MAX;
+    if (sumfin) sumfin[c] = INT64_MAX;
+    if (slack)
+      for (int r = 0; r < R; ++r) slack[c * R + r] = INT64_MIN;
+    violation[c] = SS_VIOLATION_INVALID;
+    return;
+  }
+  makespan[c] = ms;
+  if (sumfin) sumfin[c] = (int64_t)sum;
+  violation[c] = 0;
+  if (slack)
+    for (int r = 0; r < R; ++r) slack[c * R + r] = G.deadline[r] - (int64_t)comp[r * kWave + lane];
+}
+
+size_t ready_ops_lds(int64_t D, int64_t R) { return (size_t)(D + R) * kWave * 4 + (size_t)D * kWave * 2; }
+
+template <int kSlots>
+const void *ready_ops_fn(bool one_class, bool shift) {
+  if (one_class)
+    return shift ? reinterpret_cast<const void *>(&ready_ops<kSlots, true, true>)
+                 : reinterpret_cast<const void *>(&ready_ops<kSlots, true, false>);
+  return shift ? reinterpret_cast<const void *>(&ready_ops<kSlots, false, true>)
+               : reinterpret_cast<const void *>(&ready_ops<kSlots, false, false>);
+}
+
+// Fills n words with x.
+__global__ __launch_bounds__(256) void fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t x) {
+  uint4 *q = reinterpret_cast<uint4 *>(p);
+  const int64_t n4 = n / 4;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256)
+    q[i] = make_uint4(x, x, x, x);
+  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) p[4 * n4 + threadIdx.x] = x;
 }
 
 // ------------------------------------------------------------------ memory
@@ -2073,6 +2266,17 @@ hipError_t ss_rows_from_op_major(const uint8_t *P, int64_t n_ops, int64_t B, int
   return hipGetLastError();
 }
 
+// Candidates' placement rows [nb][N] -> op-major [N][nb].
+static void placements_to_op_major(const uint8_t *P, int64_t nb, int64_t N, uint8_t *PT, hipStream_t stream) {
+  if (N % 4 == 0 && nb % 4 == 0 && (reinterpret_cast<uintptr_t>(P) & 3) == 0) {
+    const dim3 tg((unsigned)((N + 127) / 128), (unsigned)((nb + 127) / 128));
+    hipLaunchKernelGGL(transpose_u8_words, tg, dim3(256), 0, stream, P, nb, N, N, PT);
+  } else {
+    const dim3 tg((unsigned)((N + 63) / 64), (unsigned)((nb + 63) / 64));
+    hipLaunchKernelGGL(transpose_tiles<uint8_t>, tg, dim3(256), 0, stream, P, nb, N, N, PT);
+  }
+}
+
 int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_t *peak, uint8_t *violation,
                          int64_t *slack, int64_t *sumfin, hipStream_t stream, SsWork &W) {
   const GmgView &G = g->view;
@@ -2280,16 +2484,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       if (te != hipSuccess && rc == SS_OK) rc = hip_fail(te, "transpose launch");
     } else {
       Pc = src.p + b0 * N;
-      if (N > 0) {  // candidates' placement rows -> op-major [op][candidate]
-        if (N % 4 == 0 && nb % 4 == 0 && (reinterpret_cast<uintptr_t>(Pc) & 3) == 0) {
-          const dim3 tg((unsigned)((N + 127) / 128), (unsigned)((nb + 127) / 128));
-          hipLaunchKernelGGL(transpose_u8_words, tg, dim3(256), 0, stream, Pc, nb, (int64_t)N, (int64_t)N, PT);
-        } else {
-          const dim3 tg((unsigned)((N + 63) / 64), (unsigned)((nb + 63) / 64));
-          hipLaunchKernelGGL(transpose_tiles<uint8_t>, tg, dim3(256), 0, stream, Pc, nb, (int64_t)N, (int64_t)N,
-                             PT);
-        }
-      }
+      if (N > 0) placements_to_op_major(Pc, nb, N, PT, stream);
     }
     ss_timing_stop(tp, stream);
     if (!check("transpose launch")) break;
@@ -2370,6 +2565,9 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   const bool lanes_env = !(rmode && std::strcmp(rmode, "wave") == 0);
   const size_t lane_lds = (size_t)(D + R) * kWave * 4;
   const bool lanes = lanes_env && lane_lds <= (size_t)lds_blk;  // else one wave per candidate throughout
+  // op-major lanes when the loader made their records; their arrays (7 bytes
+  // per op and candidate) lie where ready_schedule's spill lists go afterwards
+  const bool ops = lanes && G.ready_rec && ready_ops_lds(D, R) <= (size_t)lds_blk;
   struct Plan {
     int64_t chunk, sub, nslots, n_ticket;
     size_t sz_fin, sz_rank, sz_miss, sz_spill, sz_rows, sz_own, sz_cp, sz_meta, sz_wk, sz_wb, sz_tk, sz_lane, sz_slots, total;
@@ -2384,7 +2582,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
     q.sz_rank = align(((size_t)chunk * N + 1) * 2);
     q.sz_miss = align(((size_t)chunk * N + 1) * 2);
-    q.sz_spill = align((size_t)chunk * N * 8 + 8);
+    q.sz_spill = align((size_t)chunk * N * 8 + 1024);
     q.sz_rows = src.op_major ? align((size_t)chunk * N + 1) : 0;
     q.sz_lane = lanes ? align((size_t)chunk * D * 2) + align((size_t)chunk * 4) : 0;
     if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
@@ -2415,7 +2613,9 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   // the call can get now: sub-chunks shrink first (down to a sixteenth of the
   // chunk), then the chunk halves.
   const int64_t budget_pref = lanes ? kFastScratchBudget : kScratchBudget;
-  const Plan ppref = plan_of(budget_pref / std::max<int64_t>(1, per_cand), sub_pref);
+  const Plan ppref = plan_of(std::min<int64_t>(budget_pref / std::max<int64_t>(1, per_cand),
+                                               int64_t(65535) * 64),  // transpose grids index 64 candidates in y
+                             sub_pref);
   const Plan pmin = plan_of(1, 1);
   auto plan_fit = [&](int64_t bytes) {
     if ((int64_t)ppref.total <= bytes) return ppref;
@@ -2449,12 +2649,15 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   err = hipFuncSetAttribute(reinterpret_cast<const void *>(&ready_schedule), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds);
   if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
-  const int packed = G.succ2 && g->n_link <= 2 ? (g->max_indeg <= 2 ? 2 : g->max_indeg <= 4 ? 4 : 0) : 0;
-  const void *lane_fn = packed == 2   ? reinterpret_cast<const void *>(&ready_lanes<2>)
-                        : packed == 4 ? reinterpret_cast<const void *>(&ready_lanes<4>)
-                                      : reinterpret_cast<const void *>(&ready_lanes<0>);
+  const bool shift = G.link_shift >= 0, one_class = g->n_class == 1;
+  const void *ops_fn = G.ready_width <= 4    ? ready_ops_fn<8>(one_class, shift)
+                       : G.ready_width <= 10 ? ready_ops_fn<16>(one_class, shift)
+                                             : ready_ops_fn<32>(one_class, shift);
+  const void *lane_fn = G.succ2 && g->n_link <= 2 && g->max_indeg <= 4 ? reinterpret_cast<const void *>(&ready_lanes<4>)
+                                                                        : reinterpret_cast<const void *>(&ready_lanes<0>);
   if (lanes) {
-    err = hipFuncSetAttribute(lane_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lane_lds);
+    err = hipFuncSetAttribute(ops ? ops_fn : lane_fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(ops ? ready_ops_lds(D, R) : lane_lds));
     if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
   }
   Plan pl = ppref;
@@ -2533,7 +2736,34 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       Pc = rows;
     }
     SsTimingRec *ts = ss_timing_start(SS_KERNEL_SCHEDULE, stream);
-    if (lanes) {
+    if (ops) {
+      auto *finT = reinterpret_cast<uint32_t *>(spill);
+      auto *rankT = reinterpret_cast<uint16_t *>(reinterpret_cast<unsigned char *>(spill) + align((size_t)(nb * N) * 4));
+      auto *PT = reinterpret_cast<uint8_t *>(rankT) + align((size_t)(nb * N) * 2);
+      const uint8_t *pt = src.op_major ? src.p + b0 : PT;
+      int64_t ppitch = src.op_major ? B : nb, nbv = nb;
+      int64_t *ms_out = makespan + b0, *sf_out = sumfin ? sumfin + b0 : nullptr,
+              *sl_out = slack ? slack + b0 * R : nullptr;
+      uint8_t *vi_out = violation + b0;
+      if (!src.op_major && N > 0) placements_to_op_major(Pc, nb, N, PT, stream);
+      hipLaunchKernelGGL(fill_u32, dim3((unsigned)(4 * cus)), dim3(256), 0, stream, finT, nb * N, kFinUnset);
+      void *args[] = {const_cast<GmgView *>(&G), &pt, &ppitch, &nbv, &finT, &rankT, &lovf, &ms_out, &sf_out, &sl_out,
+                      &vi_out};
+      err = hipLaunchKernel(ops_fn, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave), args,
+                            ready_ops_lds(D, R), stream);
+      if (N > 0) {
+        const dim3 tg((unsigned)((nb + 63) / 64), (unsigned)((N + 63) / 64));
+        hipLaunchKernelGGL(transpose_tiles<uint32_t>, tg, dim3(256), 0, stream, static_cast<const uint32_t *>(finT), N,
+                           nb, nb, fin);
+        hipLaunchKernelGGL(transpose_tiles<uint16_t>, tg, dim3(256), 0, stream, static_cast<const uint16_t *>(rankT),
+                           N, nb, nb, rank);
+      }
+      if (err == hipSuccess) err = hipGetLastError();
+      if (err != hipSuccess) {
+        rc = hip_fail(err, "ready_ops launch");
+        break;
+      }
+    } else if (lanes) {
       int64_t *ms_out = makespan + b0, *sf_out = sumfin ? sumfin + b0 : nullptr,
               *sl_out = slack ? slack + b0 * R : nullptr;
       uint8_t *vi_out = violation + b0;
@@ -2548,7 +2778,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
         break;
       }
     }
-    // the candidates ready_lanes flagged (all of them without it), one wave each
+    // the candidates the lanes flagged (all of them without lanes), one wave each
     hipLaunchKernelGGL(ready_schedule, dim3((unsigned)nb), dim3(kWave), lds, stream, G, Pc, fin, rank, miss, spill,
                        makespan + b0, sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr,
                        violation + b0, static_cast<const uint32_t *>(lovf));

@@ -79,6 +79,14 @@ struct GmgView {
   const int32_t *src_ops;
   const uint64_t *src_keys;
   int32_t n_src;
+  // ready-time dispatch with at most two successors and two predecessors per
+  // op and at most two link classes: three uint4 per op, {duration (one device
+  // class), transfer time over class 0, over class 1, first two successors as
+  // u16}, {those successors' other predecessors as u16, the releases of their
+  // requests, the op's request} and the other predecessors' transfer times over
+  // class 0 and 1 each (0xFFFF: no such op); null otherwise
+  const uint4 *ready_rec;
+  int32_t ready_width;  // most ops ready at once, sources aside, when ops run in index order
 };
 
 // Fields of op_meta for op v.  Predecessors beyond the first four and link

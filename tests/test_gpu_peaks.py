@@ -161,3 +161,41 @@ def test_many_pending_transfers(D, fan):
     P[4, 3] = D if D < 255 else 255  # names an unknown device
     check(g, P, links="ports")
     check(g, P)
+
+
+@pytest.mark.parametrize("layout", ["row", "op"])
+@pytest.mark.parametrize("width", [2, 4, 5, 8, 10, 11, 16, 31, 33, 64])
+def test_ready_widths(width, layout):
+    """`width` ops ready at once (chains out of a binary tree, some joined
+    again): each slot count of the ready-time lanes, and more than they hold."""
+    rng = np.random.default_rng(width)
+    edges, leaves, n = [], [0], 1
+    while len(leaves) < width:  # split the earliest leaf in two
+        v = leaves.pop(0)
+        edges += [(v, n), (v, n + 1)]
+        leaves += [n, n + 1]
+        n += 2
+    for _ in range(6):  # chains, now and then two joined into one and split again
+        nxt = []
+        for i, v in enumerate(leaves):
+            edges.append((v, n))
+            nxt.append(n)
+            n += 1
+        leaves = nxt
+        if len(leaves) > 2:
+            edges += [(leaves[0], n), (leaves[1], n), (n, n + 1), (n, n + 2)]
+            leaves = leaves[2:] + [n + 1, n + 2]
+            n += 3
+    D, B = 5, 101
+    g = synth.make_gmg(D, ["op"] * n, edges, rng.integers(0, 3, n), [[int(x), int(x) + 2] for x in rng.integers(1, 30, n)],
+                       rng.integers(0, 900, n), [[(3 * d, 40 + 6 * d), (70 + d, synth.TIME_INF)] for d in range(D)],
+                       [4_000] * D, [0, 11, 5], [600, 900, 300], link_class=rng.integers(0, 2, (D, D)).astype(np.uint8),
+                       bw=(40, 9), lat=(1, 4), dev_class=[d % 2 for d in range(D)])
+    P = rng.integers(0, D, (B, n)).astype(np.uint8)
+    P[3], P[9, -1] = 1, D
+    ref = oracle.simulate_batch(g, P, dispatch=oracle.READY_ORDER, n_threads=8)
+    A = torch.from_numpy(np.ascontiguousarray(P if layout == "row" else P.T)).cuda()
+    out = ss.simulate_batch(ss.Gmg(g), A, dispatch="ready", layout=layout)
+    torch.cuda.synchronize()
+    for f in FIELDS:
+        assert np.array_equal(out[f].cpu().numpy(), ref[f]), f
