@@ -29,14 +29,14 @@
 // beyond the placement and finish rows is a two-byte rank and a two-byte gap
 // per op, which stay in the CU's caches.
 //
-// Bound: instruction issue and LDS access (no phase waits for memory beyond the
-// L2).  It takes the place of interval records in global memory, bucketed per
-// device and evaluated one device at a time in a wave of its own, whose fixed
-// cost per device was most of the pass on small graphs; before and after, for
-// the whole call: 256 candidates of 32 ops 111 and 52 us, 65,536 of 322 ops
-// 3.07 and 1.26 ms, 100,003 of 2,052 ops 13.97 and 7.20 ms, 131,072 of 10,000
-// ops 48.7 and 28.9 ms, 32,771 of a 2,001-op graph with 34 consumers of some
-// outputs 19.0 and 6.69 ms.  Graphs that do not fit keep the records.
+// Bound: the latency of each pass over the ops at sixteen waves a CU, then LDS
+// access.  It takes the place of interval records in global memory, bucketed
+// per device and evaluated one device at a time in a wave of its own, whose
+// fixed cost per device was most of the pass on small graphs; the two passes
+// before and this one: 65,536 candidates of 322 ops 2.8 and 0.73 ms, 100,003 of
+// 2,052 ops 11.5 and 3.6 ms, 131,072 of 10,000 ops 38.2 and 17.5 ms, 32,771 of
+// a 2,001-op graph with 34 consumers of some outputs 16.5 and 4.2 ms.  Graphs
+// that do not fit keep the records.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -47,11 +47,8 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr uint32_t kInf32 = 0xFFFFFFFFu;
-constexpr uint32_t kNoEvent = 0xFFFFu;  // gap table: the own output is never freed
-// gap table entries hold the flat gap of the own free in the low bits and
-// this flag for an op with a copy on some device
-constexpr uint32_t kHasCopy = 0x8000u;
-constexpr int kMaxFlat = 0x7FFF;  // flat gaps a table entry can hold (kNoEvent & ~kHasCopy is none of them)
+constexpr uint32_t kNoGap = 0xFFFFu;  // gap table: no own free (never freed, or the op is on the list)
+constexpr int kMaxFlat = 0xFFFF;      // flat gaps a table entry can hold
 
 __device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
 
@@ -136,20 +133,42 @@ struct WideLds {
 };
 constexpr int kWide = 8;  // successors a lane walks alone (three nested walks of them); more are walked by the wave
 
+// An op's fields, and its successors' (absent ones repeat the op itself).
+struct OpIn {
+  uint32_t d, rv, f, b, s2;
+};
+struct SuccIn {
+  uint32_t dx0, dx1, fx0, fx1, rx0, rx1;
+};
+
+template <bool kCsr>
+__device__ __forceinline__ OpIn load_op(const GmgView &G, const uint8_t *prow, const uint32_t *frow,
+                                        const uint16_t *rk, int v) {
+  return OpIn{prow[v], rk[v], frow[v], G.bytes32[v], kCsr ? 0u : G.succ2[v]};
+}
+
+template <bool kCsr>
+__device__ __forceinline__ SuccIn load_succ(const uint8_t *prow, const uint32_t *frow, const uint16_t *rk,
+                                            const OpIn &a, int v) {
+  if (kCsr) return SuccIn{};
+  const uint32_t i0 = a.s2 & 0xFFFFu, i1 = a.s2 >> 16;
+  const int y0 = i0 != 0xFFFFu ? (int)i0 : v, y1 = i1 != 0xFFFFu ? (int)i1 : v;
+  return SuccIn{prow[y0], prow[y1], frow[y0], frow[y1], rk[y0], rk[y1]};
+}
+
 // The residency events of op v, passed to `ev` (an op per lane):
 //   ev.own_free(d, q, t, b)      the own output's free on v's device, flat gap q
 //   ev.copy(e, qa, ta, qf, tf, b)  a copy on device e: allocated in gap qa, freed in qf (from any lane)
 //   ev.copied()                  v has a copy
 // kCsr: any graph, successors from the CSR.  Otherwise at most two successors
-// per op, one device class and at most two link classes: the successors come
-// from succ2 and the fields of both are loaded unconditionally (absent ones
-// repeat v), with kShift the link class comes from the device ids.  kPorts:
+// per op, one device class and at most two link classes: with kShift the link class comes from the device ids.  kPorts:
 // arrivals of the transfers per predecessor edge in arow.
 template <bool kCsr, bool kShift, bool kPorts, class Ev>
 __device__ __forceinline__ void op_events(const GmgView &G, const uint8_t *prow, const uint32_t *frow,
-                                          const uint16_t *rk, const uint32_t *arow, int v, bool act, int sh,
-                                          const uint32_t *S, const int *gb, const WideLds &wl, Ev &&ev) {
-  const uint32_t d = prow[v], rv = rk[v], f = frow[v], b = G.bytes32[v] >> sh;
+                                          const uint16_t *rk, const uint32_t *arow, int v, bool act, const OpIn &op,
+                                          const SuccIn &su, int sh, const uint32_t *S, const int *gb,
+                                          const WideLds &wl, Ev &&ev) {
+  const uint32_t d = op.d, rv = op.rv, f = op.f, b = op.b >> sh;
   if (kCsr) {
     const int x0 = G.succ_ptr[v], x1 = act ? G.succ_ptr[v + 1] : x0;
     const int qd = gb[d];
@@ -245,15 +264,12 @@ __device__ __forceinline__ void op_events(const GmgView &G, const uint8_t *prow,
       wave_lds_fence();
     }
   } else {
-    const uint32_t s2 = G.succ2[v];
-    const uint32_t i0 = s2 & 0xFFFFu, i1 = s2 >> 16;
-    const bool has0 = act && i0 != 0xFFFFu, has1 = act && i1 != 0xFFFFu;
-    const int y0 = has0 ? (int)i0 : v, y1 = has1 ? (int)i1 : v;
-    const uint32_t dx0 = prow[y0], dx1 = prow[y1];
-    const uint32_t fx0 = frow[y0], fx1 = frow[y1];
-    const uint32_t rx0 = rk[y0], rx1 = rk[y1];
+    // an op with a consumer on another device
+    const bool has0 = act && (op.s2 & 0xFFFFu) != 0xFFFFu, has1 = act && (op.s2 >> 16) != 0xFFFFu;
+    const uint32_t dx0 = su.dx0, dx1 = su.dx1, fx0 = su.fx0, fx1 = su.fx1, rx0 = su.rx0, rx1 = su.rx1;
     const bool loc0 = dx0 == d, loc1 = dx1 == d;
     const bool rem0 = has0 && !loc0, rem1 = has1 && !loc1;
+    if (!__any(has0)) return;
     // own output: until the local consumer that finishes last (an absent
     // successor repeats v itself, whose finish is f)
     uint32_t L = f, rl = rv;
@@ -264,63 +280,59 @@ __device__ __forceinline__ void op_events(const GmgView &G, const uint8_t *prow,
     const int qd = gb[d];
     int g = (int)rl + 1;
     uint32_t F = L;
-    if (__any(rem0 || rem1)) {
-      auto cls = [&](uint32_t to) -> uint32_t {
-        if (!kShift) return link_bit(G, d, to);
-        const uint32_t s = (uint32_t)G.link_shift, same = (uint32_t)G.link_same;
-        return (d >> s) == (to >> s) ? same : 1u - same;
-      };
-      const int K = G.n_link;
-      const uint32_t xa = G.xfer32[v * K], xb = G.xfer32[v * K + K - 1];
-      const uint32_t X0 = cls(dx0) ? xb : xa, X1 = cls(dx1) ? xb : xa;
-      uint32_t T0 = f + X0, T1 = f + X1;  // arrivals
-      if (kPorts) {
-        const uint32_t pe = G.succ2_pe[v], e0 = pe & 0xFFFFu, e1 = pe >> 16;
-        T0 = arow[e0 == 0xFFFFu ? 0u : e0];  // (an absent one's is not used)
-        T1 = arow[e1 == 0xFFFFu ? 0u : e1];
-      }
-      // two successors on one remote device share the first one's transfer
-      uint32_t A = rem0 ? T0 : 0u;
-      A = rem1 ? umax32(A, T1) : A;
-      if (A > L) {
-        F = A;
-        g = gap_up(S + qd, (int)rv + 1, gb[d + 1] - qd - 1, A);
-      }
-      if (has0) ev.own_free((int)d, qd + g, F, b);
-      if ((rem0 || rem1) && b != 0) ev.copied();
-      const bool same = has1 && dx1 == dx0;
-      if (rem0 && b != 0) {
-        const bool late1 = same && fx1 > fx0;
-        const int ra = same ? (int)min(rx0, rx1) : (int)rx0;
-        const uint32_t st = kPorts ? T0 - X0 : f;  // the transfer's start
-        const int qe = gb[dx0];
-        ev.copy((int)dx0, qe + gap_down(S + qe, ra, st), st, qe + (int)(late1 ? rx1 : rx0) + 1, late1 ? fx1 : fx0, b);
-      }
-      if (rem1 && !same && b != 0) {
-        const uint32_t st = kPorts ? T1 - X1 : f;
-        const int qe = gb[dx1];
-        ev.copy((int)dx1, qe + gap_down(S + qe, (int)rx1, st), st, qe + (int)rx1 + 1, fx1, b);
-      }
-    } else if (has0) {
-      ev.own_free((int)d, qd + g, F, b);
+    auto cls = [&](uint32_t to) -> uint32_t {
+      if (!kShift) return link_bit(G, d, to);
+      const uint32_t s = (uint32_t)G.link_shift, same = (uint32_t)G.link_same;
+      return (d >> s) == (to >> s) ? same : 1u - same;
+    };
+    const int K = G.n_link;
+    const uint32_t xa = G.xfer32[v * K], xb = G.xfer32[v * K + K - 1];
+    const uint32_t X0 = cls(dx0) ? xb : xa, X1 = cls(dx1) ? xb : xa;
+    uint32_t T0 = f + X0, T1 = f + X1;  // arrivals
+    if (kPorts) {
+      const uint32_t pe = G.succ2_pe[v], e0 = pe & 0xFFFFu, e1 = pe >> 16;
+      T0 = arow[e0 == 0xFFFFu ? 0u : e0];  // (an absent one's is not used)
+      T1 = arow[e1 == 0xFFFFu ? 0u : e1];
+    }
+    // two successors on one remote device share the first one's transfer
+    uint32_t A = rem0 ? T0 : 0u;
+    A = rem1 ? umax32(A, T1) : A;
+    if (A > L) {
+      F = A;
+      g = gap_up(S + qd, (int)rv + 1, gb[d + 1] - qd - 1, A);
+    }
+    if (has0) ev.own_free((int)d, qd + g, F, b);
+    const bool same = has1 && dx1 == dx0;
+    if (rem0 && b != 0) {
+      const bool late1 = same && fx1 > fx0;
+      const int ra = same ? (int)min(rx0, rx1) : (int)rx0;
+      const uint32_t st = kPorts ? T0 - X0 : f;  // the transfer's start
+      const int qe = gb[dx0];
+      ev.copy((int)dx0, qe + gap_down(S + qe, ra, st), st, qe + (int)(late1 ? rx1 : rx0) + 1, late1 ? fx1 : fx0, b);
+    }
+    if (rem1 && !same && b != 0) {
+      const uint32_t st = kPorts ? T1 - X1 : f;
+      const int qe = gb[dx1];
+      ev.copy((int)dx1, qe + gap_down(S + qe, (int)rx1, st), st, qe + (int)rx1 + 1, fx1, b);
     }
   }
 }
 
-// First walk: bytes allocated and freed per gap, and the gap table.
+// First walk: bytes allocated and freed per gap.
 template <class Acc>
 struct Accumulate {
   Acc *A, *F;
-  uint32_t gap;  // this op's table entry
+  uint32_t gap;  // of this op's own free
+  bool remote;   // it has copies
   __device__ void own_free(int, int q, uint32_t, uint32_t b) {
     lds_add(&F[q], (Acc)b);
-    gap = (gap & kHasCopy) | (uint32_t)q;
+    gap = (uint32_t)q;
   }
   __device__ void copy(int, int qa, uint32_t, int qf, uint32_t, uint32_t b) {
     lds_add(&A[qa], (Acc)b);
     lds_add(&F[qf], (Acc)b);
   }
-  __device__ void copied() { gap |= kHasCopy; }
+  __device__ void copied() { remote = true; }
 };
 
 // Second walk: the events of hard gaps, as a list per gap whose head replaces
@@ -354,7 +366,8 @@ template <bool kCsr, bool kGiven, bool kShift, bool kPorts, bool kNarrow>
 __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t *__restrict__ P,
                                                   const uint32_t *__restrict__ fin, int64_t fpitch,
                                                   const uint32_t *__restrict__ arr, uint16_t *__restrict__ rank_all,
-                                                  uint16_t *__restrict__ gap_all, uint4 *__restrict__ node_all,
+                                                  uint16_t *__restrict__ gap_all, uint16_t *__restrict__ list_all,
+                                                  uint4 *__restrict__ node_all,
                                                   int64_t node_cap, int lds_nodes, int64_t nb,
                                                   uint32_t *__restrict__ ticket, int64_t *__restrict__ peak,
                                                   uint8_t *__restrict__ violation) {
@@ -372,10 +385,10 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
   Acc *sb = best + D;                                        // [D] prefix sum before the device's first gap
   Acc *wsum = sb + D;                                        // [16] sums of the waves' runs
   int *gb = reinterpret_cast<int *>(wsum + 16);              // [D + 1] first flat entry of the device
-  uint32_t *misc = reinterpret_cast<uint32_t *>(gb + D + 1);  // [0] ticket, [1] hard gaps, [2] events, [3] violated
+  uint32_t *misc = reinterpret_cast<uint32_t *>(gb + D + 1);  // [0] ticket, [1] hard gaps, [2] events, [3] violated, [4] listed ops
   WideLds wl{nullptr, nullptr};
   if (kCsr) {  // [W][D] each
-    unsigned char *p = reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(misc + 4) + 7) & ~uintptr_t(7));
+    unsigned char *p = reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(misc + 5) + 7) & ~uintptr_t(7));
     wl.last = reinterpret_cast<uint64_t *>(p) + (size_t)w * D;
     wl.low = reinterpret_cast<uint32_t *>(p + (size_t)W * D * 8) + (size_t)w * D;
     for (int d = lane; d < D; d += kWave) {
@@ -389,13 +402,23 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
   uint32_t *whist = hist + (size_t)w * D;
   const int sh = kNarrow ? G.peak_shift : 0;
   uint16_t *gap_of = gap_all + (int64_t)blockIdx.x * N;
+  uint16_t *list = list_all + (int64_t)blockIdx.x * N;  // ops with a consumer on another device
   const int seg = ((N + T - 1) / T) * kWave;  // ops of a wave while ranks are made
 
+  // Candidates: kPeakTickets contiguous ranges, each with its share of the
+  // workgroups and a counter on a line of its own (one counter for all took
+  // 14 ns a candidate, as long as a small candidate's work over the chip);
+  // a workgroup's first candidate needs none, the next is fetched meanwhile.
+  const int n_cls = min(kPeakTickets, (int)gridDim.x), cls = blockIdx.x % n_cls;
+  const int64_t c_hi = nb * (cls + 1) / n_cls, c_lo = nb * cls / n_cls;
+  const int64_t c_rest = c_lo + ((int)gridDim.x - cls + n_cls - 1) / n_cls;  // past the first ones
+  int64_t c_next = c_lo + blockIdx.x / n_cls;
   for (;;) {
     __syncthreads();  // the last candidate's LDS state has been read
     if (tid == 0) {
-      misc[0] = atomicAdd(ticket, 1u);
-      misc[1] = misc[2] = misc[3] = 0;
+      misc[0] = (uint32_t)(c_next < c_hi ? c_next : nb);
+      misc[1] = misc[2] = misc[3] = misc[4] = 0;
+      c_next = c_rest < c_hi ? c_rest + atomicAdd(&ticket[cls * kTicketPitch], 1u) : nb;
     }
     for (int d = lane; d < D; d += kWave) {
       whist[d] = 0;
@@ -414,9 +437,36 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     const uint32_t *arow = kPorts ? arr + c * E : nullptr;
     uint16_t *rk = rank_all + (kGiven ? c : (int64_t)blockIdx.x) * N;
 
-    // ops per device, and with index ranks per wave's segment of the ops
+    // Each wave counts its segment's ops per device; with index ranks it ranks
+    // them too, among the segment's: the lanes of a chunk on one device come
+    // from a lane mask per device, and the lowest of them moves the count on
+    // (many lanes of a chunk share a device where a request's ops follow each
+    // other on it, and an atomic from each would take its turn).
     const int v_lo = min(w * seg, N), v_hi = min(v_lo + seg, N);
-    for (int v = v_lo + lane; v < v_hi; v += kWave) atomicAdd(&whist[prow[v]], 1u);
+    if (v_lo < v_hi) {
+      uint32_t dn = prow[min(v_lo + lane, v_hi - 1)];
+      for (int v0 = v_lo; v0 < v_hi; v0 += kWave) {
+        const int v = v0 + lane;
+        const bool act = v < v_hi;
+        const uint32_t d = dn;
+        dn = prow[min(v + kWave, v_hi - 1)];  // the next chunk's, in flight meanwhile
+        if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
+        wave_lds_fence();
+        const uint64_t peers = mask[d];
+        const uint32_t before = whist[d];
+        wave_lds_fence();
+        const uint32_t below =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+        if (act) {
+          if (below == 0) {
+            mask[d] = 0;
+            whist[d] = before + (uint32_t)__popcll(peers);
+          }
+          if (!kGiven) rk[v] = (uint16_t)(before + below);
+        }
+        wave_lds_fence();
+      }
+    }
     __syncthreads();
     for (int d = tid; d < D; d += T) {
       uint32_t s = 0;
@@ -447,30 +497,30 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     }
     __syncthreads();
     // every op's rank on its device and its start
-    for (int v0 = v_lo; v0 < v_hi; v0 += kWave) {
-      const int v = v0 + lane;
-      const bool act = v < v_hi;
-      const int vc = act ? v : v_hi - 1;
-      const uint32_t d = prow[vc];
-      uint32_t r;
-      if (kGiven) {
-        r = rk[vc];
-      } else {
-        // the lanes of this chunk on d, from a lane mask per device
-        if (act) atomicOr(reinterpret_cast<unsigned long long *>(&mask[d]), 1ull << lane);
-        wave_lds_fence();
-        const uint64_t peers = mask[d];
-        const uint32_t before = whist[d];
-        wave_lds_fence();
-        r = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-        if (act) {
-          mask[d] = 0;
-          atomicAdd(&whist[d], 1u);
-          rk[v] = (uint16_t)r;
+    if (v_lo < v_hi) {
+      auto load = [&](int v, uint32_t &d, uint32_t &r, uint32_t &f, uint32_t &w_) {
+        v = min(v, v_hi - 1);
+        d = prow[v];
+        r = rk[v];
+        f = frow[v];
+        w_ = !kCsr || C == 1 ? G.dur32[v] : 0u;
+      };
+      uint32_t dn, rn, fn, wn;
+      load(v_lo + lane, dn, rn, fn, wn);
+      for (int v0 = v_lo; v0 < v_hi; v0 += kWave) {
+        const int v = v0 + lane;
+        const uint32_t d = dn, f = fn;
+        uint32_t r = rn, dur = wn;
+        load(v + kWave, dn, rn, fn, wn);  // in flight meanwhile
+        if (v < v_hi) {
+          if (!kGiven) {
+            r += whist[d];
+            rk[v] = (uint16_t)r;
+          }
+          if (kCsr && C != 1) dur = G.dur32[(int64_t)v * C + G.dev_class[d]];
+          S[gb[d] + r] = f - dur;
         }
       }
-      const uint32_t dur = !kCsr || C == 1 ? G.dur32[vc] : G.dur32[(int64_t)vc * C + G.dev_class[d]];
-      if (act) S[gb[d] + r] = frow[vc] - dur;
     }
     __syncthreads();
     for (int q = tid; q < n; q += T) {
@@ -479,19 +529,60 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     }
     __syncthreads();
 
-    // bytes allocated and freed per gap
+    // bytes allocated and freed per gap: ops whose consumers are all local at
+    // once; those with a remote one, whose gaps take searches, go to a list and
+    // are taken from it with full lanes (a candidate that moves a few ops has
+    // one or two of them in every chunk)
     for (int v0 = w * kWave; v0 < N; v0 += T) {
       const int v = v0 + lane, vc = min(v, N - 1);
       const bool act = v < N;
-      Accumulate<Acc> ev{A, F, kNoEvent & ~kHasCopy};
-      op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, sh, S, gb, wl, ev);
+      const OpIn op = load_op<kCsr>(G, prow, frow, rk, vc);
+      const uint32_t b = op.b >> sh;
+      uint32_t gap = kNoGap;
+      bool listed;
+      if (kCsr) {
+        Accumulate<Acc> ev{A, F, kNoGap, false};
+        op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, op, SuccIn{}, sh, S, gb, wl, ev);
+        listed = act && ev.remote;
+        gap = listed ? kNoGap : ev.gap;
+      } else {
+        const SuccIn su = load_succ<kCsr>(prow, frow, rk, op, vc);
+        const bool has0 = act && (op.s2 & 0xFFFFu) != 0xFFFFu;
+        // (absent successors repeat the op itself)
+        listed = act && (su.dx0 != op.d || su.dx1 != op.d);
+        if (has0 && !listed) {
+          gap = (uint32_t)(gb[op.d] + (int)(su.fx1 > su.fx0 ? su.rx1 : su.rx0) + 1);
+          lds_add(&F[gap], (Acc)b);
+        }
+      }
+      const uint64_t m = __ballot(listed);
+      if (m) {
+        int at = lane == 0 ? (int)atomicAdd(&misc[4], (uint32_t)__popcll(m)) : 0;
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (listed) list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+            (uint16_t)v;
+      }
       if (act) {
-        lds_add(&A[gb[prow[v]] + rk[v] + 1], (Acc)(G.bytes32[v] >> sh));  // the own output opens gap rank + 1
-        gap_of[v] = (uint16_t)ev.gap;
+        lds_add(&A[gb[op.d] + op.rv + 1], (Acc)b);  // the own output opens gap rank + 1
+        gap_of[v] = (uint16_t)gap;
       }
     }
     __syncthreads();
-
+    const int n_list = (int)misc[4];
+    // the listed ops' events, passed to ev (CSR graphs: in the second walk only)
+    auto walk_list = [&](auto ev) {
+      for (int i0 = w * kWave; i0 < n_list; i0 += T) {
+        const bool act = i0 + lane < n_list;
+        const int v = list[min(i0 + lane, n_list - 1)];
+        const OpIn op = load_op<kCsr>(G, prow, frow, rk, v);
+        op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, v, act, op, load_succ<kCsr>(prow, frow, rk, op, v), sh,
+                                        S, gb, wl, ev);
+      }
+    };
+    if (!kCsr) {
+      walk_list(Accumulate<Acc>{A, F, kNoGap, false});
+      __syncthreads();
+    }
     // prefix sums over the flat entries (modulo 2^32 with 32-bit sums): each
     // thread a run, of odd length so that the lanes' accesses spread over the banks
     {
@@ -519,9 +610,21 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     }
     __syncthreads();
     // the exact values: live bytes at every own start
-    for (int v = tid; v < N; v += T) {
-      const uint32_t d = prow[v];
-      lds_max(&best[d], (Acc)(A[gb[d] + rk[v]] - sb[d] + (Acc)(G.bytes32[v] >> sh)));
+    // (few raise their device's best: reading it first spares the atomic)
+    for (int v0 = tid; v0 < N; v0 += 4 * T) {
+      uint32_t d[4], r[4], b[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int v = min(v0 + k * T, N - 1);
+        d[k] = prow[v];
+        r[k] = rk[v];
+        b[k] = G.bytes32[v] >> sh;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {  // (the last op again past the end)
+        const Acc live = A[gb[d[k]] + r[k]] - sb[d[k]] + (Acc)b[k];
+        if (live > best[d[k]]) lds_max(&best[d[k]], live);
+      }
     }
     __syncthreads();
     // hard gaps: their bound replaces their frees, an empty list their sum
@@ -540,18 +643,20 @@ __global__ __launch_bounds__(1024) void lds_peaks(const GmgView G, const uint8_t
     }
     __syncthreads();
     if (misc[1]) {
-      // the events of the hard gaps: an op whose own free falls into one, or
-      // that has copies
+      // the events of the hard gaps: own frees that fall into one, and the
+      // listed ops'
       auto collect = [&](uint4 *node, uint32_t cap) {
+        Collect<Acc> ev{A, node, &misc[2], cap};
         for (int v0 = w * kWave; v0 < N; v0 += T) {
           const int v = v0 + lane, vc = min(v, N - 1);
-          const uint32_t e = gap_of[vc], q = e & ~kHasCopy;
-          const bool own = q != (kNoEvent & ~kHasCopy) && *reinterpret_cast<const uint32_t *>(&A[q]) != kEasy;
-          const bool act = v < N && (own || (e & kHasCopy));
+          const uint32_t q = gap_of[vc];
+          const bool act = v < N && q != kNoGap && *reinterpret_cast<const uint32_t *>(&A[q]) != kEasy;
           if (!__any(act)) continue;
-          op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, sh, S, gb, wl,
-                                          Collect<Acc>{A, node, &misc[2], cap});
+          const OpIn op = load_op<kCsr>(G, prow, frow, rk, vc);
+          op_events<kCsr, kShift, kPorts>(G, prow, frow, rk, arow, vc, act, op, load_succ<kCsr>(prow, frow, rk, op, vc),
+                                          sh, S, gb, wl, ev);
         }
+        walk_list(ev);
         __syncthreads();
       };
       // live bytes at each collected allocation: the gap's bound less the
@@ -647,7 +752,7 @@ PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_bloc
 size_t ss_peaks_slot_bytes(const ss_gmg *g, const PeaksShape &s, bool given_ranks) {
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t N = (size_t)g->n_ops;
-  return align(N * 2) * (given_ranks ? 1 : 2) + align((size_t)s.node_cap * sizeof(uint4));
+  return align(N * 2) * (given_ranks ? 2 : 3) + align((size_t)s.node_cap * sizeof(uint4));
 }
 
 int ss_launch_peaks(const ss_gmg *g, const PeaksShape &s, const uint8_t *P, const uint32_t *fin, int64_t fpitch,
@@ -661,12 +766,14 @@ int ss_launch_peaks(const ss_gmg *g, const PeaksShape &s, const uint8_t *P, cons
   p += align((size_t)s.node_cap * sizeof(uint4)) * (size_t)n_slots;
   auto *gap = reinterpret_cast<uint16_t *>(p);
   p += align((size_t)N * 2) * (size_t)n_slots;
+  auto *list = reinterpret_cast<uint16_t *>(p);
+  p += align((size_t)N * 2) * (size_t)n_slots;
   uint16_t *rank = given ? given : reinterpret_cast<uint16_t *>(p);
   const bool shift = G.link_shift >= 0;
   const void *fn = G.peak_narrow ? peaks_fn<true>(s.csr, given, shift, arr) : peaks_fn<false>(s.csr, given, shift, arr);
   int64_t node_cap = s.node_cap;
   int lds_nodes = s.lds_nodes;
-  void *args[] = {const_cast<GmgView *>(&G), &P, &fin, &fpitch, &arr, &rank, &gap, &node, &node_cap, &lds_nodes, &nb,
+  void *args[] = {const_cast<GmgView *>(&G), &P, &fin, &fpitch, &arr, &rank, &gap, &list, &node, &node_cap, &lds_nodes, &nb,
                   &ticket, &peak, &violation};
   hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
   if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");

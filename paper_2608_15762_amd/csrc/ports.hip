@@ -404,8 +404,8 @@ size_t ports_lds(int64_t D, int64_t R) {
   return (size_t)kPendLds * 16 + (size_t)D * (sizeof(PortDev) + 8) + (size_t)R * 4 + 16;
 }
 
-__global__ __launch_bounds__(64) void zero_two(uint32_t *p) {
-  if (threadIdx.x < 2) p[threadIdx.x] = 0;
+__global__ __launch_bounds__(256) void zero_words(uint32_t *p, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) p[i] = 0;
 }
 
 int hip_fail(hipError_t err, const char *what) {
@@ -444,6 +444,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
   // per candidate: finish and arrival rows (and placement rows from op-major
   // input); per wave: queues, posting list and pending transfers
+  const size_t sz_tk = align((size_t)(kTicketPitch + kTicketWords) * 4);
   struct Plan {
     int64_t chunk, waves, slots;
     size_t sz_fin, sz_arr, sz_rows, sz_rec, sz_post, sz_pend, sz_slots, total;
@@ -460,7 +461,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
     q.sz_post = align((size_t)(q.waves * N) * 2);
     q.sz_pend = align((size_t)(q.waves * (E + 1)) * 16);
     q.sz_slots = pk_slot * (size_t)q.slots;
-    q.total = q.sz_fin + q.sz_arr + q.sz_rows + q.sz_rec + q.sz_post + q.sz_pend + q.sz_slots + 256;
+    q.total = q.sz_fin + q.sz_arr + q.sz_rows + q.sz_rec + q.sz_post + q.sz_pend + q.sz_slots + sz_tk;
     return q;
   };
   const int64_t per_cand = (N + E) * 4 + (src.op_major ? N : 0);
@@ -509,7 +510,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
   auto *post = reinterpret_cast<uint16_t *>(take(pl.sz_post));
   auto *pend = reinterpret_cast<uint4 *>(take(pl.sz_pend));
   void *slots = take(pl.sz_slots);
-  auto *ticket = reinterpret_cast<uint32_t *>(take(256));  // of the schedule, of the memory pass
+  auto *ticket = reinterpret_cast<uint32_t *>(take(sz_tk));  // of the schedule, then of the memory pass
   int rc = SS_OK;
   err = hipFuncSetAttribute(reinterpret_cast<const void *>(&port_events32),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -525,7 +526,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
       }
       Pc = rows;
     }
-    hipLaunchKernelGGL(zero_two, dim3(1), dim3(64), 0, stream, ticket);
+    hipLaunchKernelGGL(zero_words, dim3(1), dim3(256), 0, stream, ticket, kTicketPitch + kTicketWords);
     SsTimingRec *t = ss_timing_start(SS_KERNEL_SCHEDULE, stream);
     hipLaunchKernelGGL(port_events32, dim3((unsigned)std::min(pl.waves, nb)), dim3(kWave), lds, stream, G, Pc, nb,
                        fin, arr, rec, post, pend, ticket, makespan + b0, sumfin ? sumfin + b0 : nullptr,
@@ -536,7 +537,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
       rc = hip_fail(err, "port_events32 launch");
       break;
     }
-    rc = ss_launch_peaks(g, pk, Pc, fin, N, arr, nullptr, slots, pl.slots, nb, ticket + 1,
+    rc = ss_launch_peaks(g, pk, Pc, fin, N, arr, nullptr, slots, pl.slots, nb, ticket + kTicketPitch,
                          peak ? peak + b0 * D : nullptr, violation + b0, stream);
   }
   if (!W.ptr) {

@@ -20,8 +20,8 @@
 //                 registers, into each candidate's row for the memory passes.
 // then lds_peaks (peaks.hip), one workgroup per candidate, when the graph's gap
 // table fits a CU's LDS (up to about 11,600 ops): 131,072 candidates of the
-// 10,000-op workload take 18.7 ms in it against 38.2 ms in the two passes
-// below, 65,536 of a 322-op graph 0.91 against 2.8 ms.  Larger graphs take, per
+// 10,000-op workload take 17.5 ms in it against 38.2 ms in the two passes
+// below, 65,536 of a 322-op graph 0.73 against 2.8 ms.  Larger graphs take, per
 // sub-chunk of candidates:
 //   fast_intervals one wave per candidate, lanes = consecutive ops (coalesced
 //                 row reads).  Pass A ranks every op among the ops of its
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = kOneClass ? 1 : G.n_class, K = G.n_link;
   const int lane = threadIdx.x;
-  if (blockIdx.x == 0 && lane == 0) *ticket = 0;  // the memory pass takes its candidates from it
+  if (ticket && blockIdx.x == 0 && lane < kPeakTickets) ticket[lane * kTicketPitch] = 0;  // the memory pass's counters
   uint32_t *clk = reinterpret_cast<uint32_t *>(lds_raw);                  // [D][64]
   uint32_t *comp = clk + (size_t)D * kWave;                               // [R][64]
   int32_t *sbase = reinterpret_cast<int32_t *>(comp + (size_t)R * kWave);  // [D+1] slice ranges of the devices
@@ -2341,7 +2341,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
       q.n_ticket = 1;
-      q.sz_tk = 256;
+      q.sz_tk = align((size_t)kTicketWords * 4);
       q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + q.sz_slots + q.sz_tk;
       return q;
     }
@@ -2353,7 +2353,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_wk = align((size_t)q.nslots * 2 * (slot_cap + 2) * 4);
     q.sz_wb = align((size_t)q.nslots * slot_cap * 8);
     q.n_ticket = (B + chunk - 1) / chunk * ((chunk + sub - 1) / sub);
-    q.sz_tk = align(((size_t)q.n_ticket + 1) * 4);
+    q.sz_tk = align((size_t)q.n_ticket * 4);
     q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
               q.sz_rank + q.sz_wk + q.sz_wb + q.sz_tk;
     return q;
@@ -2497,7 +2497,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       int64_t *ms_out = makespan + b0, *sf_out = sumfin ? sumfin + b0 : nullptr,
               *sl_out = slack ? slack + b0 * R : nullptr;
       uint8_t *vi_out = violation + b0;
-      uint32_t *rows_out = fin, *tk = pk.ok ? M.ticket : M.ticket + M.n_ticket;  // the last one is spare
+      uint32_t *rows_out = fin, *tk = pk.ok ? M.ticket : nullptr;
       int64_t rpitch = pitch;
       void *args[] = {const_cast<GmgView *>(&G), &sched_P, &ppitch, const_cast<int64_t *>(&nb), &finT, &ms_out,
                       &sf_out, &sl_out, &vi_out, &rows_out, &rpitch, &tk};
@@ -2589,7 +2589,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       q.sub = chunk;
       q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
-      q.n_ticket = (B + chunk - 1) / chunk;
+      q.n_ticket = (B + chunk - 1) / chunk * kTicketWords;
       q.sz_tk = align((size_t)q.n_ticket * 4);
       q.total = q.sz_fin + q.sz_rank + q.sz_miss + q.sz_spill + q.sz_rows + q.sz_slots + q.sz_tk + q.sz_lane;
       return q;
@@ -2789,7 +2789,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       break;
     }
     if (pk.ok)
-      rc = ss_launch_peaks(g, pk, Pc, fin, N, nullptr, rank, slots, pl.nslots, nb, M.ticket + M.it++,
+      rc = ss_launch_peaks(g, pk, Pc, fin, N, nullptr, rank, slots, pl.nslots, nb, M.ticket + kTicketWords * M.it++,
                            peak ? peak + b0 * D : nullptr, violation + b0, stream);
     else
       rc = memory_passes(g, M, Pc, fin, N, nb, true, peak ? peak + b0 * D : nullptr, violation + b0, stream);
@@ -2867,7 +2867,7 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
   const size_t sz_wk = align((size_t)nslots * 2 * (slot_cap + 2) * 4);
   const size_t sz_wb = align((size_t)nslots * slot_cap * 8);
   const int64_t n_chunk = (B + chunk - 1) / chunk;
-  const int64_t n_ticket = n_chunk * ((chunk + sub - 1) / sub);
+  const int64_t n_ticket = pk.ok ? n_chunk * kTicketWords : n_chunk * ((chunk + sub - 1) / sub);
   const size_t sz_tk = align((size_t)n_ticket * 4);
   const size_t sz_arr = ports ? align((size_t)chunk * E * 4) : 0;
   const size_t sz_mem = pk.ok ? ss_peaks_slot_bytes(g, pk, false) * (size_t)nslots
@@ -2931,7 +2931,7 @@ int ss_run_memory_fast(const ss_gmg *g, const uint8_t *P, const int64_t *fin64, 
       }
     }
     if (pk.ok)
-      rc = ss_launch_peaks(g, pk, P + b0 * N, fin, N, arr, nullptr, slots, nslots, nb, M.ticket + M.it++,
+      rc = ss_launch_peaks(g, pk, P + b0 * N, fin, N, arr, nullptr, slots, nslots, nb, M.ticket + kTicketWords * M.it++,
                            peak ? peak + b0 * D : nullptr, violation + b0, stream);
     else
       rc = memory_passes(g, M, P + b0 * N, fin, N, nb, false, peak ? peak + b0 * D : nullptr, violation + b0, stream, arr);
