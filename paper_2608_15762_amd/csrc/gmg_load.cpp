@@ -19,12 +19,13 @@ constexpr i128 kSumLimit = (i128)1 << 63;
 // The arrays of one device allocation at 256-byte aligned offsets: add()
 // records where each goes, pack() copies them once into a buffer of the
 // calling thread that its later loads reuse (a load has uploaded it before it
-// returns); gaps and arrays without a source are zero.  The sources must stay
-// alive until pack().
+// returns); gaps and arrays without a source are zero, reserved ones are the
+// caller's to fill after pack().  The sources must stay alive until pack().
 struct Packer {
   struct Part {
     const void *src;
     size_t bytes, off;
+    bool reserved = false;
   };
   std::vector<Part> parts;
   size_t size = 0;
@@ -38,13 +39,18 @@ struct Packer {
   size_t add(const std::vector<T> &v) {
     return add(v.data(), v.size() * sizeof(T));
   }
-  const unsigned char *pack() const {
+  size_t reserve(size_t bytes) {
+    const size_t off = add(nullptr, bytes);
+    parts.back().reserved = true;
+    return off;
+  }
+  unsigned char *pack() const {
     static thread_local std::vector<unsigned char> buf;
     if (buf.size() < size) buf.resize(size);
     size_t end = 0;
     for (const Part &p : parts) {
       if (p.off > end) std::memset(buf.data() + end, 0, p.off - end);
-      if (p.bytes) {
+      if (p.bytes && !p.reserved) {
         if (p.src) std::memcpy(buf.data() + p.off, p.src, p.bytes);
         else std::memset(buf.data() + p.off, 0, p.bytes);
       }
@@ -454,7 +460,8 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
         time_limit = (uint32_t)limit;
     }
     const bool tab32 = time32 || time_limit > 0;
-    std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe, lutk, lutw, rrec;
+    std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe;
+    bool records = false;  // of the ready-time lanes
     int64_t rwidth = 0;
     std::vector<uint8_t> lgrp;
     // ready-time dispatch: the ops without predecessors by (release of their
@@ -521,31 +528,11 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
             }
         }
       }
-      // records of the ready-time lanes, and how many ops wait ready at once
-      // when ops run in index order
+      // how many ops wait ready at once when ops run in index order
       int64_t max_in = 0;
       for (int64_t v = 0; v < N; ++v) max_in = std::max<int64_t>(max_in, d->pred_ptr[v + 1] - d->pred_ptr[v]);
       if (time32 && K <= 2 && max_in <= 2 && max_outdeg <= 2) {
-        rrec.assign((size_t)N * 12, 0u);
-        for (int64_t v = 0; v < N; ++v) {
-          uint32_t *q = &rrec[(size_t)v * 12], other[2] = {0xFFFFu, 0xFFFFu};
-          q[0] = C == 1 ? (uint32_t)d->dur[v] : 0u;
-          q[1] = (uint32_t)xfer[v * K];
-          q[2] = (uint32_t)xfer[v * K + K - 1];
-          q[3] = succ2[v];
-          for (int64_t i = 0; i < outdeg[v]; ++i) {
-            const int64_t x = succ_idx[succ_ptr[v] + i], e0 = d->pred_ptr[x];
-            if (d->pred_ptr[x + 1] - e0 == 2) {
-              const int64_t u = d->pred_idx[e0] == v ? d->pred_idx[e0 + 1] : d->pred_idx[e0];
-              other[i] = (uint32_t)u;
-              q[8 + 2 * i] = (uint32_t)xfer[u * K];
-              q[9 + 2 * i] = (uint32_t)xfer[u * K + K - 1];
-            }
-            q[5 + i] = (uint32_t)d->release[d->op_req[x]];
-          }
-          q[4] = other[0] | other[1] << 16;
-          q[7] = (uint32_t)d->op_req[v];
-        }
+        records = true;
         std::vector<int32_t> left(N);
         int64_t open = 0;
         for (int64_t v = 0; v < N; ++v) left[v] = (int32_t)(d->pred_ptr[v + 1] - d->pred_ptr[v]);
@@ -615,22 +602,6 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
       const int64_t nb_target = std::max<int64_t>(64, 131072 / D);
       while (((int64_t)max_end >> lut_shift) + 2 > nb_target) ++lut_shift;
       lut_nb = ((int64_t)max_end >> lut_shift) + 2;
-      lutk.assign((size_t)D * lut_nb, 0u);
-      lutw.assign((size_t)D * lut_nb * 4, UINT32_MAX);
-      for (int64_t x = 0; x < D; ++x) {
-        const int64_t a = d->slice_ptr[x], b = d->slice_ptr[x + 1];
-        int64_t k = 0;
-        for (int64_t bk = 0; bk < lut_nb; ++bk) {
-          const uint64_t t0 = (uint64_t)bk << lut_shift;
-          while (a + k < b - 1 && (uint64_t)se32[a + k] < t0) ++k;  // the last slice is open
-          const size_t e = (size_t)(x * lut_nb + bk);
-          lutk[e] = (uint32_t)k;
-          lutw[4 * e] = sb32[a + k];
-          lutw[4 * e + 1] = se32[a + k];
-          lutw[4 * e + 2] = sb32[a + k + 1];  // spare entry past the last slice
-          lutw[4 * e + 3] = se32[a + k + 1];
-        }
-      }
     }
 
     // ------------------------------------------------------------- staging
@@ -656,8 +627,9 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     const size_t o_issue = d->issue_at ? pk.add(d->issue_at, N * sizeof(int64_t)) : 0;
     const size_t o_dur32 = pk.add(dur32), o_xfer32 = pk.add(xfer32), o_sb32 = pk.add(sb32), o_se32 = pk.add(se32),
                  o_rel32 = pk.add(rel32), o_meta = pk.add(meta), o_lbits = pk.add(lbits), o_b32 = pk.add(bytes32),
-                 o_succ2 = pk.add(succ2), o_succ2_pe = pk.add(succ2_pe), o_lutk = pk.add(lutk), o_lutw = pk.add(lutw), o_lgrp = pk.add(lgrp),
-                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops), o_rrec = pk.add(rrec);
+                 o_succ2 = pk.add(succ2), o_succ2_pe = pk.add(succ2_pe), o_lutk = pk.reserve((size_t)D * lut_nb * 4),
+                 o_lutw = pk.reserve((size_t)D * lut_nb * 16), o_lgrp = pk.add(lgrp),
+                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops), o_rrec = pk.reserve(records ? (size_t)N * 48 : 0);
     pk.add(nullptr, 256);  // tail padding
 
     ss_gmg *g = new ss_gmg();
@@ -667,7 +639,55 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     }
     g->aux = ss_device_aux(g->device);
     g->pool = g->aux ? ss_device_pool(g->device) : nullptr;
-    const unsigned char *packed = pk.pack();
+    unsigned char *packed = pk.pack();
+    // The lookup (2.6 MB) and the records (48 bytes an op) in place: in arrays of
+    // their own first (the lookup only) a load of 322 ops took 0.20 ms, now 0.16 ms.
+    if (records) {
+      auto *q = reinterpret_cast<uint32_t *>(packed + o_rrec);
+      for (int64_t v = 0; v < N; ++v, q += 12) {
+        uint32_t other[2] = {0xFFFFu, 0xFFFFu}, rel[2] = {0, 0}, x[4] = {0, 0, 0, 0};
+        for (int64_t i = 0; i < outdeg[v]; ++i) {
+          const int64_t y = succ_idx[succ_ptr[v] + i], e0 = d->pred_ptr[y];
+          if (d->pred_ptr[y + 1] - e0 == 2) {
+            const int64_t u = d->pred_idx[e0] == v ? d->pred_idx[e0 + 1] : d->pred_idx[e0];
+            other[i] = (uint32_t)u;
+            x[2 * i] = (uint32_t)xfer[u * K];
+            x[2 * i + 1] = (uint32_t)xfer[u * K + K - 1];
+          }
+          rel[i] = (uint32_t)d->release[d->op_req[y]];
+        }
+        const uint32_t rec[12] = {C == 1 ? (uint32_t)d->dur[v] : 0u,
+                                  (uint32_t)xfer[v * K],
+                                  (uint32_t)xfer[v * K + K - 1],
+                                  succ2[v],
+                                  other[0] | other[1] << 16,
+                                  rel[0],
+                                  rel[1],
+                                  (uint32_t)d->op_req[v],
+                                  x[0],
+                                  x[1],
+                                  x[2],
+                                  x[3]};
+        std::memcpy(q, rec, sizeof rec);
+      }
+    }
+    if (tab32) {
+      auto *lutk = reinterpret_cast<uint32_t *>(packed + o_lutk), *lutw = reinterpret_cast<uint32_t *>(packed + o_lutw);
+      for (int64_t x = 0; x < D; ++x) {
+        const int64_t a = d->slice_ptr[x], b = d->slice_ptr[x + 1];
+        int64_t k = 0;
+        for (int64_t bk = 0; bk < lut_nb; ++bk) {
+          const uint64_t t0 = (uint64_t)bk << lut_shift;
+          while (a + k < b - 1 && (uint64_t)se32[a + k] < t0) ++k;  // the last slice is open
+          const size_t e = (size_t)(x * lut_nb + bk);
+          lutk[e] = (uint32_t)k;
+          lutw[4 * e] = sb32[a + k];
+          lutw[4 * e + 1] = se32[a + k];
+          lutw[4 * e + 2] = sb32[a + k + 1];  // spare entry past the last slice
+          lutw[4 * e + 3] = se32[a + k + 1];
+        }
+      }
+    }
     int arc = g->pool ? ss_pool_alloc(g->device, pk.size, g->aux, &g->dev_mem) : SS_ERR_DEVICE;
     hipError_t e = hipSuccess;
     if (arc == SS_OK) {
@@ -730,7 +750,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     V.src_keys = reinterpret_cast<const uint64_t *>(base + o_src);
     V.src_ops = reinterpret_cast<const int32_t *>(base + o_src_ops);
     V.n_src = (int32_t)src_ops.size();
-    V.ready_rec = rrec.empty() ? nullptr : reinterpret_cast<const uint4 *>(base + o_rrec);
+    V.ready_rec = !records ? nullptr : reinterpret_cast<const uint4 *>(base + o_rrec);
     V.ready_width = (int32_t)rwidth;
     V.link_same = lsame;
     V.link_shift = lshift;
