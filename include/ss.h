@@ -357,8 +357,8 @@ int ss_select_best(const ss_gmg *g, const uint8_t *violation, const int64_t *key
  * and their summed duration in milliseconds, and forgets them.  Disabling
  * drops unread records.  Errors: SS_ERR_INVALID_ARG, SS_ERR_DEVICE.
  */
-#define SS_KERNEL_SCHEDULE 0     /* per-candidate list schedule (one lane per candidate) */
-#define SS_KERNEL_MEMORY 1       /* per-device peak memory (one wave per candidate) */
+#define SS_KERNEL_SCHEDULE 0     /* per-candidate list schedule (a lane or a wave per candidate) */
+#define SS_KERNEL_MEMORY 1       /* per-device peak memory (a wave or a workgroup per candidate) */
 #define SS_KERNEL_SELECT 2       /* best-candidate reduction (both passes) */
 #define SS_KERNEL_INTERVALS 3    /* residency intervals into per-device buckets (fast path) */
 #define SS_KERNEL_TRANSPOSE 4    /* layout changes between the passes (fast path) */
