@@ -29,13 +29,13 @@
 // beyond the placement and finish rows is a two-byte rank and a two-byte gap
 // per op, which stay in the CU's caches.
 //
-// Bound: the latency of each pass over the ops at sixteen waves a CU, then LDS
+// Bound: the latency of each pass over the ops at 16 to 24 waves a CU, then LDS
 // access.  It takes the place of interval records in global memory, bucketed
 // per device and evaluated one device at a time in a wave of its own, whose
 // fixed cost per device was most of the pass on small graphs; the two passes
 // before and this one: 65,536 candidates of 322 ops 2.8 and 0.73 ms, 100,003 of
-// 2,052 ops 11.5 and 3.6 ms, 131,072 of 10,000 ops 38.2 and 17.5 ms, 32,771 of
-// a 2,001-op graph with 34 consumers of some outputs 16.5 and 4.2 ms.  Graphs
+// 2,052 ops 11.5 and 3.2 ms, 131,072 of 10,000 ops 38.2 and 17.5 ms, 32,771 of
+// a 2,001-op graph with 34 consumers of some outputs 16.5 and 3.9 ms.  Graphs
 // that do not fit keep the records.
 #include <algorithm>
 #include <climits>
@@ -733,10 +733,12 @@ PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_bloc
   int64_t lds = n4 * (2 * acc + 4) + s.lds_nodes * 16 + (2 * D + 16) * acc + (D + 1) * 4 + 32;
   const int64_t wave_lds = s.csr ? 12 * D : 0;  // the device arrays of ops with many successors
   if (lds + wave_lds > lds_block) return s;
-  // about sixteen waves per CU, none with less than two chunks of 64 ops; the
+  // at least twenty waves per CU where more than one table fits it (100,003
+  // candidates of 2,052 ops 3.6 ms with fifteen, 3.2 with twenty), none with
+  // less than two chunks of 64 ops; the
   // ranks' counts and masks (12 bytes per wave and device) lie on A and F
   const int64_t fit = std::max<int64_t>(1, lds_cu / lds);
-  int64_t waves = std::min<int64_t>(16, std::max<int64_t>(1, 16 / fit));
+  int64_t waves = std::min<int64_t>(16, std::max<int64_t>(1, (20 + fit - 1) / fit));
   waves = std::min(waves, (N + 2 * kWave - 1) / (2 * kWave));
   waves = std::max<int64_t>(1, std::min(waves, 2 * acc * n4 / (12 * D)));
   if (s.csr) waves = std::min(waves, (lds_block - lds) / wave_lds);
