@@ -547,10 +547,12 @@ __global__ __launch_bounds__(kWave) void ready_schedule(const GmgView G, const u
                                                         uint16_t *__restrict__ missing, uint64_t *__restrict__ spill,
                                                         int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
                                                         int64_t *__restrict__ slack, uint8_t *__restrict__ violation,
-                                                        const uint32_t *__restrict__ only) {
+                                                        const uint32_t *__restrict__ only,
+                                                        uint32_t *__restrict__ ticket) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = G.n_class;
   const int lane = threadIdx.x;
+  if (ticket && blockIdx.x == 0 && lane < kPeakTickets) ticket[lane * kTicketPitch] = 0;  // the memory pass's counters
   if (only && only[blockIdx.x] == 0) return;  // candidates the lane kernel has already placed
   uint32_t *clk = reinterpret_cast<uint32_t *>(lds_raw);  // [D]
   uint32_t *comp = clk + D;                               // [R]
@@ -2582,15 +2584,17 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
     q.sz_rank = align(((size_t)chunk * N + 1) * 2);
     q.sz_miss = align(((size_t)chunk * N + 1) * 2);
-    q.sz_spill = align((size_t)chunk * N * 8 + 1024);
+    // spill lists; with op-major lanes first their three arrays
+    q.sz_spill = std::max(align((size_t)chunk * N * 8 + 8),
+                          align((size_t)chunk * N * 4) + align((size_t)chunk * N * 2) + align((size_t)chunk * N + 1));
     q.sz_rows = src.op_major ? align((size_t)chunk * N + 1) : 0;
     q.sz_lane = lanes ? align((size_t)chunk * D * 2) + align((size_t)chunk * 4) : 0;
     if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
       q.sub = chunk;
       q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
-      q.n_ticket = (B + chunk - 1) / chunk * kTicketWords;
-      q.sz_tk = align((size_t)q.n_ticket * 4);
+      q.n_ticket = 1;
+      q.sz_tk = align((size_t)kTicketWords * 4);  // every chunk's in turn
       q.total = q.sz_fin + q.sz_rank + q.sz_miss + q.sz_spill + q.sz_rows + q.sz_slots + q.sz_tk + q.sz_lane;
       return q;
     }
@@ -2718,7 +2722,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   M.aux = g->aux;
 
   int rc = mem_pass_events(M);
-  if (rc == SS_OK) {
+  if (rc == SS_OK && !pk.ok) {
     hipLaunchKernelGGL(fill_zero_u32, dim3((unsigned)std::min<int64_t>((pl.n_ticket + 255) / 256, 1024)), dim3(256),
                        0, stream, M.ticket, pl.n_ticket);
     const hipError_t fe = hipGetLastError();
@@ -2781,7 +2785,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
     // the candidates the lanes flagged (all of them without lanes), one wave each
     hipLaunchKernelGGL(ready_schedule, dim3((unsigned)nb), dim3(kWave), lds, stream, G, Pc, fin, rank, miss, spill,
                        makespan + b0, sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr,
-                       violation + b0, static_cast<const uint32_t *>(lovf));
+                       violation + b0, static_cast<const uint32_t *>(lovf), pk.ok ? M.ticket : nullptr);
     ss_timing_stop(ts, stream);
     err = hipGetLastError();
     if (err != hipSuccess) {
@@ -2789,7 +2793,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
       break;
     }
     if (pk.ok)
-      rc = ss_launch_peaks(g, pk, Pc, fin, N, nullptr, rank, slots, pl.nslots, nb, M.ticket + kTicketWords * M.it++,
+      rc = ss_launch_peaks(g, pk, Pc, fin, N, nullptr, rank, slots, pl.nslots, nb, M.ticket,
                            peak ? peak + b0 * D : nullptr, violation + b0, stream);
     else
       rc = memory_passes(g, M, Pc, fin, N, nb, true, peak ? peak + b0 * D : nullptr, violation + b0, stream);
