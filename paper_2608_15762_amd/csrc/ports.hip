@@ -476,6 +476,7 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace src, int64_t *makespan, int
   SsScratch scr;
   void *scratch = nullptr;
   if (W.ptr) {  // the caller's workspace: the largest chunk that fits
+    W.need_min = pmin.total;
     if (pmin.total > W.bytes)
       return ss_set_error(SS_ERR_INVALID_ARG, "workspace of " + std::to_string(W.bytes) +
                                                    " bytes is smaller than this call's minimum of " +

@@ -2410,6 +2410,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   SsScratch scr;
   void *scratch = nullptr;
   if (W.ptr) {  // the caller's workspace: the largest layout that fits, nothing allocated
+    W.need_min = pmin.total;
     if (pmin.total > W.bytes)
       return ss_set_error(SS_ERR_INVALID_ARG, "workspace of " + std::to_string(W.bytes) +
                                                    " bytes is smaller than this call's minimum of " +
@@ -2668,6 +2669,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   SsScratch scr;
   void *scratch = nullptr;
   if (W.ptr) {
+    W.need_min = pmin.total;
     if (pmin.total > W.bytes)
       return ss_set_error(SS_ERR_INVALID_ARG, "workspace of " + std::to_string(W.bytes) +
                                                    " bytes is smaller than this call's minimum of " +

@@ -1568,13 +1568,31 @@ int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak
   bool generic = false, ports_mem_fast = false;
   const int route = simulate_route(g, ready_dispatch, link_ports, &generic, &ports_mem_fast);
   if (route != SS_OK) return route;
-  if (ports_mem_fast && ss_ports32_ok(g))
-    return ss_run_simulate_ports32(g, P, makespan, peak, violation, slack, sumfin, stream, W);
-  if (generic)
-    return run_simulate_generic(g, P, makespan, peak, violation, slack, sumfin, stream, ready_dispatch, link_ports, W,
-                                nullptr, nullptr, ports_mem_fast && !W.ptr && !W.query);
-  if (ready_dispatch) return ss_run_simulate_ready(g, P, makespan, peak, violation, slack, sumfin, stream, W);
-  return ss_run_simulate_fast(g, P, makespan, peak, violation, slack, sumfin, stream, W);
+  const bool ports32 = ports_mem_fast && ss_ports32_ok(g);
+  auto run_generic = [&](SsWork &w, bool mem_fast) {
+    return run_simulate_generic(g, P, makespan, peak, violation, slack, sumfin, stream, ready_dispatch, link_ports, w,
+                                nullptr, nullptr, mem_fast);
+  };
+  if (generic && !ports32) return run_generic(W, ports_mem_fast && !W.ptr && !W.query);
+  if (!ports32 && g->view.time32)
+    return ready_dispatch ? ss_run_simulate_ready(g, P, makespan, peak, violation, slack, sumfin, stream, W)
+                          : ss_run_simulate_fast(g, P, makespan, peak, violation, slack, sumfin, stream, W);
+  // 32-bit kernels for a call that the general ones can serve as well, one
+  // candidate at a time: those take the workspaces too small for the 32-bit
+  // kernels' smallest chunk (64 candidates of a long horizon, 2.5 MB against
+  // 0.17 MB for 2,052 ops)
+  const int rc = ports32 ? ss_run_simulate_ports32(g, P, makespan, peak, violation, slack, sumfin, stream, W)
+                         : ss_run_simulate_fast(g, P, makespan, peak, violation, slack, sumfin, stream, W);
+  const bool small = W.ptr && W.need_min > W.bytes;  // nothing was launched
+  if (!small && !(W.query && rc == SS_OK)) return rc;
+  SsWork q;
+  q.query = true;
+  if (run_generic(q, false) != SS_OK || q.need_min >= W.need_min) return rc;
+  if (W.query) {
+    W.need_min = q.need_min;
+    return SS_OK;
+  }
+  return run_generic(W, false);
 }
 
 // The state's buffer grows to hold a capture of g (synchronising the stream

@@ -213,7 +213,8 @@ void ss_run_sched_state(const ss_sched *s, uint8_t *state, uint8_t *place, int64
 // allocates beyond.  single: every kernel on the caller's stream (no second
 // stream, no events; one set of interval records).  query: the call only
 // reports need_min (the smallest workspace that works) and need_pref (what
-// the pool path takes for this batch) and launches nothing.
+// the pool path takes for this batch) and launches nothing.  With a workspace
+// the 32-bit kernels set need_min too.
 struct SsWork {
   void *ptr = nullptr;
   size_t bytes = 0;

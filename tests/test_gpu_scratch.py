@@ -54,3 +54,34 @@ def test_ready_scratch_of_many_candidates():
     a = noalloc(h, P, dispatch="ready")
     idx = np.unique(np.linspace(0, B - 1, 300).astype(np.int64))
     same(a, oracle.simulate_batch(g, P.cpu().numpy()[idx], dispatch=oracle.READY_ORDER, n_threads=8), idx)
+
+
+@pytest.mark.parametrize("links", ["latency", "ports"])
+@pytest.mark.parametrize("layout", ["row", "op"])
+def test_smallest_workspace_of_the_general_kernels(links, layout, monkeypatch):
+    """A horizon past 32 bits, and ports on a packed graph: a workspace that
+    holds one candidate of the general kernels is enough, for both."""
+    g = synth.random_gmg(3, n_ops=700, n_dev=4, n_req=3, n_link=2, edge_p=0.3, max_outdeg=2, n_slices=4,
+                         slice_scale=400, cap_scale=20_000)
+    if links == "latency":  # the last windows begin past 2^32
+        last = np.asarray(g.slice_ptr[1:]) - 1
+        first = np.setdiff1d(np.arange(len(g.slice_begin)), last)
+        g.slice_begin[last] += 1 << 33
+        assert len(first)
+    h = ss.Gmg(g)
+    P = np.random.default_rng(1).integers(0, 4, (70, g.n_ops)).astype(np.uint8)
+    ref = oracle.simulate_batch(g, P, dispatch=oracle.LINK_PORTS if links == "ports" else 0, n_threads=8)
+    A = torch.from_numpy(np.ascontiguousarray(P if layout == "row" else P.T)).cuda()
+    lo, hi = ss.workspace_size(h, len(P), layout=layout, links=links)
+    monkeypatch.setenv("SS_PATH", "generic")
+    general, _ = ss.workspace_size(h, len(P), layout=layout, links=links)
+    monkeypatch.delenv("SS_PATH")
+    assert lo <= general
+    for size in (lo, lo + 4096, (lo + hi) // 2, hi):
+        out = ss.simulate_batch(h, A, layout=layout, links=links,
+                                workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        same({f: out[f].cpu().numpy() for f in FIELDS}, ref)
+    with pytest.raises(ss.SSError):
+        ss.simulate_batch(h, A, layout=layout, links=links,
+                          workspace=torch.empty(lo - 256, dtype=torch.uint8, device="cuda"))
