@@ -226,11 +226,13 @@ __global__ __launch_bounds__(kWave) void fast_schedule(const GmgView G, const ui
                                                        uint32_t *__restrict__ finT, int64_t *__restrict__ makespan,
                                                        int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
                                                        uint8_t *__restrict__ violation, uint32_t *__restrict__ finR,
-                                                       int64_t rpitch, uint32_t *__restrict__ ticket) {
+                                                       int64_t rpitch, uint32_t *__restrict__ ticket,
+                                                       uint32_t *__restrict__ marked) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = G.n_dev, N = G.n_ops, R = G.n_req, C = kOneClass ? 1 : G.n_class, K = G.n_link;
   const int lane = threadIdx.x;
   if (ticket && blockIdx.x == 0 && lane < kPeakTickets) ticket[lane * kTicketPitch] = 0;  // the memory pass's counters
+  if (marked && blockIdx.x == 0 && lane == 0) marked[0] = 0;  // the number of candidates left to the int64 kernels
   uint32_t *clk = reinterpret_cast<uint32_t *>(lds_raw);                  // [D][64]
   uint32_t *comp = clk + (size_t)D * kWave;                               // [R][64]
   int32_t *sbase = reinterpret_cast<int32_t *>(comp + (size_t)R * kWave);  // [D+1] slice ranges of the devices
@@ -2256,7 +2258,7 @@ size_t ss_fast_schedule_lds(const ss_gmg *g) {
 struct FastPlan {
   int64_t chunk = 0, sub = 0, nslots = 0, n_ticket = 0, retry_slots = 0;
   int sets = kRecSets;
-  size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_retry = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
+  size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_mark = 0, sz_comp = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
          total = 0;
 };
 
@@ -2312,8 +2314,12 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   // chunk: placements (op-major for the schedule from row-major input, rows
   // for the memory passes from op-major input), op-major and row-major finish
   // times
-  const bool retry = G.time_limit > 0;  // int64 kernels for candidates whose times pass 32 bits
-  const int64_t per_cand = N * (1 + 4) + pitch * 4 + (retry ? (N + R) * 8 : 0);
+  // with a time limit: int64 kernels for the marked candidates after the
+  // memory pass, their finish rows where the 32-bit ones were, op-major and by
+  // candidate, their memory pass's scratch on the 32-bit one's
+  const bool retry = G.time_limit > 0;
+  const size_t retry_slot = retry ? ss_retry_slot_bytes(g) : 0;
+  const int64_t per_cand = N * (1 + 4) + pitch * 4 + (retry ? 4 + R * 8 : 0);
   // A schedule launch is best a whole number of rounds of the waves the chip
   // holds at once (every wave runs about as long as any other).
   const int64_t round =
@@ -2336,15 +2342,21 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_pt = align((size_t)chunk * N + 1);
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
     q.sz_row = align((size_t)chunk * pitch * 4 + 4);
-    q.retry_slots = std::min<int64_t>({(int64_t)cus, chunk, chunk > kWave ? chunk : std::max<int64_t>(1, sub_cap)});
-    q.sz_retry = retry ? align(ss_retry_scratch(g, chunk, q.retry_slots)) : 0;
+    q.sz_mark = retry ? align((size_t)(chunk + 1) * 4) : 0;
+    q.sz_comp = retry && chunk > ss_retry_lanes() ? align((size_t)(chunk * R) * 8 + 8) : 0;
+    auto fit_retry = [&](size_t have) {  // have: scratch of the memory pass
+      if (!retry) return;
+      if (have < retry_slot) q.sz_slots += align(retry_slot - have);
+      q.retry_slots = std::min<int64_t>({(int64_t)cus, chunk, std::max<int64_t>(1, (int64_t)(have / retry_slot))});
+    };
     if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
       q.sub = chunk;
       q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
+      fit_retry(q.sz_slots);
       q.n_ticket = 1;
       q.sz_tk = align((size_t)kTicketWords * 4);
-      q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + q.sz_slots + q.sz_tk;
+      q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_mark + q.sz_comp + q.sz_slots + q.sz_tk;
       return q;
     }
     q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * kPeakBlocksPerCU, sub));
@@ -2356,8 +2368,9 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_wb = align((size_t)q.nslots * slot_cap * 8);
     q.n_ticket = (B + chunk - 1) / chunk * ((chunk + sub - 1) / sub);
     q.sz_tk = align((size_t)q.n_ticket * 4);
-    q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_retry + (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) +
-              q.sz_rank + q.sz_wk + q.sz_wb + q.sz_tk;
+    const size_t rec = (size_t)sets * (q.sz_own + q.sz_cp + q.sz_meta) + q.sz_rank + q.sz_wk + q.sz_wb;
+    fit_retry(rec);
+    q.total = q.sz_pt + q.sz_fin + q.sz_row + q.sz_mark + q.sz_comp + q.sz_slots + rec + q.sz_tk;
     return q;
   };
   // the largest chunk within a budget, in whole rounds of schedule waves
@@ -2438,8 +2451,9 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   auto *PT = reinterpret_cast<uint8_t *>(take(pl.sz_pt));  // op-major copy, or candidate rows of op-major input
   auto *finT = reinterpret_cast<uint32_t *>(take(pl.sz_fin));
   auto *fin = reinterpret_cast<uint32_t *>(take(pl.sz_row));
-  void *const retry_mem = take(pl.sz_retry);
-  void *const slots = take(pl.sz_slots);
+  auto *marked = retry ? reinterpret_cast<uint32_t *>(take(pl.sz_mark)) : nullptr;
+  auto *comp = pl.sz_comp ? reinterpret_cast<int64_t *>(take(pl.sz_comp)) : nullptr;
+  void *const slots = take(pl.sz_slots);  // and the records
   MemPass M{};
   for (int k = 0; k < pl.sets; ++k) {
     M.own[k] = reinterpret_cast<Rec *>(take(pl.sz_own));
@@ -2503,7 +2517,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       uint32_t *rows_out = fin, *tk = pk.ok ? M.ticket : nullptr;
       int64_t rpitch = pitch;
       void *args[] = {const_cast<GmgView *>(&G), &sched_P, &ppitch, const_cast<int64_t *>(&nb), &finT, &ms_out,
-                      &sf_out, &sl_out, &vi_out, &rows_out, &rpitch, &tk};
+                      &sf_out, &sl_out, &vi_out, &rows_out, &rpitch, &tk, &marked};
       const hipError_t le = hipLaunchKernel(sched_fn, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave), args,
                                             sched_lds, stream);
       if (le != hipSuccess && rc == SS_OK) rc = hip_fail(le, "fast_schedule launch");
@@ -2521,7 +2535,8 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
         if (we != hipSuccess) rc = hip_fail(we, "hipStreamWaitEvent");
       }
       if (rc == SS_OK)
-        rc = ss_run_retry(g, Pc, nb, retry_mem, pl.retry_slots, cus, makespan + b0, peak ? peak + b0 * D : nullptr, violation + b0,
+        rc = ss_run_retry(g, Pc, nb, marked, reinterpret_cast<int64_t *>(finT), comp, slots, pl.retry_slots, cus,
+                          makespan + b0, peak ? peak + b0 * D : nullptr, violation + b0,
                           slack ? slack + b0 * R : nullptr, sumfin ? sumfin + b0 : nullptr, stream);
     }
   }

@@ -80,6 +80,9 @@ struct Resume {
   int32_t *cap_cur = nullptr;
 };
 
+// Candidates up to which a wave schedules each, beyond which a lane does (see schedule_wave).
+constexpr int64_t kWaveCandidates = 16384;
+
 __global__ __launch_bounds__(256) void zero_u32(uint32_t *__restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
 }
@@ -108,6 +111,7 @@ __global__ __launch_bounds__(256) void fill_prefix(int64_t *__restrict__ fin, in
 __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const uint8_t *__restrict__ P,
                                                          int64_t nb, int64_t *__restrict__ fin,
                                                          int64_t *__restrict__ comp, const Resume RS,
+                                                         const uint32_t *__restrict__ marked,
                                                          int64_t *__restrict__ makespan,
                                                          int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
                                                          uint8_t *__restrict__ violation) {
@@ -116,16 +120,19 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
   const int lane = threadIdx.x;
   int64_t *clk = reinterpret_cast<int64_t *>(lds_raw);                        // [D][64]
   uint16_t *cur = reinterpret_cast<uint16_t *>(lds_raw + (size_t)D * kWave * 8);  // [D][64]
-  const int64_t c = (int64_t)blockIdx.x * kWave + lane;
-  if (c >= nb) return;
+  // row i of the scratch: candidate i, or the i-th listed one
+  const int64_t i = (int64_t)blockIdx.x * kWave + lane;
+  if (marked && marked[0] <= kWaveCandidates) return;  // left to schedule_wave
+  if (i >= (marked ? (int64_t)marked[0] : nb)) return;
+  const int64_t c = marked ? (int64_t)marked[1 + i] : i;
   const uint8_t *prow = P + c * N;
-  int64_t *frow = fin + c * N;
+  int64_t *frow = fin + i * N;
   const bool from = RS.clk != nullptr;
   for (int d = 0; d < D; ++d) {
     clk[d * kWave + lane] = from ? RS.clk[d] : 0;
     cur[d * kWave + lane] = from ? (uint16_t)RS.cur[d] : 0;
   }
-  for (int r = 0; r < R; ++r) comp[(int64_t)r * nb + c] = from ? RS.comp[r] : G.release[r];
+  for (int r = 0; r < R; ++r) comp[(int64_t)r * nb + i] = from ? RS.comp[r] : G.release[r];
 
   bool invalid = false;
   int64_t ms = from ? RS.scal[0] : 0, sum = from ? RS.scal[1] : 0;
@@ -182,7 +189,7 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
     frow[v] = f;
     ms = imax(ms, f);
     sum += f;
-    int64_t *cr = comp + (int64_t)r * nb + c;
+    int64_t *cr = comp + (int64_t)r * nb + i;
     *cr = imax(*cr, f);
   }
   if (RS.cap_clk) {  // one candidate: its state after its last op
@@ -203,7 +210,7 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
     makespan[c] = ms;
     if (sumfin) sumfin[c] = sum;
     if (slack)
-      for (int r = 0; r < R; ++r) slack[c * R + r] = G.deadline[r] - comp[(int64_t)r * nb + c];
+      for (int r = 0; r < R; ++r) slack[c * R + r] = G.deadline[r] - comp[(int64_t)r * nb + i];
     violation[c] = 0;
   }
 }
@@ -222,7 +229,6 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
 // of 2,000 ops of 16 requests 0.21 and 2.03 ms, 4,096 of 2,052 ops of 4
 // requests 0.74 and 2.2 ms; 16,384 of those 2.17 and 2.35 ms, 16,384 of one
 // chain of 322 ops 0.50 and 0.50 ms, beyond which the lanes win.
-constexpr int64_t kWaveCandidates = 16384;
 constexpr int64_t kWaveReq = 512;  // requests whose completions fit the LDS beside the devices
 
 struct DevState {  // a device's clock and its current slice
@@ -235,8 +241,8 @@ size_t schedule_wave_lds(int64_t D, int64_t R) {
 
 __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
                                                        int64_t *__restrict__ fin, int64_t *__restrict__ comp,
-                                                       const Resume RS, bool retry,
-                                                       int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
+                                                       const Resume RS, const uint32_t *__restrict__ marked,
+                                                       bool any_number, int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
                                                        int64_t *__restrict__ slack,
                                                        uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -247,11 +253,14 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
   int64_t *lcomp = reinterpret_cast<int64_t *>(mask + D);      // [R]
   int64_t *lfin = lcomp + R;                                   // [64] finish times of the chunk
   int32_t *cur = reinterpret_cast<int32_t *>(lfin + kWave);    // [D]
-  for (int64_t c = blockIdx.x; c < nb; c += gridDim.x) {
-    if (retry && violation[c] != SS_VIOLATION_RETRY) continue;
+  const int64_t n_cand = marked ? (int64_t)marked[0] : nb;
+  if (marked && !any_number && n_cand > kWaveCandidates) return;  // left to schedule_kernel
+  // row i of the scratch: candidate i, or the i-th listed one
+  for (int64_t i = blockIdx.x; i < n_cand; i += gridDim.x) {
     __syncthreads();  // the candidate before has been written
+    const int64_t c = marked ? (int64_t)marked[1 + i] : i;
     const uint8_t *prow = P + c * N;
-    int64_t *frow = fin + c * N;
+    int64_t *frow = fin + i * N;
     const bool from = RS.clk != nullptr;
     for (int d = lane; d < D; d += kWave) {
       const int k = from ? RS.cur[d] : 0, q = G.slice_ptr[d] + k;
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
     invalid = __any(invalid);
     __syncthreads();
     for (int r = lane; r < R; r += kWave) {
-      comp[(int64_t)r * nb + c] = lcomp[r];
+      if (comp) comp[(int64_t)r * nb + i] = lcomp[r];
       if (slack) slack[c * R + r] = invalid ? INT64_MIN : G.deadline[r] - lcomp[r];
     }
     if (RS.cap_clk) {  // one candidate: its state after its last op
@@ -398,8 +407,24 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
     if (lane == 0) {
       makespan[c] = invalid ? INT64_MAX : ms;
       if (sumfin) sumfin[c] = invalid ? INT64_MAX : sum;
-      violation[c] = invalid ? SS_VIOLATION_INVALID : retry ? SS_VIOLATION_RETRY : 0;
+      violation[c] = invalid ? SS_VIOLATION_INVALID : 0;
     }
+  }
+}
+
+// The candidates marked SS_VIOLATION_RETRY, listed in any order: marked[0]
+// their number, zero before.
+__global__ __launch_bounds__(256) void list_marked(const uint8_t *__restrict__ violation, int64_t nb,
+                                                   uint32_t *__restrict__ marked) {
+  const int lane = threadIdx.x % kWave;
+  for (int64_t c0 = (int64_t)blockIdx.x * 256; c0 < nb; c0 += (int64_t)gridDim.x * 256) {
+    const int64_t c = c0 + threadIdx.x;
+    const bool hit = c < nb && violation[c] == SS_VIOLATION_RETRY;
+    const uint64_t m = __ballot(hit);
+    if (!m) continue;
+    int at = lane == 0 ? (int)atomicAdd(&marked[0], (uint32_t)__popcll(m)) : 0;
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (hit) marked[1 + (uint32_t)at + __popcll(m & ((1ull << lane) - 1))] = (uint32_t)c;
   }
 }
 
@@ -1130,7 +1155,7 @@ template <bool kReady, bool kPorts>
 __global__ __launch_bounds__(kMemThreads) void memory_kernel(
     const GmgView G, const uint8_t *__restrict__ P, int64_t nb, const int64_t *__restrict__ fin,
     const int64_t *__restrict__ arr, int32_t *__restrict__ bydev_all, int64_t *__restrict__ gkeys_all,
-    int64_t *__restrict__ gvals_all, int64_t slot_cap, bool retry, int64_t *__restrict__ peak,
+    int64_t *__restrict__ gvals_all, int64_t slot_cap, const uint32_t *__restrict__ marked, int64_t *__restrict__ peak,
     uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   int64_t *skeys = reinterpret_cast<int64_t *>(lds_raw);  // [kMemWaves * kMemCap]
@@ -1146,10 +1171,11 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
   int32_t *bydev = bydev_all + (int64_t)blockIdx.x * N;
   int64_t *gkeys = gkeys_all + (int64_t)blockIdx.x * slot_cap;
   int64_t *gvals = gvals_all + (int64_t)blockIdx.x * slot_cap;
-  for (int64_t c = blockIdx.x; c < nb; c += gridDim.x) {
+  const int64_t n_cand = marked ? (int64_t)marked[0] : nb;
+  for (int64_t i = blockIdx.x; i < n_cand; i += gridDim.x) {
+    const int64_t c = marked ? (int64_t)marked[1 + i] : i;
     const uint8_t *prow = P + c * N;
-    const int64_t *frow = fin + c * N;
-    if (retry && violation[c] != SS_VIOLATION_RETRY) continue;
+    const int64_t *frow = fin + i * N;
     if (violation[c] & SS_VIOLATION_INVALID) {
       if (peak)
         for (int d = tid; d < D; d += kMemThreads) peak[c * D + d] = 0;
@@ -1424,11 +1450,11 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
                            slack ? slack + b0 * R : nullptr, violation + b0);
       } else if (nb <= kWaveCandidates && R <= kWaveReq) {
         hipLaunchKernelGGL(schedule_wave, dim3((unsigned)nb), dim3(kWave), schedule_wave_lds(D, R), stream, G, Pc, nb,
-                           fin, comp, RS, false, makespan + b0, sumfin ? sumfin + b0 : nullptr,
+                           fin, comp, RS, static_cast<const uint32_t *>(nullptr), false, makespan + b0, sumfin ? sumfin + b0 : nullptr,
                            slack ? slack + b0 * R : nullptr, violation + b0);
       } else {
         hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave),
-                           sched_lds, stream, G, Pc, nb, fin, comp, RS, makespan + b0,
+                           sched_lds, stream, G, Pc, nb, fin, comp, RS, static_cast<const uint32_t *>(nullptr), makespan + b0,
                            sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr, violation + b0);
       }
       if (capture) {  // one candidate: its finish times and request completions
@@ -1464,7 +1490,8 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
     }
     hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3(kMemThreads), kMemLds, stream, G, Pc, nb,
                        static_cast<const int64_t *>(fin), static_cast<const int64_t *>(arr), bydev, gkeys, gvals,
-                       slot_cap, false, peak ? peak + b0 * D : nullptr, violation + b0);
+                       slot_cap, static_cast<const uint32_t *>(nullptr), peak ? peak + b0 * D : nullptr,
+                       violation + b0);
     err = hipGetLastError();
     ss_timing_stop(t_mem, stream);
     if (err != hipSuccess) rc = hip_fail(err, "memory_kernel launch");
@@ -1476,45 +1503,61 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
   return rc;
 }
 
-size_t ss_retry_scratch(const ss_gmg *g, int64_t nb, int64_t slots) {
+int64_t ss_retry_lanes() { return kWaveCandidates; }
+
+size_t ss_retry_slot_bytes(const ss_gmg *g) {
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
-  const int64_t N = g->n_ops, R = g->n_req;
-  return align((size_t)(nb * N) * 8) + align((size_t)(nb * R) * 8 + 8) + align((size_t)(slots * N) * 4) +
-         2 * align((size_t)(slots * (2 * (N + g->n_edges) + 2)) * 8);
+  return align((size_t)g->n_ops * 4) + 2 * align((size_t)(2 * (g->n_ops + g->n_edges) + 2) * 8);
 }
 
-int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, void *scratch, int64_t slots, int cus,
-                 int64_t *makespan, int64_t *peak, uint8_t *violation, int64_t *slack, int64_t *sumfin, hipStream_t stream) {
+int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked, int64_t *rows, int64_t *comp,
+                 void *slots, int64_t n_slots, int cus, int64_t *makespan, int64_t *peak, uint8_t *violation,
+                 int64_t *slack, int64_t *sumfin, hipStream_t stream) {
   const GmgView &G = g->view;
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
   const int64_t N = g->n_ops, R = g->n_req, D = g->n_dev;
   const int64_t slot_cap = 2 * (N + g->n_edges) + 2;
-  auto *p = static_cast<unsigned char *>(scratch);
+  auto *p = static_cast<unsigned char *>(slots);
   auto take = [&](size_t bytes) {
     unsigned char *q = p;
-    p += align(bytes);
+    p += align(bytes) * (size_t)n_slots;
     return q;
   };
-  auto *fin = reinterpret_cast<int64_t *>(take((size_t)(nb * N) * 8));
-  auto *comp = reinterpret_cast<int64_t *>(take((size_t)(nb * R) * 8 + 8));
-  auto *bydev = reinterpret_cast<int32_t *>(take((size_t)(slots * N) * 4));
-  auto *gkeys = reinterpret_cast<int64_t *>(take((size_t)(slots * slot_cap) * 8));
-  auto *gvals = reinterpret_cast<int64_t *>(take((size_t)(slots * slot_cap) * 8));
-  // resident waves walk the chunk's verdict bytes for marked candidates
-  SsTimingRec *t = ss_timing_start(SS_KERNEL_SCHEDULE, stream);
-  hipLaunchKernelGGL(schedule_wave, dim3((unsigned)std::min<int64_t>(nb, (int64_t)cus * 16)), dim3(kWave),
-                     schedule_wave_lds(D, R), stream, G, P, nb, fin, comp, Resume(), true, makespan, sumfin, slack,
-                     violation);
-  ss_timing_stop(t, stream);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return hip_fail(err, "schedule launch");
-  err = hipFuncSetAttribute(reinterpret_cast<const void *>(&memory_kernel<false, false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMemLds);
+  auto *bydev = reinterpret_cast<int32_t *>(take((size_t)N * 4));
+  auto *gkeys = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
+  auto *gvals = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
+  const bool lanes = nb > kWaveCandidates && comp;
+  const size_t lane_lds = (size_t)D * kWave * (sizeof(int64_t) + sizeof(uint16_t));
+  hipError_t err = hipSuccess;
+  if (lanes)
+    err = hipFuncSetAttribute(reinterpret_cast<const void *>(&schedule_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lane_lds);
+  if (err == hipSuccess)
+    err = hipFuncSetAttribute(reinterpret_cast<const void *>(&memory_kernel<false, false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMemLds);
   if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
+  // Listed on the device, so that no launch waits for their number: kernels
+  // with nothing to do end at once, and the schedule runs with a wave or a lane
+  // per candidate by that number, not the chunk's.  2,052 ops, a wave for every
+  // marked candidate of a chunk and this: 65,536 candidates all marked 65.8 and
+  // 44.5 ms the whole call, half of them 45.1 and 34.0 ms.
+  SsTimingRec *t = ss_timing_start(SS_KERNEL_SCHEDULE, stream);
+  hipLaunchKernelGGL(list_marked, dim3((unsigned)std::min<int64_t>((nb + 255) / 256, 4 * (int64_t)cus)), dim3(256), 0,
+                     stream, static_cast<const uint8_t *>(violation), nb, marked);
+  hipLaunchKernelGGL(schedule_wave, dim3((unsigned)std::min<int64_t>(nb, (int64_t)cus * 16)), dim3(kWave),
+                     schedule_wave_lds(D, R), stream, G, P, nb, rows, static_cast<int64_t *>(nullptr), Resume(),
+                     static_cast<const uint32_t *>(marked), !lanes, makespan, sumfin, slack, violation);
+  if (lanes)
+    hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave), lane_lds, stream, G,
+                       P, nb, rows, comp, Resume(), static_cast<const uint32_t *>(marked), makespan, sumfin, slack,
+                       violation);
+  ss_timing_stop(t, stream);
+  err = hipGetLastError();
+  if (err != hipSuccess) return hip_fail(err, "schedule launch");
   t = ss_timing_start(SS_KERNEL_MEMORY, stream);
-  hipLaunchKernelGGL((memory_kernel<false, false>), dim3((unsigned)slots), dim3(kMemThreads), kMemLds, stream, G, P, nb,
-                     static_cast<const int64_t *>(fin), static_cast<const int64_t *>(nullptr), bydev, gkeys, gvals,
-                     slot_cap, true, peak, violation);
+  hipLaunchKernelGGL((memory_kernel<false, false>), dim3((unsigned)n_slots), dim3(kMemThreads), kMemLds, stream, G, P, nb,
+                     static_cast<const int64_t *>(rows), static_cast<const int64_t *>(nullptr), bydev, gkeys, gvals,
+                     slot_cap, static_cast<const uint32_t *>(marked), peak, violation);
   ss_timing_stop(t, stream);
   err = hipGetLastError();
   return err == hipSuccess ? SS_OK : hip_fail(err, "memory_kernel launch");

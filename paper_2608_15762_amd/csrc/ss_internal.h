@@ -238,12 +238,15 @@ int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak
                     int64_t *slack, int64_t *sumfin, hipStream_t stream, bool ready_dispatch, bool link_ports,
                     SsWork &W);
 // The candidates marked SS_VIOLATION_RETRY of a chunk of nb (placement rows P),
-// simulated by the general index-order kernels with `slots` workgroups of the
-// memory pass.
-size_t ss_retry_scratch(const ss_gmg *g, int64_t nb, int64_t slots);
-int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, void *scratch, int64_t slots, int cus,
-                 int64_t *makespan,
-                 int64_t *peak, uint8_t *violation, int64_t *slack, int64_t *sumfin, hipStream_t stream);
+// simulated by the general index-order kernels.  marked: nb + 1 words, the
+// first of them zero; rows: int64 finish times [nb][n_ops]; comp: [n_req][nb]
+// int64 for chunks past ss_retry_lanes() candidates, else null; slots: scratch
+// of n_slots workgroups of the memory pass.
+int64_t ss_retry_lanes();
+size_t ss_retry_slot_bytes(const ss_gmg *g);
+int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked, int64_t *rows, int64_t *comp,
+                 void *slots, int64_t n_slots, int cus, int64_t *makespan, int64_t *peak, uint8_t *violation,
+                 int64_t *slack, int64_t *sumfin, hipStream_t stream);
 // Resumption from a captured state (general schedule kernel; the 32-bit
 // memory passes when the GMG has a 32-bit horizon); from may be null or empty.
 int ss_run_simulate_resume(const ss_gmg *g, const ss_state *from, const uint8_t *placements, int64_t B,

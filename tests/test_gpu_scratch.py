@@ -85,3 +85,46 @@ def test_smallest_workspace_of_the_general_kernels(links, layout, monkeypatch):
     with pytest.raises(ss.SSError):
         ss.simulate_batch(h, A, layout=layout, links=links,
                           workspace=torch.empty(lo - 256, dtype=torch.uint8, device="cuda"))
+
+
+def far_graph(n=257, D=5, seed=11, far=3 << 31, **kw):
+    """A graph whose last device is idle from `far` on only (past a 32-bit
+    horizon): a candidate that uses it passes the limit."""
+    g = synth.random_gmg(seed, n_ops=n, n_dev=D, **dict(dict(n_req=3, n_link=2, edge_p=0.3, max_outdeg=2, n_slices=4,
+                                                             slice_scale=400, cap_scale=20_000), **kw))
+    last = slice(int(g.slice_ptr[-2]), int(g.slice_ptr[-1]))
+    g.slice_begin[last] += far
+    g.slice_end[last][:-1] += far
+    return g
+
+
+@pytest.mark.parametrize("scratch", ["pool", "small", "middle"])
+@pytest.mark.parametrize("layout", ["row", "op"])
+@pytest.mark.parametrize("B,share", [(300, 0.5), (17_000, 0.03), (17_000, 0.99), (40_001, 0.6)])
+def test_candidates_past_the_limit(B, share, layout, scratch):
+    """Candidates left to the int64 kernels: few, up to and past the number
+    from which a lane schedules each, in one chunk and in several."""
+    g = far_graph()
+    h = ss.Gmg(g)
+    rng = np.random.default_rng(B)
+    P = rng.integers(0, g.n_dev - 1, (B, g.n_ops)).astype(np.uint8)
+    late = rng.random(B) < share
+    P[late, rng.integers(0, g.n_ops, int(late.sum()))] = g.n_dev - 1
+    P[B // 2, 5] = g.n_dev  # names an unknown device
+    ref = oracle.simulate_batch(g, P, n_threads=8)
+    assert np.array_equal((ref["makespan"] > 1 << 32) & (ref["violation"] != 4), late & (np.arange(B) != B // 2))
+    A = torch.from_numpy(np.ascontiguousarray(P if layout == "row" else P.T)).cuda()
+    lo, hi = ss.workspace_size(h, B, layout=layout)
+    size = {"pool": None, "small": hi // 20, "middle": hi // 3}[scratch]
+    ws = None if size is None else torch.empty(max(lo, size), dtype=torch.uint8, device="cuda")
+    out = ss.simulate_batch(h, A, layout=layout, workspace=ws)
+    torch.cuda.synchronize()
+    same({f: out[f].cpu().numpy() for f in FIELDS}, ref)
+
+
+def test_scratch_past_the_limit():
+    """The int64 kernels reuse the 32-bit ones' scratch: about four bytes a
+    candidate more than the same graph without far windows takes."""
+    near, far = ss.Gmg(far_graph(far=0)), ss.Gmg(far_graph())
+    B = 16_384
+    assert ss.workspace_size(far, B)[1] <= ss.workspace_size(near, B)[1] + 8 * B + 4096
