@@ -2281,6 +2281,36 @@ static void placements_to_op_major(const uint8_t *P, int64_t nb, int64_t N, uint
   }
 }
 
+// The layout that does the most with `bytes` when the memory pass is lds_peaks
+// (plan_of(chunk, workgroups of the memory pass)).  A schedule launch lasts as
+// long for a few candidates as for as many as the chip holds, 0.5 us an op in
+// index order; the memory pass takes 40 to 50 us a candidate and workgroup, but
+// a workgroup's scratch is that of seven candidates (mostly its list of every
+// possible event).  A third of the scratch for workgroups is near the least
+// sum of both for 322 to 10,000 ops; the candidates get the rest, in whole
+// `round`s or waves, and the workgroups what that leaves.  In 128 MiB with a
+// workgroup per candidate and with this split: 4,096 candidates of 10,000 ops
+// 172.8 and 29.0 ms (64.6 with interval records), 16,384 of 2,052 ops 41.3 and
+// 6.5 (22.6), 65,536 of 322 ops 3.9 and 2.0 (4.4).
+template <class PlanOf>
+auto fit_peaks(PlanOf &&plan_of, int64_t max_chunk, int64_t round, const PeaksShape &pk, size_t pk_slot,
+               int64_t bytes) {
+  // the largest x in [lo, hi] whose layout fits; that of lo does
+  auto largest = [&](int64_t lo, int64_t hi, auto &&plan) {
+    while (lo < hi) {
+      const int64_t mid = lo + (hi - lo + 1) / 2;
+      if ((int64_t)plan(mid).total <= bytes) lo = mid;
+      else hi = mid - 1;
+    }
+    return lo;
+  };
+  const int64_t share = std::max<int64_t>(1, std::min(pk.blocks, bytes / 3 / (int64_t)pk_slot));
+  int64_t chunk = largest(1, max_chunk, [&](int64_t c) { return plan_of(c, share); });
+  if (chunk < max_chunk)  // (one that takes the whole batch stays)
+    chunk = chunk >= round ? chunk / round * round : chunk >= kWave ? chunk / kWave * kWave : chunk;
+  return plan_of(chunk, largest(share, pk.blocks, [&](int64_t n) { return plan_of(chunk, n); }));
+}
+
 int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_t *peak, uint8_t *violation,
                          int64_t *slack, int64_t *sumfin, hipStream_t stream, SsWork &W) {
   const GmgView &G = g->view;
@@ -2349,9 +2379,9 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
       if (have < retry_slot) q.sz_slots += align(retry_slot - have);
       q.retry_slots = std::min<int64_t>({(int64_t)cus, chunk, std::max<int64_t>(1, (int64_t)(have / retry_slot))});
     };
-    if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
+    if (pk.ok) {  // sub_cap: workgroups of the memory pass
       q.sub = chunk;
-      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
+      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
       fit_retry(q.sz_slots);
       q.n_ticket = 1;
@@ -2378,14 +2408,17 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     int64_t chunk = budget / std::max<int64_t>(1, per_cand);
     chunk = chunk >= round ? chunk / round * round : std::max<int64_t>(kWave, chunk / kWave * kWave);
     chunk = std::min<int64_t>(chunk, int64_t(65535) * 64);  // transpose grids index 64-candidate tiles in y
-    return plan_of(chunk, std::max<int64_t>(1, kRecordBudget / std::max<int64_t>(1, rec_per_cand)));
+    return plan_of(chunk, pk.ok ? pk.blocks : std::max<int64_t>(1, kRecordBudget / std::max<int64_t>(1, rec_per_cand)));
   };
-  const FastPlan pmin = plan_of(kWave, 1), pref = plan_for_budget(kFastScratchBudget);
-  // the largest layout within `bytes`: the preferred chunk with sub-chunks as
-  // large as fit (down to a sixteenth of the chunk), else smaller chunks (by
-  // whole rounds, then halves), down to the smallest layout
+  const FastPlan pmin = plan_of(1, 1), pref = plan_for_budget(kFastScratchBudget);
+  // the largest layout within `bytes`; with interval records the preferred
+  // chunk with sub-chunks as large as fit (down to a sixteenth of the chunk),
+  // else smaller chunks (by whole rounds, then halves), down to the smallest
+  // layout
   auto plan_fit = [&](int64_t bytes) {
     if ((int64_t)pref.total <= bytes) return pref;
+    if ((int64_t)pmin.total >= bytes) return pmin;
+    if (pk.ok) return fit_peaks(plan_of, pref.chunk, round, pk, pk_slot, bytes);
     int64_t chunk = pref.chunk;
     for (;;) {
       const int64_t lo0 = chunk > kWave ? std::max<int64_t>(1, std::min<int64_t>(pref.sub, chunk / 16)) : 1;
@@ -2400,8 +2433,10 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
         }
         return plan_of(chunk, lo);
       }
-      if (chunk <= kWave) return plan_of(chunk, 1);
-      chunk = chunk > round ? chunk - round : std::max<int64_t>(kWave, chunk / 2 / kWave * kWave);
+      if (chunk <= 1) return pmin;
+      chunk = chunk > round   ? chunk - round
+              : chunk > kWave ? std::max<int64_t>(kWave, chunk / 2 / kWave * kWave)
+                              : chunk / 2;
     }
   };
   // the pool path's budget: up to the preferred layout, within the memory the
@@ -2605,9 +2640,9 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
                           align((size_t)chunk * N * 4) + align((size_t)chunk * N * 2) + align((size_t)chunk * N + 1));
     q.sz_rows = src.op_major ? align((size_t)chunk * N + 1) : 0;
     q.sz_lane = lanes ? align((size_t)chunk * D * 2) + align((size_t)chunk * 4) : 0;
-    if (pk.ok) {  // scratch for every workgroup the device holds; in the smallest chunks sub_cap bounds it
+    if (pk.ok) {  // sub_cap: workgroups of the memory pass
       q.sub = chunk;
-      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, chunk > kWave ? chunk : sub_cap}));
+      q.nslots = std::max<int64_t>(1, std::min({pk.blocks, chunk, sub_cap}));
       q.sz_slots = pk_slot * (size_t)q.nslots;
       q.n_ticket = 1;
       q.sz_tk = align((size_t)kTicketWords * 4);  // every chunk's in turn
@@ -2635,10 +2670,12 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   const int64_t budget_pref = lanes ? kFastScratchBudget : kScratchBudget;
   const Plan ppref = plan_of(std::min<int64_t>(budget_pref / std::max<int64_t>(1, per_cand),
                                                int64_t(65535) * 64),  // transpose grids index 64 candidates in y
-                             sub_pref);
+                             pk.ok ? pk.blocks : sub_pref);
   const Plan pmin = plan_of(1, 1);
   auto plan_fit = [&](int64_t bytes) {
     if ((int64_t)ppref.total <= bytes) return ppref;
+    if ((int64_t)pmin.total >= bytes) return pmin;
+    if (pk.ok) return fit_peaks(plan_of, ppref.chunk, (int64_t)kWave, pk, pk_slot, bytes);
     int64_t chunk = ppref.chunk;
     for (;;) {
       const int64_t lo0 = chunk > kWave ? std::max<int64_t>(1, std::min<int64_t>(ppref.sub, chunk / 16)) : 1;

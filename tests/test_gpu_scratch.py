@@ -56,6 +56,56 @@ def test_ready_scratch_of_many_candidates():
     same(a, oracle.simulate_batch(g, P.cpu().numpy()[idx], dispatch=oracle.READY_ORDER, n_threads=8), idx)
 
 
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+@pytest.mark.parametrize("config,ops,index,ready", [(1, 322, 16_384, 16_384), (2, 2052, 4096, 2048),
+                                                    (3, 10_000, 512, 512)])
+def test_chunks_of_the_fixed_array(config, ops, index, ready, dispatch):
+    """A schedule launch lasts about as long for one candidate as for as many
+    as the chip holds: the fixed array's chunks are no smaller than those the
+    interval records' layout had (2.5 schedule launches' worth of them here)."""
+    g = synth.build_gmg(config)
+    assert g.n_ops == ops
+    h = ss.Gmg(g)
+    chunk = index if dispatch == "index" else ready
+    B = chunk * 5 // 2
+    P = torch.from_numpy(synth.placements(g, config, 0, B)).cuda()
+    noalloc(h, P[:64], dispatch=dispatch)
+    ss.kernel_timing(True)
+    a = noalloc(h, P, dispatch=dispatch)
+    n, _ = ss.kernel_time(0)
+    ss.kernel_timing(False)
+    assert 1 <= n <= 3
+    idx = np.unique(np.linspace(0, B - 1, 40).astype(np.int64))
+    same(a, oracle.simulate_batch(g, P.cpu().numpy()[idx], n_threads=8,
+                                  dispatch=oracle.READY_ORDER if dispatch == "ready" else 0), idx)
+
+
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+@pytest.mark.parametrize("n,outdeg", [(33, 2), (321, 3), (11_901, 2)])
+def test_smallest_workspace_holds_one_candidate(n, outdeg, dispatch):
+    """Both memory passes, finish rows padded to whole groups of eight: one
+    candidate's rows and records are enough."""
+    g = synth.random_gmg(7, n_ops=n, n_dev=3, n_req=2, n_link=2, edge_p=0.15, max_outdeg=outdeg,
+                         n_slices=4, slice_scale=400, cap_scale=20_000)
+    h = ss.Gmg(g)
+    B = 70 if n < 1000 else 9
+    P = np.random.default_rng(n).integers(0, 3, (B, n)).astype(np.uint8)
+    ref = oracle.simulate_batch(g, P, dispatch=oracle.READY_ORDER if dispatch == "ready" else 0, n_threads=8)
+    E = len(g.pred_idx)
+    for layout in ("row", "op"):
+        A = torch.from_numpy(np.ascontiguousarray(P if layout == "row" else P.T)).cuda()
+        lo, hi = ss.workspace_size(h, B, layout=layout, dispatch=dispatch)
+        # 64 candidates' finish times alone are 512 bytes an op
+        assert lo <= 200 * (n + E) + 16 * 1024
+        for size in (lo, lo + (hi - lo) // 100, lo + (hi - lo) // 3, hi - 256):
+            out = ss.simulate_batch(h, A, layout=layout, dispatch=dispatch,
+                                    workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+            torch.cuda.synchronize()
+            same({f: out[f].cpu().numpy() for f in FIELDS}, ref)
+    if n == 33 and dispatch == "index":  # what 64 candidates with interval records took
+        assert ss.workspace_size(h, 64)[0] <= 23_552
+
+
 @pytest.mark.parametrize("links", ["latency", "ports"])
 @pytest.mark.parametrize("layout", ["row", "op"])
 def test_smallest_workspace_of_the_general_kernels(links, layout, monkeypatch):
