@@ -2377,7 +2377,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     auto fit_retry = [&](size_t have) {  // have: scratch of the memory pass
       if (!retry) return;
       if (have < retry_slot) q.sz_slots += align(retry_slot - have);
-      q.retry_slots = std::min<int64_t>({(int64_t)cus, chunk, std::max<int64_t>(1, (int64_t)(have / retry_slot))});
+      q.retry_slots = std::min<int64_t>({ss_retry_blocks(g, cus, chunk), chunk, std::max<int64_t>(1, (int64_t)(have / retry_slot))});
     };
     if (pk.ok) {  // sub_cap: workgroups of the memory pass
       q.sub = chunk;

@@ -37,10 +37,9 @@
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kMemWaves = 16;                     // waves of a memory-pass workgroup
-constexpr int kMemThreads = kMemWaves * kWave;
+constexpr int kMemWaves = 16;                     // waves of the memory pass on a CU, in workgroups of 4 to 16
 constexpr int kMemCap = 512;                      // endpoints a wave sorts in its share of the LDS
-constexpr size_t kMemLds = (size_t)kMemWaves * kMemCap * 16;  // keys and deltas: 128 KB
+constexpr size_t mem_lds(int64_t waves) { return (size_t)waves * kMemCap * 16; }  // keys and deltas, 8 KB a wave
 constexpr int64_t kFinBudget = int64_t(16) << 30; // bytes of finish-time scratch per chunk
 
 __device__ __forceinline__ int64_t imax(int64_t a, int64_t b) { return a > b ? a : b; }
@@ -1060,8 +1059,7 @@ struct WaveTeam {
   __device__ void sync() const { wave_fence(); }
 };
 struct BlockTeam {
-  int id;  // thread
-  static constexpr int size = kMemThreads;
+  int id, size;  // thread, threads
   __device__ void sync() const { __syncthreads(); }
 };
 
@@ -1076,7 +1074,7 @@ __device__ void sort_pairs(const Team &team, KP keys, VP vals, int n) {
   const int half_total = 1 << (lg - 1);
   for (int kb = 1; kb <= lg; ++kb) {
     const int k = 1 << kb, hmask = (k >> 1) - 1;
-    for (int q = team.id; q < half_total; q += Team::size) {
+    for (int q = team.id; q < half_total; q += team.size) {
       const int base = (q >> (kb - 1)) << kb, off = q & hmask;
       const int l = base + k - 1 - off;
       if (l < n) compare_swap(keys, vals, base + off, l);
@@ -1084,7 +1082,7 @@ __device__ void sort_pairs(const Team &team, KP keys, VP vals, int n) {
     team.sync();
     for (int jb = kb - 2; jb >= 0; --jb) {
       const int j = 1 << jb;
-      for (int q = team.id; q < half_total; q += Team::size) {
+      for (int q = team.id; q < half_total; q += team.size) {
         const int i = ((q >> jb) << (jb + 1)) + (q & (j - 1));
         if (i + j < n) compare_swap(keys, vals, i, i + j);
       }
@@ -1117,8 +1115,8 @@ __device__ int64_t max_prefix_sum(VP vals, int n, int lane) {
 // values per wave.  Every thread gets the result.
 template <class VP>
 __device__ int64_t max_prefix_block(VP vals, int n, int64_t *part) {
-  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-  const int per = (n + kMemThreads - 1) / kMemThreads, lo = min(tid * per, n), hi = min(lo + per, n);
+  const int T = blockDim.x, W = T / kWave, tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  const int per = (n + T - 1) / T, lo = min(tid * per, n), hi = min(lo + per, n);
   int64_t s = 0, best = 0;
   for (int i = lo; i < hi; ++i) {
     s += vals[i];
@@ -1135,9 +1133,9 @@ __device__ int64_t max_prefix_block(VP vals, int n, int64_t *part) {
   for (int k = 0; k < w; ++k) before += part[k];
   best = imax(0, before + best);
   for (int o = kWave / 2; o >= 1; o >>= 1) best = imax(best, __shfl_xor(best, o, kWave));
-  if (lane == 0) part[kMemWaves + w] = best;
+  if (lane == 0) part[W + w] = best;
   __syncthreads();
-  for (int k = 0; k < kMemWaves; ++k) best = imax(best, part[kMemWaves + k]);
+  for (int k = 0; k < W; ++k) best = imax(best, part[W + k]);
   __syncthreads();
   return best;
 }
@@ -1148,18 +1146,19 @@ __device__ int64_t max_prefix_block(VP vals, int n, int64_t *part) {
 // (a batch placed whole on one device) is evaluated by the whole workgroup in
 // all of the LDS, and beyond that in the workgroup's global buffer.
 // Bound: the waves' chains of dependent loads and LDS round trips, so all
-// sixteen waves of a CU work on devices of one candidate instead of four on
-// candidates of their own (240 candidates of 2,000 ops on 128 devices 1.18 ms
-// before, 16,384 of 2,052 ops on 32 devices 8.64 ms).
+// sixteen waves of a CU work on devices of one to four candidates (mem_waves)
+// where four had a candidate each (240 candidates of 2,000 ops on 128 devices
+// 1.18 ms with those, 16,384 of 2,052 ops on 32 devices 8.64 ms).
 template <bool kReady, bool kPorts>
-__global__ __launch_bounds__(kMemThreads) void memory_kernel(
+__global__ __launch_bounds__(kMemWaves * kWave) void memory_kernel(
     const GmgView G, const uint8_t *__restrict__ P, int64_t nb, const int64_t *__restrict__ fin,
     const int64_t *__restrict__ arr, int32_t *__restrict__ bydev_all, int64_t *__restrict__ gkeys_all,
     int64_t *__restrict__ gvals_all, int64_t slot_cap, const uint32_t *__restrict__ marked, int64_t *__restrict__ peak,
     uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  int64_t *skeys = reinterpret_cast<int64_t *>(lds_raw);  // [kMemWaves * kMemCap]
-  int64_t *svals = skeys + kMemWaves * kMemCap;
+  const int T = blockDim.x, W = T / kWave, tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  int64_t *skeys = reinterpret_cast<int64_t *>(lds_raw);  // [W * kMemCap]
+  int64_t *svals = skeys + W * kMemCap;
   __shared__ int64_t part[2 * kMemWaves];
   __shared__ int32_t start[257];
   __shared__ int32_t fillp[256];
@@ -1167,7 +1166,6 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
   __shared__ int32_t viol, n_large;
   __shared__ uint8_t large[256];  // devices left to the workgroup
   const int D = G.n_dev, N = G.n_ops;
-  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   int32_t *bydev = bydev_all + (int64_t)blockIdx.x * N;
   int64_t *gkeys = gkeys_all + (int64_t)blockIdx.x * slot_cap;
   int64_t *gvals = gvals_all + (int64_t)blockIdx.x * slot_cap;
@@ -1178,15 +1176,15 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
     const int64_t *frow = fin + i * N;
     if (violation[c] & SS_VIOLATION_INVALID) {
       if (peak)
-        for (int d = tid; d < D; d += kMemThreads) peak[c * D + d] = 0;
+        for (int d = tid; d < D; d += T) peak[c * D + d] = 0;
       continue;
     }
     // group the ops by device (order inside a device is irrelevant: the
     // endpoints are sorted afterwards)
-    for (int d = tid; d <= D; d += kMemThreads) start[d] = 0;
+    for (int d = tid; d <= D; d += T) start[d] = 0;
     if (tid == 0) viol = n_large = 0;
     __syncthreads();
-    for (int v = tid; v < N; v += kMemThreads) atomicAdd(&start[prow[v]], 1);
+    for (int v = tid; v < N; v += T) atomicAdd(&start[prow[v]], 1);
     __syncthreads();
     if (w == 0) {
       int carry = 0;
@@ -1203,12 +1201,12 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
       if (lane == 0) start[D] = carry;
     }
     __syncthreads();
-    for (int v = tid; v < N; v += kMemThreads) bydev[atomicAdd(&fillp[prow[v]], 1)] = v;
+    for (int v = tid; v < N; v += T) bydev[atomicAdd(&fillp[prow[v]], 1)] = v;
     __syncthreads();
 
     int64_t *wkeys = skeys + w * kMemCap, *wvals = svals + w * kMemCap;
     const WaveTeam wave{lane};
-    for (int e = w; e < D; e += kMemWaves) {
+    for (int e = w; e < D; e += W) {
       const int lo = start[e], hi = start[e + 1];
       int64_t pk = 0;
       if (hi > lo) {
@@ -1243,7 +1241,7 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
       auto gather = [&](int64_t *keys, int64_t *vals, int cap) {
         if (tid == 0) count[kMemWaves] = 0;
         __syncthreads();
-        for (int q = lo + tid; q < hi; q += kMemThreads)
+        for (int q = lo + tid; q < hi; q += T)
           op_events<kReady, kPorts>(G, prow, frow, bydev[q], e, arr, nb, c, [&](int64_t key, int64_t val) {
             const int at = atomicAdd(&count[kMemWaves], 1);
             if (at < cap) {
@@ -1254,10 +1252,10 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
         __syncthreads();
         return count[kMemWaves];
       };
-      const BlockTeam team{tid};
+      const BlockTeam team{tid, T};
       int64_t pk;
-      int total = gather(skeys, svals, kMemWaves * kMemCap);
-      if (total <= kMemWaves * kMemCap) {
+      int total = gather(skeys, svals, W * kMemCap);
+      if (total <= W * kMemCap) {
         sort_pairs(team, skeys, svals, total);
         pk = max_prefix_block(svals, total, part);
       } else {
@@ -1276,6 +1274,25 @@ __global__ __launch_bounds__(kMemThreads) void memory_kernel(
     __syncthreads();
   }
 }
+
+// Waves of a memory-pass workgroup for nb candidates, and how many such
+// workgroups fill the chip.  One candidate per CU when there are no more than
+// CUs, and with 16 waves for each; two and four per CU beyond, whose waves
+// share what few devices leave to do, unless a device's average share of the
+// endpoints then outgrows the LDS.  Measured, 8,192 candidates with 16 waves
+// each and by this rule: 32 ops on one device 268 and 73 us, 300 ops on two
+// 1,392 and 443, 1,000 ops on eight 4,081 and 1,825, 3,000 ops on 32 4,252 and
+// 3,981; 3,000 ops on one device 5.2 ms with 16 waves and 9.1 with four, on
+// three 7.0 with 16, 5.2 with eight and 16.2 with four.  240 candidates of
+// 1,000 ops on 32 devices: 56 us with 16 waves, 146 with four.
+int64_t mem_waves(const ss_gmg *g, int cus, int64_t nb) {
+  const int64_t D = std::max<int64_t>(1, g->n_dev);
+  const int64_t share = 2 * (g->n_ops + g->n_edges * (D - 1) / D) / D;
+  int64_t w = nb <= cus ? kMemWaves : nb <= 2 * (int64_t)cus ? kMemWaves / 2 : kMemWaves / 4;
+  while (w < kMemWaves && w * kMemCap < share) w *= 2;
+  return w;
+}
+int64_t mem_blocks(int cus, int64_t waves) { return (int64_t)cus * (kMemWaves / waves); }
 
 int hip_fail(hipError_t err, const char *what) {
   return ss_set_error(err == hipErrorOutOfMemory ? SS_ERR_OOM : SS_ERR_DEVICE,
@@ -1332,7 +1349,7 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
   auto plan_of = [&](int64_t chunk) {
     Plan q{};
     q.chunk = chunk = std::min<int64_t>(std::max<int64_t>(1, chunk), B);
-    q.nslots = std::max<int64_t>(1, std::min<int64_t>((int64_t)cus, chunk));
+    q.nslots = std::max<int64_t>(1, std::min(mem_blocks(cus, mem_waves(g, cus, chunk)), chunk));
     q.sz_fin = align((size_t)chunk * N * 8 + 8);
     q.sz_comp = align((size_t)chunk * R * 8 + 8);
     q.sz_miss = ready ? align((size_t)chunk * N * 4 + 4) : 0;
@@ -1479,16 +1496,17 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
                               ports ? static_cast<const int64_t *>(arr) : nullptr, nb);
       continue;
     }
-    const int64_t grid = std::min<int64_t>(nb, nslots);
+    // (the last chunk, with fewer candidates, may take more waves and fewer workgroups)
+    const int64_t mw = mem_waves(g, cus, nb), grid = std::min({nb, nslots, mem_blocks(cus, mw)});
     SsTimingRec *t_mem = ss_timing_start(SS_KERNEL_MEMORY, stream);
     auto *mem_fn = ready ? &memory_kernel<true, false> : ports ? &memory_kernel<false, true> : &memory_kernel<false, false>;
     err = hipFuncSetAttribute(reinterpret_cast<const void *>(mem_fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kMemLds);
+                              (int)mem_lds(mw));
     if (err != hipSuccess) {
       rc = hip_fail(err, "hipFuncSetAttribute");
       break;
     }
-    hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3(kMemThreads), kMemLds, stream, G, Pc, nb,
+    hipLaunchKernelGGL(mem_fn, dim3((unsigned)grid), dim3((unsigned)(mw * kWave)), mem_lds(mw), stream, G, Pc, nb,
                        static_cast<const int64_t *>(fin), static_cast<const int64_t *>(arr), bydev, gkeys, gvals,
                        slot_cap, static_cast<const uint32_t *>(nullptr), peak ? peak + b0 * D : nullptr,
                        violation + b0);
@@ -1504,6 +1522,12 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
 }
 
 int64_t ss_retry_lanes() { return kWaveCandidates; }
+
+// Few candidates of a chunk are marked as a rule: 16 waves for each, except on
+// so few devices that most of them would idle.
+static int64_t retry_waves(const ss_gmg *g, int cus, int64_t nb) { return mem_waves(g, cus, g->n_dev < 8 ? nb : 1); }
+
+int64_t ss_retry_blocks(const ss_gmg *g, int cus, int64_t nb) { return mem_blocks(cus, retry_waves(g, cus, nb)); }
 
 size_t ss_retry_slot_bytes(const ss_gmg *g) {
   auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
@@ -1527,6 +1551,7 @@ int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked
   auto *gkeys = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
   auto *gvals = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
   const bool lanes = nb > kWaveCandidates && comp;
+  const int64_t mw = retry_waves(g, cus, nb);
   const size_t lane_lds = (size_t)D * kWave * (sizeof(int64_t) + sizeof(uint16_t));
   hipError_t err = hipSuccess;
   if (lanes)
@@ -1534,7 +1559,7 @@ int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lane_lds);
   if (err == hipSuccess)
     err = hipFuncSetAttribute(reinterpret_cast<const void *>(&memory_kernel<false, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMemLds);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)mem_lds(mw));
   if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute");
   // Listed on the device, so that no launch waits for their number: kernels
   // with nothing to do end at once, and the schedule runs with a wave or a lane
@@ -1555,8 +1580,8 @@ int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked
   err = hipGetLastError();
   if (err != hipSuccess) return hip_fail(err, "schedule launch");
   t = ss_timing_start(SS_KERNEL_MEMORY, stream);
-  hipLaunchKernelGGL((memory_kernel<false, false>), dim3((unsigned)n_slots), dim3(kMemThreads), kMemLds, stream, G, P, nb,
-                     static_cast<const int64_t *>(rows), static_cast<const int64_t *>(nullptr), bydev, gkeys, gvals,
+  hipLaunchKernelGGL((memory_kernel<false, false>), dim3((unsigned)n_slots), dim3((unsigned)(mw * kWave)), mem_lds(mw),
+                     stream, G, P, nb, static_cast<const int64_t *>(rows), static_cast<const int64_t *>(nullptr), bydev, gkeys, gvals,
                      slot_cap, static_cast<const uint32_t *>(marked), peak, violation);
   ss_timing_stop(t, stream);
   err = hipGetLastError();

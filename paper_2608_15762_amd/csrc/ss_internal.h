@@ -243,6 +243,7 @@ int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak
 // int64 for chunks past ss_retry_lanes() candidates, else null; slots: scratch
 // of n_slots workgroups of the memory pass.
 int64_t ss_retry_lanes();
+int64_t ss_retry_blocks(const ss_gmg *g, int cus, int64_t nb);  // workgroups the memory pass is best given
 size_t ss_retry_slot_bytes(const ss_gmg *g);
 int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked, int64_t *rows, int64_t *comp,
                  void *slots, int64_t n_slots, int cus, int64_t *makespan, int64_t *peak, uint8_t *violation,

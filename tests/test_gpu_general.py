@@ -89,3 +89,16 @@ def test_endpoints(n, D):
     P[1, n // 2:] = D - 1
     P[2, ::3] = D - 1
     check(g, P)
+
+
+@pytest.mark.parametrize("B", [256, 257, 513])  # sixteen, eight and four waves to a candidate
+@pytest.mark.parametrize("n,D", [(61, 1), (128, 1), (300, 1), (500, 1), (300, 3), (700, 3), (2000, 3), (700, 9)])
+def test_team_sizes(n, D, B):
+    """Workgroups of every size the memory pass has, with devices whose
+    endpoints fit a wave's share of its LDS, all of it, or the global buffer:
+    a third of the candidates on one device whole."""
+    print(f"{B} candidates of {n} ops on {D} devices", flush=True)
+    g = graph(12, n, D=D, edge_p=0.2, cap_scale=100_000)
+    P = batch(g, B)
+    P[::3] = D - 1
+    check(g, P)
