@@ -245,9 +245,13 @@ int ss_simulate_chunking(const ss_gmg *g, int64_t B, int layout, int64_t *chunk,
  * flags computes its simulated times in (Sec. 3.3.2-3.3.3; the results are
  * the same either way): 32 when the loader proved that every time of the GMG
  * fits in 32 bits and the call takes the 32-bit kernels (index-order or
- * ready-time dispatch; byte sums are then 32-bit too when their bound allows
- * it, else 64-bit), 64 on the general path (a GMG beyond 32 bits, a running
- * schedule's state, SS_LINK_PORTS, or SS_PATH=generic in the environment).
+ * ready-time dispatch, and SS_LINK_PORTS on graphs of at most two successors
+ * per op, one device class and two link classes whose memory pass fits the
+ * LDS; byte sums are then 32-bit too when their bound allows it, else 64-bit),
+ * 64 when some candidates' times may be computed in 64 bits (a GMG beyond 32
+ * bits, even where the candidates that stay below are simulated on the 32-bit
+ * kernels) and on the general path (a running schedule's state, SS_LINK_PORTS
+ * on other graphs, or SS_PATH=generic in the environment).
  * Launches nothing.  Errors: SS_ERR_INVALID_ARG (g or bits NULL, an unknown
  * flag), SS_ERR_DEVICE, SS_ERR_UNSUPPORTED (as ss_simulate_batch would).
  */

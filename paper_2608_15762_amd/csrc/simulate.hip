@@ -1613,7 +1613,8 @@ static int simulate_route(const ss_gmg *g, bool ready_dispatch, bool link_ports,
   const char *path = std::getenv("SS_PATH");
   if (path && std::strcmp(path, "fast") == 0 && (!fast_ok || link_ports))
     return ss_set_error(SS_ERR_UNSUPPORTED, "SS_PATH=fast but this GMG or dispatch needs the general path");
-  // transfer ports: the event-driven schedule of the general path, whose
+  // transfer ports: the 32-bit event kernel when the GMG is of the packed form
+  // (ss_ports32_ok), else the event-driven schedule of the general path, whose
   // memory pass is the 32-bit one when the GMG fits the branch-free interval
   // writer (SS_PATH=generic: the general kernels throughout)
   const bool force_generic = path && std::strcmp(path, "generic") == 0;
@@ -1626,8 +1627,11 @@ static int simulate_route(const ss_gmg *g, bool ready_dispatch, bool link_ports,
 int ss_simulate_time_bits_of(const ss_gmg *g, bool ready_dispatch, bool link_ports, int *bits) {
   bool generic = false, ports_mem_fast = false;
   const int rc = simulate_route(g, ready_dispatch, link_ports, &generic, &ports_mem_fast);
-  if (rc == SS_OK) *bits = generic || !g->view.time32 ? 64 : 32;
-  return rc;
+  if (rc != SS_OK) return rc;
+  // past a 32-bit horizon any candidate may be left to the int64 kernels
+  const bool narrow = generic ? ports_mem_fast && ss_ports32_ok(g) : g->view.time32 != 0;
+  *bits = narrow ? 32 : 64;
+  return SS_OK;
 }
 
 int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,

@@ -191,3 +191,11 @@ def test_time_bits_follow_the_path(dev, monkeypatch):
     g.slice_begin = g.slice_begin + shift
     g.slice_end = np.where(g.slice_end == synth.TIME_INF, synth.TIME_INF, g.slice_end + shift)
     assert ss.time_bits(ss.Gmg(g)) == 64
+    # transfer ports: 32 bits on packed graphs whose memory pass fits the LDS
+    h = ss.Gmg(synth.build_gmg(2))
+    assert ss.time_bits(h, links="ports") == 32
+    monkeypatch.setenv("SS_PATH", "generic")
+    assert ss.time_bits(h, links="ports") == 64
+    monkeypatch.delenv("SS_PATH")
+    wide = ss.Gmg(random_gmg(3, n_ops=90, n_dev=4, n_class=2, n_link=2, max_outdeg=2))
+    assert ss.time_bits(wide, links="ports") == 64 and ss.time_bits(wide) == 32
