@@ -19,13 +19,12 @@ constexpr i128 kSumLimit = (i128)1 << 63;
 // The arrays of one device allocation at 256-byte aligned offsets: add()
 // records where each goes, pack() copies them once into a buffer of the
 // calling thread that its later loads reuse (a load has uploaded it before it
-// returns); gaps and arrays without a source are zero, reserved ones are the
-// caller's to fill after pack().  The sources must stay alive until pack().
+// returns); gaps and arrays without a source are zero.  The sources must stay
+// alive until pack().
 struct Packer {
   struct Part {
     const void *src;
     size_t bytes, off;
-    bool reserved = false;
   };
   std::vector<Part> parts;
   size_t size = 0;
@@ -39,18 +38,13 @@ struct Packer {
   size_t add(const std::vector<T> &v) {
     return add(v.data(), v.size() * sizeof(T));
   }
-  size_t reserve(size_t bytes) {
-    const size_t off = add(nullptr, bytes);
-    parts.back().reserved = true;
-    return off;
-  }
-  unsigned char *pack() const {
+  const unsigned char *pack() const {
     static thread_local std::vector<unsigned char> buf;
     if (buf.size() < size) buf.resize(size);
     size_t end = 0;
     for (const Part &p : parts) {
       if (p.off > end) std::memset(buf.data() + end, 0, p.off - end);
-      if (p.bytes && !p.reserved) {
+      if (p.bytes) {
         if (p.src) std::memcpy(buf.data() + p.off, p.src, p.bytes);
         else std::memset(buf.data() + p.off, 0, p.bytes);
       }
@@ -460,7 +454,7 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
         time_limit = (uint32_t)limit;
     }
     const bool tab32 = time32 || time_limit > 0;
-    std::vector<uint32_t> dur32, xfer32, sb32, se32, rel32, meta, lbits, bytes32, succ2, succ2_pe;
+    std::vector<uint32_t> dur32, xfer32, rel32, meta, lbits, bytes32, succ2, succ2_pe;
     bool records = false;  // of the ready-time lanes
     int64_t rwidth = 0;
     std::vector<uint8_t> lgrp;
@@ -584,21 +578,13 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
       }
       xfer32.assign(xfer.begin(), xfer.end());
       rel32.assign(d->release, d->release + R);
-      sb32.assign(S + 1, UINT32_MAX);  // spare entry: read ahead, never used
-      se32.assign(S + 1, UINT32_MAX);
-
-      for (int64_t k = 0; k < S; ++k) {
-        // with a limit, a slice that begins past it is an open one at the
-        // limit, and one that ends past 32 bits is open: what is placed there
-        // finishes past the limit or is placed as without it
-        const bool past = time_limit > 0 && d->slice_begin[k] >= (int64_t)time_limit;
-        sb32[k] = past ? time_limit : (uint32_t)d->slice_begin[k];
-        se32[k] = past || d->slice_end[k] >= (int64_t)UINT32_MAX ? UINT32_MAX : (uint32_t)d->slice_end[k];
-      }
-      // time -> slice lookup: about 128K buckets in all (at least 64 per device)
+      // time -> slice lookup: about 128K buckets in all (at least 64 per
+      // device) up to the last end of a slice that is not open in 32 bits
       uint32_t max_end = 0;
-      for (int64_t k = 0; k < S; ++k)
-        if (se32[k] != UINT32_MAX) max_end = std::max(max_end, se32[k]);
+      for (int64_t k = 0; k < S; ++k) {
+        const bool past = time_limit > 0 && d->slice_begin[k] >= (int64_t)time_limit;
+        if (!past && d->slice_end[k] < (int64_t)UINT32_MAX) max_end = std::max(max_end, (uint32_t)d->slice_end[k]);
+      }
       const int64_t nb_target = std::max<int64_t>(64, 131072 / D);
       while (((int64_t)max_end >> lut_shift) + 2 > nb_target) ++lut_shift;
       lut_nb = ((int64_t)max_end >> lut_shift) + 2;
@@ -625,12 +611,24 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     const size_t o_link = pk.add(d->link_class, D * D);
     const size_t o_done = d->done_fin ? pk.add(d->done_fin, N * sizeof(int64_t)) : 0;
     const size_t o_issue = d->issue_at ? pk.add(d->issue_at, N * sizeof(int64_t)) : 0;
-    const size_t o_dur32 = pk.add(dur32), o_xfer32 = pk.add(xfer32), o_sb32 = pk.add(sb32), o_se32 = pk.add(se32),
+    const size_t o_dur32 = pk.add(dur32), o_xfer32 = pk.add(xfer32), 
                  o_rel32 = pk.add(rel32), o_meta = pk.add(meta), o_lbits = pk.add(lbits), o_b32 = pk.add(bytes32),
-                 o_succ2 = pk.add(succ2), o_succ2_pe = pk.add(succ2_pe), o_lutk = pk.reserve((size_t)D * lut_nb * 4),
-                 o_lutw = pk.reserve((size_t)D * lut_nb * 16), o_lgrp = pk.add(lgrp),
-                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops), o_rrec = pk.reserve(records ? (size_t)N * 48 : 0);
-    pk.add(nullptr, 256);  // tail padding
+                 o_succ2 = pk.add(succ2), o_succ2_pe = pk.add(succ2_pe), o_lgrp = pk.add(lgrp),
+                 o_src = pk.add(src_keys), o_src_ops = pk.add(src_ops);
+    pk.add(nullptr, 256);  // padding
+    // past what is uploaded, made by the device from the rest: the 32-bit
+    // slices, their lookup (2.6 MB) and the ready-time records (48 bytes an
+    // op).  All made here and uploaded, a load of 50,000 ops took 2.40 ms and
+    // one of 2,052 ops with a day of idle windows 0.39 ms (1.96 and 0.16 ms
+    // before there were records and 32-bit tables of such horizons); now 1.73
+    // and 0.23 ms.
+    Packer made;
+    made.size = pk.size;
+    const size_t o_lutk = made.add(nullptr, (size_t)D * lut_nb * 4), o_lutw = made.add(nullptr, (size_t)D * lut_nb * 16),
+                 o_sb32 = made.add(nullptr, tab32 ? (size_t)(S + 1) * 4 : 0),
+                 o_se32 = made.add(nullptr, tab32 ? (size_t)(S + 1) * 4 : 0),
+                 o_rrec = made.add(nullptr, records ? (size_t)N * 48 : 0);
+    made.add(nullptr, 256);
 
     ss_gmg *g = new ss_gmg();
     if (hipGetDevice(&g->device) != hipSuccess) {
@@ -639,70 +637,19 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     }
     g->aux = ss_device_aux(g->device);
     g->pool = g->aux ? ss_device_pool(g->device) : nullptr;
-    unsigned char *packed = pk.pack();
-    // The lookup (2.6 MB) and the records (48 bytes an op) in place: in arrays of
-    // their own first (the lookup only) a load of 322 ops took 0.20 ms, now 0.16 ms.
-    if (records) {
-      auto *q = reinterpret_cast<uint32_t *>(packed + o_rrec);
-      for (int64_t v = 0; v < N; ++v, q += 12) {
-        uint32_t other[2] = {0xFFFFu, 0xFFFFu}, rel[2] = {0, 0}, x[4] = {0, 0, 0, 0};
-        for (int64_t i = 0; i < outdeg[v]; ++i) {
-          const int64_t y = succ_idx[succ_ptr[v] + i], e0 = d->pred_ptr[y];
-          if (d->pred_ptr[y + 1] - e0 == 2) {
-            const int64_t u = d->pred_idx[e0] == v ? d->pred_idx[e0 + 1] : d->pred_idx[e0];
-            other[i] = (uint32_t)u;
-            x[2 * i] = (uint32_t)xfer[u * K];
-            x[2 * i + 1] = (uint32_t)xfer[u * K + K - 1];
-          }
-          rel[i] = (uint32_t)d->release[d->op_req[y]];
-        }
-        const uint32_t rec[12] = {C == 1 ? (uint32_t)d->dur[v] : 0u,
-                                  (uint32_t)xfer[v * K],
-                                  (uint32_t)xfer[v * K + K - 1],
-                                  succ2[v],
-                                  other[0] | other[1] << 16,
-                                  rel[0],
-                                  rel[1],
-                                  (uint32_t)d->op_req[v],
-                                  x[0],
-                                  x[1],
-                                  x[2],
-                                  x[3]};
-        std::memcpy(q, rec, sizeof rec);
-      }
-    }
-    if (tab32) {
-      auto *lutk = reinterpret_cast<uint32_t *>(packed + o_lutk), *lutw = reinterpret_cast<uint32_t *>(packed + o_lutw);
-      for (int64_t x = 0; x < D; ++x) {
-        const int64_t a = d->slice_ptr[x], b = d->slice_ptr[x + 1];
-        int64_t k = 0;
-        for (int64_t bk = 0; bk < lut_nb; ++bk) {
-          const uint64_t t0 = (uint64_t)bk << lut_shift;
-          while (a + k < b - 1 && (uint64_t)se32[a + k] < t0) ++k;  // the last slice is open
-          const size_t e = (size_t)(x * lut_nb + bk);
-          lutk[e] = (uint32_t)k;
-          lutw[4 * e] = sb32[a + k];
-          lutw[4 * e + 1] = se32[a + k];
-          lutw[4 * e + 2] = sb32[a + k + 1];  // spare entry past the last slice
-          lutw[4 * e + 3] = se32[a + k + 1];
-        }
-      }
-    }
-    int arc = g->pool ? ss_pool_alloc(g->device, pk.size, g->aux, &g->dev_mem) : SS_ERR_DEVICE;
-    hipError_t e = hipSuccess;
-    if (arc == SS_OK) {
-      e = hipMemcpyAsync(g->dev_mem, packed, pk.size, hipMemcpyHostToDevice, g->aux);
-      if (e == hipSuccess) e = hipStreamSynchronize(g->aux);
-      if (e != hipSuccess) arc = ss_set_error(SS_ERR_DEVICE, "copying the staged GMG failed");
-    }
-    if (arc != SS_OK) {
+    const unsigned char *packed = pk.pack();
+    int arc = g->pool ? ss_pool_alloc(g->device, made.size, g->aux, &g->dev_mem) : SS_ERR_DEVICE;
+    auto fail = [&](int rc) {
       if (g->aux) {
         ss_pool_free(g->dev_mem, g->aux);
         (void)hipStreamSynchronize(g->aux);
       }
       delete g;
-      return arc;
-    }
+      return rc;
+    };
+    if (arc != SS_OK) return fail(arc);
+    if (hipMemcpyAsync(g->dev_mem, packed, pk.size, hipMemcpyHostToDevice, g->aux) != hipSuccess)
+      return fail(ss_set_error(SS_ERR_DEVICE, "copying the staged GMG failed"));
     auto *base = static_cast<unsigned char *>(g->dev_mem);
     GmgView &V = g->view;
     V.n_ops = (int32_t)N;
@@ -758,6 +705,9 @@ extern "C" int ss_gmg_load(const ss_gmg_desc *d, ss_gmg **out) {
     V.lut_w = reinterpret_cast<const uint4 *>(base + o_lutw);
     V.lut_nb = (int32_t)lut_nb;
     V.lut_shift = (int32_t)lut_shift;
+    hipError_t e = tab32 ? ss_make_tables(V, S, g->aux) : hipSuccess;
+    if (e == hipSuccess) e = hipStreamSynchronize(g->aux);
+    if (e != hipSuccess) return fail(ss_set_error(SS_ERR_DEVICE, "copying the staged GMG failed"));
     g->n_ops = N;
     g->n_edges = E;
     g->n_dev = D;

@@ -1123,6 +1123,67 @@ const void *ready_ops_fn(bool one_class, bool shift) {
                : reinterpret_cast<const void *>(&ready_ops<kSlots, false, false>);
 }
 
+// The tables that follow from the rest of a GMG, an entry, slice or op per
+// thread: the slice lookup, entry [d][b] the first slice of d that ends at or
+// after b << lut_shift (its last one if none does) and the next, the 32-bit
+// slices, and the records of the ready-time lanes.
+__global__ __launch_bounds__(256) void make_tables(const GmgView G, int64_t S) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n_lut = (int64_t)G.n_dev * G.lut_nb;
+  // slice k in 32 bits, and a spare entry past the last (read ahead, never
+  // used).  With a time limit, a slice that begins past it is an open one at
+  // the limit, and one that ends past 32 bits is open: what is placed there
+  // finishes past the limit or is placed as without it.
+  auto slice = [&](int64_t k) -> uint2 {
+    if (k >= S) return make_uint2(kInf32, kInf32);
+    const int64_t b = G.slice_begin[k], e = G.slice_end[k];
+    const bool past = G.time_limit > 0 && b >= (int64_t)G.time_limit;
+    return make_uint2(past ? G.time_limit : (uint32_t)b, past || e >= (int64_t)kInf32 ? kInf32 : (uint32_t)e);
+  };
+  if (i < n_lut) {
+    const int d = (int)(i / G.lut_nb);
+    const uint64_t t0 = (uint64_t)(i - (int64_t)d * G.lut_nb) << G.lut_shift;
+    const int a = G.slice_ptr[d];
+    int lo = 0, hi = G.slice_ptr[d + 1] - a - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (slice(a + mid).y < t0)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    const_cast<uint32_t *>(G.lut_k)[i] = (uint32_t)lo;
+    const uint2 s = slice(a + lo), n = slice(a + lo + 1);
+    const_cast<uint4 *>(G.lut_w)[i] = make_uint4(s.x, s.y, n.x, n.y);
+    return;
+  }
+  const int64_t k = i - n_lut;
+  if (k <= S) {
+    const uint2 s = slice(k);
+    const_cast<uint32_t *>(G.slice_begin32)[k] = s.x;
+    const_cast<uint32_t *>(G.slice_end32)[k] = s.y;
+    return;
+  }
+  const int64_t v = k - S - 1;
+  if (!G.ready_rec || v >= G.n_ops) return;
+  const int K = G.n_link, s0 = G.succ_ptr[v], n = G.succ_ptr[v + 1] - s0;
+  uint32_t other[2] = {0xFFFFu, 0xFFFFu}, rel[2] = {0, 0}, x[4] = {0, 0, 0, 0};
+  for (int k = 0; k < 2; ++k) {
+    if (k >= n) continue;
+    const int y = G.succ_idx[s0 + k], e0 = G.pred_ptr[y];
+    if (G.pred_ptr[y + 1] - e0 == 2) {
+      const int u = G.pred_idx[e0] == (int)v ? G.pred_idx[e0 + 1] : G.pred_idx[e0];
+      other[k] = (uint32_t)u;
+      x[2 * k] = G.xfer32[(int64_t)u * K];
+      x[2 * k + 1] = G.xfer32[(int64_t)u * K + K - 1];
+    }
+    rel[k] = G.release32[G.op_req[y]];
+  }
+  uint4 *rec = const_cast<uint4 *>(G.ready_rec) + 3 * v;
+  rec[0] = make_uint4(G.n_class == 1 ? G.dur32[v] : 0u, G.xfer32[v * K], G.xfer32[v * K + K - 1], G.succ2[v]);
+  rec[1] = make_uint4(other[0] | other[1] << 16, rel[0], rel[1], (uint32_t)G.op_req[v]);
+  rec[2] = make_uint4(x[0], x[1], x[2], x[3]);
+}
+
 // Fills n words with x.
 __global__ __launch_bounds__(256) void fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t x) {
   uint4 *q = reinterpret_cast<uint4 *>(p);
@@ -2261,6 +2322,12 @@ struct FastPlan {
   size_t sz_pt = 0, sz_fin = 0, sz_row = 0, sz_mark = 0, sz_comp = 0, sz_slots = 0, sz_own = 0, sz_cp = 0, sz_meta = 0, sz_rank = 0, sz_wk = 0, sz_wb = 0, sz_tk = 0,
          total = 0;
 };
+
+hipError_t ss_make_tables(const GmgView &G, int64_t S, hipStream_t stream) {
+  const int64_t n = (int64_t)G.n_dev * G.lut_nb + S + 1 + (G.ready_rec ? G.n_ops : 0);
+  hipLaunchKernelGGL(make_tables, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, G, S);
+  return hipGetLastError();
+}
 
 hipError_t ss_rows_from_op_major(const uint8_t *P, int64_t n_ops, int64_t B, int64_t b0, int64_t nb, uint8_t *rows,
                                  hipStream_t stream) {

@@ -275,6 +275,9 @@ int ss_run_simulate_ports32(const ss_gmg *g, SsPlace P, int64_t *makespan, int64
 size_t ss_ready_schedule_lds(const ss_gmg *g);
 int ss_run_simulate_ready(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak, uint8_t *violation,
                           int64_t *slack, int64_t *sumfin, hipStream_t stream, SsWork &W);
+// Writes a loaded GMG's 32-bit slices (S of them and the spare), lut_k, lut_w
+// and (where it has them) ready_rec from its other tables (sim_fast.hip).
+hipError_t ss_make_tables(const GmgView &G, int64_t S, hipStream_t stream);
 // Candidate rows [nb][n_ops] of candidates [b0, b0 + nb) from op-major
 // placements [n_ops][B] (sim_fast.hip).
 hipError_t ss_rows_from_op_major(const uint8_t *P, int64_t n_ops, int64_t B, int64_t b0, int64_t nb, uint8_t *rows,
