@@ -207,15 +207,24 @@ void launch_group(const ss_est *E, const int64_t *ptr, int64_t S, const double *
 }
 
 // Lanes per estimator from the average samples per estimator of the batch
-// (4 .. 16, so that most lanes have a sample); 32 and 64 only for batches of
-// fewer estimators, whose groups of 16 would leave the chip's waves idle.
+// (4 .. 16, so that most lanes have a sample).  32 and 64 for batches of fewer
+// estimators, whose groups of 16 would leave the chip's waves idle, and the
+// more estimators the longer the sums that outweigh the wider reduction; that
+// grows with the features, so the lines lie at fewer estimators for more of
+// them.  Measured, 16, 32 and 64 lanes in us: 2,048 estimators of three
+// features with 1,000 samples each 26.9, 17.0 and 14.5, with 4,000 129, 66 and
+// 41; 4,096 with 4,000 155, 98 and 93; 6,000 with 1,500 60, 44 and 51; 8,192
+// with 1,500 76, 71 and 73, with 400 19.3, 20.8 and 22.7; of eight features
+// 2,048 with 1,000 39, 32 and 35, 6,000 with 800 66, 69 and 85; of five 8,192
+// with 1,000 73, 76 and 79.
 template <int F>
 void launch_accumulate(const ss_est *E, const int64_t *ptr, int64_t S, const double *x, const double *y,
                        hipStream_t stream) {
   const int64_t avg = S / E->n_est;
-  if (avg >= 48 && E->n_est < 2048)
+  const int64_t n = E->n_est;
+  if (avg >= 48 && (n < 2048 || (avg >= 600 && n * F < 12288) || (avg >= 3000 && n < 6144)))
     launch_group<F, 64>(E, ptr, S, x, y, stream);
-  else if (avg >= 24 && E->n_est < 4096)
+  else if (avg >= 24 && (n < 4096 || (avg >= 1000 && n < 8192 && n * F < 40960) || (avg >= 1500 && n < 12288)))
     launch_group<F, 32>(E, ptr, S, x, y, stream);
   else if (avg >= 12)
     launch_group<F, 16>(E, ptr, S, x, y, stream);

@@ -172,3 +172,36 @@ def test_lane_groups_for_every_batch_density(dev, n_est, hi):
     rc, rs = ref.solve()
     gc, gs = gpu_fit(dev, n_est, F, [(ptr, x, y)])
     assert np.array_equal(gs, rs) and np.allclose(gc, rc, rtol=RTOL, atol=ATOL)
+
+
+@pytest.mark.parametrize("n_est,per,F", [(2047, 48, 2), (2048, 47, 2), (2048, 600, 3), (4095, 30, 3), (4096, 1000, 2),
+                                         (6143, 600, 2), (6144, 600, 2), (4096, 999, 1), (6143, 3000, 1),
+                                         (8191, 1000, 1), (8192, 1000, 1), (8192, 1500, 1), (12287, 1500, 1)])
+def test_lanes_per_estimator(dev, n_est, per, F):
+    """Both sides of the lines between 16, 32 and 64 lanes an estimator: the
+    sums of whole numbers, which every order gives exactly."""
+    gen = torch.Generator("cuda").manual_seed(n_est + per)
+    counts = np.full(n_est, per)
+    counts[::7] -= per // 2
+    counts[1::7] += per // 2
+    ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    S = int(ptr[-1])
+    x = torch.randint(-3, 4, (S, F), generator=gen, device=dev).double()
+    x[:, -1] = 1.0
+    y = torch.randint(-9, 10, (S,), generator=gen, device=dev).double()
+    E = ss.Estimators(n_est, F)
+    E.add(to_dev(ptr, dev), x, y)
+    coef, status = (t.cpu().numpy() for t in E.solve())
+    E.free()
+    ids = torch.repeat_interleave(torch.arange(n_est, device=dev), to_dev(counts, dev), output_size=S)
+    z = torch.cat([x, y[:, None]], 1)
+    sums = torch.zeros((n_est, F, F + 1), dtype=torch.float64, device=dev)
+    for i in range(F):
+        for j in range(F + 1):
+            sums[:, i, j].index_add_(0, ids, z[:, i] * z[:, j])
+    sums = sums.cpu().numpy()
+    assert (status == 0).all()
+    # whole-number sums are exact; the solve of a Gram matrix of condition below
+    # 10 leaves a few rounding steps
+    ref = np.linalg.solve(sums[:, :, :F], sums[:, :, F:])[:, :, 0]
+    assert np.abs(coef - ref).max() <= 1e-12
