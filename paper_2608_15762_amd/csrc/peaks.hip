@@ -29,7 +29,8 @@
 // beyond the placement and finish rows is a two-byte rank and a two-byte gap
 // per op, which stay in the CU's caches.
 //
-// Bound: the latency of each pass over the ops at 16 to 24 waves a CU, then LDS
+// Bound: the latency of each pass over the ops at 16 to 24 waves a CU (fewer on
+// graphs with wide successors whose table nearly fills the LDS), then LDS
 // access.  It takes the place of interval records in global memory, bucketed
 // per device and evaluated one device at a time in a wave of its own, whose
 // fixed cost per device was most of the pass on small graphs; the two passes
@@ -741,7 +742,15 @@ PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_bloc
   int64_t waves = std::min<int64_t>(16, std::max<int64_t>(1, (20 + fit - 1) / fit));
   waves = std::min(waves, (N + 2 * kWave - 1) / (2 * kWave));
   waves = std::max<int64_t>(1, std::min(waves, 2 * acc * n4 / (12 * D)));
-  if (s.csr) waves = std::min(waves, (lds_block - lds) / wave_lds);
+  if (s.csr) {
+    // where the table leaves room for the device arrays of one wave alone, the
+    // records are faster (4,096 candidates of 11,300 ops on 128 devices at
+    // random: 25.8 ms with one wave, 18.5 with records; of 10,000 ops 11.5 with
+    // two waves on 64 devices, 15.8 with records on 128)
+    const int64_t most = (lds_block - lds) / wave_lds;
+    if (most < std::min<int64_t>(waves, 2)) return s;
+    waves = std::min(waves, most);
+  }
   lds += waves * wave_lds;
   s.lds = (size_t)lds;
   s.threads = (int)waves * kWave;

@@ -42,14 +42,45 @@ def test_sizes(n, D, outdeg, dispatch):
     check(*random_case(n + D, n, D, 37, max_outdeg=outdeg), dispatch=dispatch)
 
 
+def in_lds(g, P, dispatch="index"):
+    """Whether the memory pass of a call ran in LDS (no interval records)."""
+    h, A = ss.Gmg(g), torch.from_numpy(P).cuda()
+    torch.cuda.synchronize()
+    ss.kernel_timing(True)
+    ss.simulate_batch(h, A, dispatch=dispatch)
+    torch.cuda.synchronize()
+    n, _ = ss.kernel_time(3)
+    ss.kernel_timing(False)
+    return n == 0
+
+
 @pytest.mark.parametrize("max_bytes", [1000, 1 << 31])  # 32- and 64-bit byte sums
 @pytest.mark.parametrize("step", [-600, -1, 0, 1, 600])
 def test_largest_table(step, max_bytes):
-    """12 (20 with 64-bit sums) bytes an entry, two an op of event list: about
-    11,600 (7,400) ops on three devices fill 160 KB; both sides of it."""
-    n = (11_600 if max_bytes == 1000 else 7_400) + step
+    """12 (20 with 64-bit sums) bytes an entry, two an op of event list: 11,689
+    (7,433) ops on three devices fill 160 KB; both sides of it."""
+    n = (11_689 if max_bytes == 1000 else 7_433) + step
     print(f"{n} ops, sizes up to {max_bytes}", flush=True)
-    check(*random_case(5, n, 3, 6, max_bytes=max_bytes, max_outdeg=2, edge_p=0.1, cap_scale=max_bytes * 100))
+    g, P = random_case(5, n, 3, 6, max_bytes=max_bytes, max_outdeg=2, edge_p=0.1, cap_scale=max_bytes * 100)
+    check(g, P)
+    assert in_lds(g, P) == (step <= 0)
+
+
+@pytest.mark.parametrize("dispatch", ["index", "ready"])
+@pytest.mark.parametrize("D,max_bytes,last", [(3, 1000, 11_685), (128, 1000, 11_256), (255, 1000, 10_821),
+                                              (128, 1 << 31, 7_064)])
+@pytest.mark.parametrize("step", [-90, 0, 1, 40])
+def test_largest_table_with_wide_successors(step, D, max_bytes, last, dispatch):
+    """With device arrays of 12 bytes a device for each wave beside the table:
+    the last size that leaves room for two waves, and one wave's beyond."""
+    n = last + step
+    print(f"{n} ops on {D} devices, sizes up to {max_bytes}, {dispatch}", flush=True)
+    # (links fast enough for the horizon to fit 32 bits)
+    g, P = random_case(6, n, D, 5, max_bytes=max_bytes, bw_max=max_bytes // 20, edge_p=0.2, n_link=3, n_class=2,
+                       cap_scale=max_bytes * 100)
+    assert ss.time_bits(ss.Gmg(g), dispatch=dispatch) == 32
+    check(g, P, dispatch=dispatch)
+    assert in_lds(g, P, dispatch) == (step <= 0)
 
 
 @pytest.mark.parametrize("dispatch", ["index", "ready"])
@@ -133,9 +164,20 @@ def test_horizon_past_32_bits(ahead, outdeg, n_class):
     h = ss.Gmg(g)
     assert ss.time_bits(h) == 64
     ref = oracle.simulate_batch(g, P, n_threads=8)
-    late = ref["makespan"] >= 1 << 32
+    late = (ref["makespan"] >= 1 << 32) & (ref["violation"] != 4)
     print(f"{int(late.sum())} of {len(P)} candidates pass 2^32", flush=True)
+    # a horizon past 2^32 without its 32-bit tables would run no LDS memory pass
+    # beside the int64 one: two memory kernels, the second for marked candidates
+    assert 0 < late.sum() < len(P) - 1
     check(g, P)
+    A = torch.from_numpy(P).cuda()
+    torch.cuda.synchronize()
+    ss.kernel_timing(True)
+    ss.simulate_batch(h, A)
+    torch.cuda.synchronize()
+    n, _ = ss.kernel_time(1)
+    ss.kernel_timing(False)
+    assert n == 2
 
 
 @pytest.mark.parametrize("D,fan", [(3, 127), (40, 130), (255, 600), (64, 2000)])
