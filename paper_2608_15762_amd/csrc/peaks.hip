@@ -734,12 +734,20 @@ PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_bloc
   int64_t lds = n4 * (2 * acc + 4) + s.lds_nodes * 16 + (2 * D + 16) * acc + (D + 1) * 4 + 32;
   const int64_t wave_lds = s.csr ? 12 * D : 0;  // the device arrays of ops with many successors
   if (lds + wave_lds > lds_block) return s;
-  // at least twenty waves per CU where more than one table fits it (100,003
-  // candidates of 2,052 ops 3.6 ms with fifteen, 3.2 with twenty), none with
-  // less than two chunks of 64 ops; the
-  // ranks' counts and masks (12 bytes per wave and device) lie on A and F
-  const int64_t fit = std::max<int64_t>(1, lds_cu / lds);
-  int64_t waves = std::min<int64_t>(16, std::max<int64_t>(1, (20 + fit - 1) / fit));
+  // The waves per CU that the registers allow, in as many workgroups as there
+  // are tables that fit it: 16 with the CSR's 108 registers, so a power of two
+  // each (5,000 ops with wide successors, two tables: 3.5 ms in workgroups of
+  // ten, of which a CU holds one, 2.4 in two of eight); of 24 otherwise at
+  // least twenty (100,003 candidates of 2,052 ops 3.6 ms with fifteen, 3.2 with
+  // twenty).  None with less than two chunks of 64 ops; the ranks' counts and
+  // masks (12 bytes per wave and device) lie on A and F.
+  const int64_t fit = std::max<int64_t>(1, lds_cu / lds), resident = s.csr ? 16 : 24;
+  int64_t waves = 1;
+  if (s.csr) {
+    while (waves * fit < resident) waves *= 2;
+  } else {
+    waves = std::min<int64_t>(16, (20 + fit - 1) / fit);
+  }
   waves = std::min(waves, (N + 2 * kWave - 1) / (2 * kWave));
   waves = std::max<int64_t>(1, std::min(waves, 2 * acc * n4 / (12 * D)));
   if (s.csr) {
@@ -754,7 +762,7 @@ PeaksShape ss_peaks_shape(const ss_gmg *g, bool ports, int cus, int64_t lds_bloc
   lds += waves * wave_lds;
   s.lds = (size_t)lds;
   s.threads = (int)waves * kWave;
-  s.blocks = (int64_t)cus * std::max<int64_t>(1, std::min<int64_t>(lds_cu / lds, 32 / waves));
+  s.blocks = (int64_t)cus * std::max<int64_t>(1, std::min<int64_t>(lds_cu / lds, resident / waves));
   s.node_cap = N + 2 * g->n_edges + 1;
   s.ok = 12 * D * waves <= 2 * acc * n4;
   return s;
