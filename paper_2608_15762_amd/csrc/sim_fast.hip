@@ -738,7 +738,7 @@ size_t ready_schedule_lds(int D, int R) { return (size_t)(3 * D + R + 1 + D) * 4
 constexpr int kLaneSlots = 32;
 constexpr uint32_t kFinUnset = 0xFFFFFFFFu;  // above every finish (the horizon is below 2^32 - 1)
 
-// kPacked (0, 2 or 4): with at most two successors per op (succ2) and at most
+// kPacked (0 or 4): with at most two successors per op (succ2) and at most
 // kPacked predecessors, an op's successors and their predecessors, requests
 // and releases come from the packed per-op fields, all loaded unconditionally
 // (indices clamped, results discarded when unused) so that a step waits for
@@ -847,7 +847,7 @@ __global__ __launch_bounds__(kWave) void ready_lanes(const GmgView G, const uint
         xreq[i] = m_req[xs[i]];
         xrel[i] = m_rel[xs[i]];
         xp01[i] = m_p01[xs[i]];
-        xp23[i] = kPacked > 2 ? m_p23[xs[i]] : 0xFFFFFFFFu;
+        xp23[i] = m_p23[xs[i]];
         xd[i] = prow[xs[i]];
       }
     }
