@@ -369,7 +369,7 @@ def test_select_best_on_tight_memory_workload(dev, batch):
             assert gpu_select(h, got["violation"], got[key], got["slack"], sla, dev) == exp
 
 
-@pytest.mark.parametrize("B", [0, 1, 255, 256, 257, 100_003, 3_000_001])
+@pytest.mark.parametrize("B", [0, 1, 255, 256, 257, 1023, 1025, 8191, 8192, 8193, 100_003, 3_000_001])
 def test_select_best_ties_and_sizes(dev, B):
     g = synth.random_gmg(1, n_ops=4, n_dev=2, n_req=2)
     h = ss.Gmg(g)
