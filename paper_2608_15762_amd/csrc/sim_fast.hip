@@ -2354,13 +2354,13 @@ static void placements_to_op_major(const uint8_t *P, int64_t nb, int64_t N, uint
 // index order; the memory pass takes 40 to 50 us a candidate and workgroup, but
 // a workgroup's scratch is that of seven candidates (mostly its list of every
 // possible event).  A third of the scratch for workgroups is near the least
-// sum of both for 322 to 10,000 ops; the candidates get the rest, in whole
-// `round`s or waves, and the workgroups what that leaves.  In 128 MiB with a
+// sum of both for 322 to 10,000 ops; the candidates get the rest, in equal
+// chunks of whole `round`s or waves, and the workgroups what those leave.  In 128 MiB with a
 // workgroup per candidate and with this split: 4,096 candidates of 10,000 ops
 // 172.8 and 29.0 ms (64.6 with interval records), 16,384 of 2,052 ops 41.3 and
 // 6.5 (22.6), 65,536 of 322 ops 3.9 and 2.0 (4.4).
 template <class PlanOf>
-auto fit_peaks(PlanOf &&plan_of, int64_t max_chunk, int64_t round, const PeaksShape &pk, size_t pk_slot,
+auto fit_peaks(PlanOf &&plan_of, int64_t B, int64_t max_chunk, int64_t round, const PeaksShape &pk, size_t pk_slot,
                int64_t bytes) {
   // the largest x in [lo, hi] whose layout fits; that of lo does
   auto largest = [&](int64_t lo, int64_t hi, auto &&plan) {
@@ -2373,8 +2373,11 @@ auto fit_peaks(PlanOf &&plan_of, int64_t max_chunk, int64_t round, const PeaksSh
   };
   const int64_t share = std::max<int64_t>(1, std::min(pk.blocks, bytes / 3 / (int64_t)pk_slot));
   int64_t chunk = largest(1, max_chunk, [&](int64_t c) { return plan_of(c, share); });
-  if (chunk < max_chunk)  // (one that takes the whole batch stays)
-    chunk = chunk >= round ? chunk / round * round : chunk >= kWave ? chunk / kWave * kWave : chunk;
+  if (chunk < max_chunk) {  // whole units, and as many for each chunk as the last one has
+    const int64_t unit = chunk >= round ? round : chunk >= kWave ? kWave : 1;
+    const int64_t n = (B + chunk / unit * unit - 1) / (chunk / unit * unit);
+    chunk = ((B + n - 1) / n + unit - 1) / unit * unit;
+  }
   return plan_of(chunk, largest(share, pk.blocks, [&](int64_t n) { return plan_of(chunk, n); }));
 }
 
@@ -2485,7 +2488,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
   auto plan_fit = [&](int64_t bytes) {
     if ((int64_t)pref.total <= bytes) return pref;
     if ((int64_t)pmin.total >= bytes) return pmin;
-    if (pk.ok) return fit_peaks(plan_of, pref.chunk, round, pk, pk_slot, bytes);
+    if (pk.ok) return fit_peaks(plan_of, B, pref.chunk, round, pk, pk_slot, bytes);
     int64_t chunk = pref.chunk;
     for (;;) {
       const int64_t lo0 = chunk > kWave ? std::max<int64_t>(1, std::min<int64_t>(pref.sub, chunk / 16)) : 1;
@@ -2742,7 +2745,7 @@ int ss_run_simulate_ready(const ss_gmg *g, SsPlace src, int64_t *makespan, int64
   auto plan_fit = [&](int64_t bytes) {
     if ((int64_t)ppref.total <= bytes) return ppref;
     if ((int64_t)pmin.total >= bytes) return pmin;
-    if (pk.ok) return fit_peaks(plan_of, ppref.chunk, (int64_t)kWave, pk, pk_slot, bytes);
+    if (pk.ok) return fit_peaks(plan_of, B, ppref.chunk, (int64_t)kWave, pk, pk_slot, bytes);
     int64_t chunk = ppref.chunk;
     for (;;) {
       const int64_t lo0 = chunk > kWave ? std::max<int64_t>(1, std::min<int64_t>(ppref.sub, chunk / 16)) : 1;
