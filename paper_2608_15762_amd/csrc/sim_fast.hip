@@ -2355,10 +2355,10 @@ static void placements_to_op_major(const uint8_t *P, int64_t nb, int64_t N, uint
 // a workgroup's scratch is that of seven candidates (mostly its list of every
 // possible event).  A third of the scratch for workgroups is near the least
 // sum of both for 322 to 10,000 ops; the candidates get the rest, in equal
-// chunks of whole `round`s or waves, and the workgroups what those leave.  In 128 MiB with a
-// workgroup per candidate and with this split: 4,096 candidates of 10,000 ops
-// 172.8 and 29.0 ms (64.6 with interval records), 16,384 of 2,052 ops 41.3 and
-// 6.5 (22.6), 65,536 of 322 ops 3.9 and 2.0 (4.4).
+// chunks of whole `round`s or waves, and the workgroups what those leave.  In
+// 128 MiB with a workgroup per candidate and with this split: 4,096 candidates
+// of 10,000 ops 172.8 and 28.4 ms (64.6 with interval records), 16,384 of 2,052
+// ops 41.3 and 6.2 (22.6), 65,536 of 322 ops 3.9 and 1.7 (4.4).
 template <class PlanOf>
 auto fit_peaks(PlanOf &&plan_of, int64_t B, int64_t max_chunk, int64_t round, const PeaksShape &pk, size_t pk_slot,
                int64_t bytes) {
