@@ -2480,7 +2480,9 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     chunk = std::min<int64_t>(chunk, int64_t(65535) * 64);  // transpose grids index 64-candidate tiles in y
     return plan_of(chunk, pk.ok ? pk.blocks : std::max<int64_t>(1, kRecordBudget / std::max<int64_t>(1, rec_per_cand)));
   };
-  const FastPlan pmin = plan_of(1, 1), pref = plan_for_budget(kFastScratchBudget);
+  // (with a time limit the general kernels, a wave per candidate, serve the
+  // workspaces that hold fewer than a schedule wave's candidates)
+  const FastPlan pmin = plan_of(retry ? kWave : 1, 1), pref = plan_for_budget(kFastScratchBudget);
   // the largest layout within `bytes`; with interval records the preferred
   // chunk with sub-chunks as large as fit (down to a sixteenth of the chunk),
   // else smaller chunks (by whole rounds, then halves), down to the smallest

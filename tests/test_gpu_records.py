@@ -113,7 +113,7 @@ def test_events_of_one_gap(copies, mode):
 
 
 @pytest.mark.parametrize("form", [dict(max_outdeg=2), dict(n_class=2)])
-@pytest.mark.parametrize("layout,workspace", [("row", None), ("op", None), ("row", 0.02), ("op", 0.3)])
+@pytest.mark.parametrize("layout,workspace", [("row", None), ("op", None), ("row", 0.2), ("op", 0.5)])
 def test_candidates_past_the_limit(layout, workspace, form):
     """A horizon past 32 bits: candidates that use the device whose windows lie
     there are left to the int64 kernels after the record passes."""
