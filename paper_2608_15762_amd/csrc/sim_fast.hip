@@ -2443,7 +2443,7 @@ int ss_run_simulate_fast(const ss_gmg *g, SsPlace src, int64_t *makespan, int64_
     q.sz_fin = align((size_t)chunk * N * 4 + 4);
     q.sz_row = align((size_t)chunk * pitch * 4 + 4);
     q.sz_mark = retry ? align((size_t)(chunk + 1) * 4) : 0;
-    q.sz_comp = retry && chunk > ss_retry_lanes() ? align((size_t)(chunk * R) * 8 + 8) : 0;
+    q.sz_comp = retry && chunk > ss_retry_lanes(g) ? align((size_t)(chunk * R) * 8 + 8) : 0;
     auto fit_retry = [&](size_t have) {  // have: scratch of the memory pass
       if (!retry) return;
       if (have < retry_slot) q.sz_slots += align(retry_slot - have);

@@ -79,9 +79,6 @@ struct Resume {
   int32_t *cap_cur = nullptr;
 };
 
-// Candidates up to which a wave schedules each, beyond which a lane does (see schedule_wave).
-constexpr int64_t kWaveCandidates = 16384;
-
 __global__ __launch_bounds__(256) void zero_u32(uint32_t *__restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
 }
@@ -110,7 +107,7 @@ __global__ __launch_bounds__(256) void fill_prefix(int64_t *__restrict__ fin, in
 __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const uint8_t *__restrict__ P,
                                                          int64_t nb, int64_t *__restrict__ fin,
                                                          int64_t *__restrict__ comp, const Resume RS,
-                                                         const uint32_t *__restrict__ marked,
+                                                         const uint32_t *__restrict__ marked, int64_t above,
                                                          int64_t *__restrict__ makespan,
                                                          int64_t *__restrict__ sumfin, int64_t *__restrict__ slack,
                                                          uint8_t *__restrict__ violation) {
@@ -121,7 +118,7 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
   uint16_t *cur = reinterpret_cast<uint16_t *>(lds_raw + (size_t)D * kWave * 8);  // [D][64]
   // row i of the scratch: candidate i, or the i-th listed one
   const int64_t i = (int64_t)blockIdx.x * kWave + lane;
-  if (marked && marked[0] <= kWaveCandidates) return;  // left to schedule_wave
+  if (marked && marked[0] <= above) return;  // left to schedule_wave
   if (i >= (marked ? (int64_t)marked[0] : nb)) return;
   const int64_t c = marked ? (int64_t)marked[1 + i] : i;
   const uint8_t *prow = P + c * N;
@@ -224,10 +221,17 @@ __global__ __launch_bounds__(kWave) void schedule_kernel(const GmgView G, const 
 // placed, with finish times and device states in LDS.
 // Bound: the latency of those steps, as many as the chunk's longest chain
 // (about 0.15 us each); a lane per candidate walks every op in dependent global
-// loads, 1 us an op.  Measured, a wave and a lane per candidate: 240 candidates
-// of 2,000 ops of 16 requests 0.21 and 2.03 ms, 4,096 of 2,052 ops of 4
-// requests 0.74 and 2.2 ms; 16,384 of those 2.17 and 2.35 ms, 16,384 of one
-// chain of 322 ops 0.50 and 0.50 ms, beyond which the lanes win.
+// loads, 1 us an op, as long for 16,384 candidates as for one.  Measured, a wave
+// and a lane per candidate: 240 candidates of 2,000 ops of 16 requests 0.21 and
+// 2.03 ms, 4,096 of 2,052 ops of 4 requests 0.74 and 2.2 ms, 16,384 of those 2.17
+// and 2.35 ms; 8,192 of 1,000 ops of 8 requests on eight devices 0.34 to 0.61 and
+// 1.04 ms, 16,384 of those 0.64 to 1.16 and 1.06.  With fewer requests or
+// devices than four, steps place an op or two: 4,000, 8,192 and 16,384
+// candidates of one request of 1,000 ops on one device 0.45 and 0.82, 0.87 and
+// 0.82, 1.66 and 0.83 ms, on 16 devices 0.45 and 1.02, 0.87 and 1.02, 1.66 and 1.03.
+int64_t wave_candidates(const ss_gmg *g) {
+  return std::min(g->n_req, g->n_dev) >= 4 ? 16384 : g->n_dev > 1 ? 8192 : 7168;
+}
 constexpr int64_t kWaveReq = 512;  // requests whose completions fit the LDS beside the devices
 
 struct DevState {  // a device's clock and its current slice
@@ -241,7 +245,8 @@ size_t schedule_wave_lds(int64_t D, int64_t R) {
 __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const uint8_t *__restrict__ P, int64_t nb,
                                                        int64_t *__restrict__ fin, int64_t *__restrict__ comp,
                                                        const Resume RS, const uint32_t *__restrict__ marked,
-                                                       bool any_number, int64_t *__restrict__ makespan, int64_t *__restrict__ sumfin,
+                                                       int64_t most, int64_t *__restrict__ makespan,
+                                                       int64_t *__restrict__ sumfin,
                                                        int64_t *__restrict__ slack,
                                                        uint8_t *__restrict__ violation) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -253,7 +258,7 @@ __global__ __launch_bounds__(kWave) void schedule_wave(const GmgView G, const ui
   int64_t *lfin = lcomp + R;                                   // [64] finish times of the chunk
   int32_t *cur = reinterpret_cast<int32_t *>(lfin + kWave);    // [D]
   const int64_t n_cand = marked ? (int64_t)marked[0] : nb;
-  if (marked && !any_number && n_cand > kWaveCandidates) return;  // left to schedule_kernel
+  if (marked && n_cand > most) return;  // left to schedule_kernel
   // row i of the scratch: candidate i, or the i-th listed one
   for (int64_t i = blockIdx.x; i < n_cand; i += gridDim.x) {
     __syncthreads();  // the candidate before has been written
@@ -1465,14 +1470,14 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
         hipLaunchKernelGGL(port_event_schedule, dim3((unsigned)nb), dim3(kWave), sched_lds, stream, G, Pc, nb, fin,
                            arr, lists, pend, E + 1, makespan + b0, sumfin ? sumfin + b0 : nullptr,
                            slack ? slack + b0 * R : nullptr, violation + b0);
-      } else if (nb <= kWaveCandidates && R <= kWaveReq) {
+      } else if (nb <= wave_candidates(g) && R <= kWaveReq) {
         hipLaunchKernelGGL(schedule_wave, dim3((unsigned)nb), dim3(kWave), schedule_wave_lds(D, R), stream, G, Pc, nb,
-                           fin, comp, RS, static_cast<const uint32_t *>(nullptr), false, makespan + b0, sumfin ? sumfin + b0 : nullptr,
-                           slack ? slack + b0 * R : nullptr, violation + b0);
+                           fin, comp, RS, static_cast<const uint32_t *>(nullptr), nb, makespan + b0,
+                           sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr, violation + b0);
       } else {
         hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave),
-                           sched_lds, stream, G, Pc, nb, fin, comp, RS, static_cast<const uint32_t *>(nullptr), makespan + b0,
-                           sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr, violation + b0);
+                           sched_lds, stream, G, Pc, nb, fin, comp, RS, static_cast<const uint32_t *>(nullptr), nb,
+                           makespan + b0, sumfin ? sumfin + b0 : nullptr, slack ? slack + b0 * R : nullptr, violation + b0);
       }
       if (capture) {  // one candidate: its finish times and request completions
         err = hipMemcpyAsync(capture->fin, fin, (size_t)N * 8, hipMemcpyDeviceToDevice, stream);
@@ -1521,7 +1526,7 @@ static int run_simulate_generic(const ss_gmg *g, SsPlace src, int64_t *makespan,
   return rc;
 }
 
-int64_t ss_retry_lanes() { return kWaveCandidates; }
+int64_t ss_retry_lanes(const ss_gmg *g) { return wave_candidates(g); }
 
 // Few candidates of a chunk are marked as a rule: 16 waves for each, except on
 // so few devices that most of them would idle.
@@ -1550,7 +1555,8 @@ int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked
   auto *bydev = reinterpret_cast<int32_t *>(take((size_t)N * 4));
   auto *gkeys = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
   auto *gvals = reinterpret_cast<int64_t *>(take((size_t)slot_cap * 8));
-  const bool lanes = nb > kWaveCandidates && comp;
+  const int64_t most = wave_candidates(g);
+  const bool lanes = nb > most && comp;
   const int64_t mw = retry_waves(g, cus, nb);
   const size_t lane_lds = (size_t)D * kWave * (sizeof(int64_t) + sizeof(uint16_t));
   hipError_t err = hipSuccess;
@@ -1571,10 +1577,10 @@ int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked
                      stream, static_cast<const uint8_t *>(violation), nb, marked);
   hipLaunchKernelGGL(schedule_wave, dim3((unsigned)std::min<int64_t>(nb, (int64_t)cus * 16)), dim3(kWave),
                      schedule_wave_lds(D, R), stream, G, P, nb, rows, static_cast<int64_t *>(nullptr), Resume(),
-                     static_cast<const uint32_t *>(marked), !lanes, makespan, sumfin, slack, violation);
+                     static_cast<const uint32_t *>(marked), lanes ? most : nb, makespan, sumfin, slack, violation);
   if (lanes)
     hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)((nb + kWave - 1) / kWave)), dim3(kWave), lane_lds, stream, G,
-                       P, nb, rows, comp, Resume(), static_cast<const uint32_t *>(marked), makespan, sumfin, slack,
+                       P, nb, rows, comp, Resume(), static_cast<const uint32_t *>(marked), most, makespan, sumfin, slack,
                        violation);
   ss_timing_stop(t, stream);
   err = hipGetLastError();

@@ -240,9 +240,9 @@ int ss_run_simulate(const ss_gmg *g, SsPlace P, int64_t *makespan, int64_t *peak
 // The candidates marked SS_VIOLATION_RETRY of a chunk of nb (placement rows P),
 // simulated by the general index-order kernels.  marked: nb + 1 words, the
 // first of them zero; rows: int64 finish times [nb][n_ops]; comp: [n_req][nb]
-// int64 for chunks past ss_retry_lanes() candidates, else null; slots: scratch
+// int64 for chunks past ss_retry_lanes(g) candidates, else null; slots: scratch
 // of n_slots workgroups of the memory pass.
-int64_t ss_retry_lanes();
+int64_t ss_retry_lanes(const ss_gmg *g);
 int64_t ss_retry_blocks(const ss_gmg *g, int cus, int64_t nb);  // workgroups the memory pass is best given
 size_t ss_retry_slot_bytes(const ss_gmg *g);
 int ss_run_retry(const ss_gmg *g, const uint8_t *P, int64_t nb, uint32_t *marked, int64_t *rows, int64_t *comp,

@@ -1,6 +1,7 @@
 """The general (int64) kernels where their variants meet: the schedule with a
-wave per candidate and with a lane per candidate (up to 16,384 candidates and
-512 requests, and beyond), its 64-op chunks, inputs from the same chunk, and
+wave per candidate and with a lane per candidate (up to 16,384 candidates, 8,192
+with fewer than four requests or devices, 7,168 on one device, and 512 requests,
+and beyond), its 64-op chunks, inputs from the same chunk, and
 the memory pass's three ways to hold a device's endpoints (a wave's share of
 the LDS, all of it, the global buffer).  Bit-exact against the oracle."""
 import numpy as np
@@ -41,15 +42,15 @@ def batch(g, B, seed=0):
     return P
 
 
-@pytest.mark.parametrize("B", [1, 16384, 16385])
+@pytest.mark.parametrize("B,n_req", [(1, 3), (8192, 3), (8193, 3), (16384, 3), (16384, 4), (16385, 4)])
 @pytest.mark.parametrize("snapshot", [False, True])
-def test_batch_sizes(B, snapshot):
-    print(f"{B} candidates, snapshot {snapshot}", flush=True)
-    g = graph(3, 130)
+def test_batch_sizes(B, n_req, snapshot):
+    print(f"{B} candidates, {n_req} requests, snapshot {snapshot}", flush=True)
+    g = graph(3, 130, n_req=n_req)
     check(synth.random_snapshot(g, 5, done_p=0.5) if snapshot else g, batch(g, B) if B > 1 else batch(g, 2)[:1])
 
 
-@pytest.mark.parametrize("B", [40, 16400])
+@pytest.mark.parametrize("B", [40, 8195, 16400])
 def test_resumed(B):
     """Candidates resumed after a prefix that ends inside a chunk."""
     print(f"{B} candidates resumed", flush=True)
@@ -102,3 +103,9 @@ def test_team_sizes(n, D, B):
     P = batch(g, B)
     P[::3] = D - 1
     check(g, P)
+
+
+@pytest.mark.parametrize("B", [7168, 7169])
+def test_one_device(B):
+    g = graph(13, 70, D=1)
+    check(g, batch(g, B))
